@@ -41,6 +41,11 @@ Colony carve(char* base, const Layout& L, const aco_params& p, bool with_delta, 
 // initialisation kernels (nearest-neighbour tour, tau0, tau and choice fill).
 hipError_t upload_and_init(const Colony& col, const int32_t* dist_host, size_t base_bytes,
                            hipStream_t stream);
+// `rows` rows of row_bytes bytes, `pitch` bytes apart on the device, to dst
+// (host, contiguous).  Blocking.
+hipError_t read_rows(void* dst, size_t row_bytes, const void* src, size_t pitch, size_t rows);
+// Best-so-far tour (n + 1 cities) and length; either pointer may be null.
+hipError_t read_best(const Colony& col, uint16_t* tour_host, int64_t* len_host);
 // Compute units and LDS bytes per compute unit of the current device.
 hipError_t device_shape(int* cus, size_t* lds_per_cu);
 // Construction shape table: tile (cities per lane) and wavefronts per ant by n.

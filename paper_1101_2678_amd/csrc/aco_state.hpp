@@ -77,6 +77,9 @@ hipError_t launch_update_gather(const Colony& c, hipStream_t s);
 // edge of a row's workgroup); false: one global atomic per tour edge.
 hipError_t launch_update_atomic(const Colony& c, bool combine_in_lds, hipStream_t s);
 hipError_t launch_init(const Colony& c, hipStream_t s);
+// n rows of n 4-byte words (contiguous at src) to rows of pitch ld at dst; the
+// padding columns become 0.  src and dst must not overlap.
+hipError_t launch_pad_rows(const uint32_t* src, uint32_t* dst, int n, int ld, hipStream_t s);
 hipError_t launch_refresh_choice(const Colony& c, hipStream_t s);
 hipError_t launch_test_select(int tile, int n, int count, const float* rows,
                               const uint8_t* feasible, const float* u, int32_t* out,

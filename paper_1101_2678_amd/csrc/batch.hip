@@ -298,11 +298,7 @@ aco_status aco_batch_read_best(aco_batch* b, int32_t q, uint16_t* best_tour_host
                                int64_t* best_len_host) {
     const aco::Colony* c;
     if (aco_status s = batch_instance(b, q, &c)) return s;
-    hipError_t e = hipSuccess;
-    if (best_len_host) e = hipMemcpy(best_len_host, c->best_len, sizeof(int64_t), hipMemcpyDeviceToHost);
-    if (e == hipSuccess && best_tour_host)
-        e = hipMemcpy(best_tour_host, c->best_tour, ((size_t)c->n + 1) * sizeof(uint16_t),
-                      hipMemcpyDeviceToHost);
+    const hipError_t e = aco::host::read_best(*c, best_tour_host, best_len_host);
     if (e != hipSuccess) return batch_device_fail(b, e, "aco_batch_read_best");
     return ACO_OK;
 }
@@ -312,9 +308,8 @@ aco_status aco_batch_read_tours(aco_batch* b, int32_t q, uint16_t* tours_host, i
     if (aco_status s = batch_instance(b, q, &c)) return s;
     hipError_t e = hipSuccess;
     if (tours_host)
-        e = hipMemcpy2D(tours_host, ((size_t)c->n + 1) * sizeof(uint16_t), c->tours,
-                        (size_t)c->tp * sizeof(uint16_t), ((size_t)c->n + 1) * sizeof(uint16_t),
-                        (size_t)c->m, hipMemcpyDeviceToHost);
+        e = aco::host::read_rows(tours_host, ((size_t)c->n + 1) * sizeof(uint16_t), c->tours,
+                                 (size_t)c->tp * sizeof(uint16_t), (size_t)c->m);
     if (e == hipSuccess && lens_host)
         e = hipMemcpy(lens_host, c->lens, (size_t)c->m * sizeof(int64_t), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return batch_device_fail(b, e, "aco_batch_read_tours");
@@ -326,8 +321,8 @@ aco_status aco_batch_read_tau(aco_batch* b, int32_t q, float* tau_host) {
     if (aco_status s = batch_instance(b, q, &c)) return s;
     if (!tau_host) return fail(ACO_ERR_INVALID, "tau_host is NULL");
     const hipError_t e =
-        hipMemcpy2D(tau_host, (size_t)c->n * sizeof(float), c->tau, (size_t)c->ld * sizeof(float),
-                    (size_t)c->n * sizeof(float), (size_t)c->n, hipMemcpyDeviceToHost);
+        aco::host::read_rows(tau_host, (size_t)c->n * sizeof(float), c->tau,
+                             (size_t)c->ld * sizeof(float), (size_t)c->n);
     if (e != hipSuccess) return batch_device_fail(b, e, "aco_batch_read_tau");
     return ACO_OK;
 }

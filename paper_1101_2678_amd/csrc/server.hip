@@ -372,11 +372,7 @@ aco_status aco_server_result(aco_server* s, int32_t slot, uint16_t* best_tour_ho
     if (slot < 0 || slot >= (int32_t)s->slots.size() || s->slots[slot].state != kDone)
         return fail(ACO_ERR_STATE, "slot holds no finished request");
     const aco::Colony& c = s->slots[slot].col;
-    hipError_t e = hipSuccess;
-    if (best_len_host) e = hipMemcpy(best_len_host, c.best_len, sizeof(int64_t), hipMemcpyDeviceToHost);
-    if (e == hipSuccess && best_tour_host)
-        e = hipMemcpy(best_tour_host, c.best_tour, ((size_t)c.n + 1) * sizeof(uint16_t),
-                      hipMemcpyDeviceToHost);
+    const hipError_t e = aco::host::read_best(c, best_tour_host, best_len_host);
     if (e != hipSuccess) return server_fail(s, e, "aco_server_result");
     return ACO_OK;
 }
@@ -388,8 +384,8 @@ aco_status aco_server_read_tau(aco_server* s, int32_t slot, float* tau_host) {
     if (!tau_host) return fail(ACO_ERR_INVALID, "tau_host is NULL");
     const aco::Colony& c = s->slots[slot].col;
     const hipError_t e =
-        hipMemcpy2D(tau_host, (size_t)c.n * sizeof(float), c.tau, (size_t)c.ld * sizeof(float),
-                    (size_t)c.n * sizeof(float), (size_t)c.n, hipMemcpyDeviceToHost);
+        aco::host::read_rows(tau_host, (size_t)c.n * sizeof(float), c.tau,
+                             (size_t)c.ld * sizeof(float), (size_t)c.n);
     if (e != hipSuccess) return server_fail(s, e, "aco_server_read_tau");
     return ACO_OK;
 }

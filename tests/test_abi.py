@@ -103,6 +103,22 @@ def test_init_rejects_invalid_input_before_device(aco):
     assert aco.lib.aco_init(None, None, None, None, 0, None) == aco.ACO_ERR_INVALID
 
 
+@pytest.mark.parametrize("n,i,j", [(3, 0, 2), (64, 0, 63), (65, 0, 64), (65, 63, 64),
+                                   (130, 64, 129), (130, 127, 128), (200, 199, 198)])
+def test_distance_faults_on_tile_edges(aco, n, i, j):
+    """The distances are checked by 64 x 64 tiles: a fault in the first, last
+    or edge cell of a tile is refused, with the first rule broken in row order."""
+    _, d = tsp_inputs.instance(n, "uniform", side=10_000, seed=2)
+    P = aco.Params(n, 5, 1, 2, 0.5, 1)
+    for cells, message in (([(i, j)], b"symmetric"), ([(j, i)], b"symmetric"),
+                           ([(i, j), (j, i)], b">= 1"), ([(j, j)], b"diagonal")):
+        bad = d.copy()
+        for a, b in cells:
+            bad[a, b] = bad[a, b] + 1 if message == b"symmetric" else 1 if a == b else 0
+        assert _init(aco, P, bad)[0] == aco.ACO_ERR_INVALID
+        assert message in aco.lib.aco_last_error()
+
+
 def test_calls_on_null_context(aco):
     assert aco.lib.aco_construct(None, 0) == aco.ACO_ERR_INVALID
     assert aco.lib.aco_update(None, 0) == aco.ACO_ERR_INVALID
