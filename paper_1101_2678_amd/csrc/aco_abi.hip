@@ -19,6 +19,7 @@
 #include "aco_state.hpp"
 #include "nn.hpp"
 #include "product.hpp"
+#include "shortlist.hpp"
 
 
 namespace aco {
@@ -97,6 +98,7 @@ Layout make_layout(const aco_params& p) {
     L.cnn = take(sizeof(int64_t));
     L.tau0 = take(sizeof(float));
     L.iter = take(sizeof(uint32_t));
+    L.lists = take((size_t)p.n * kListLanes * sizeof(uint64_t));
     L.base_end = off;
     L.delta = take(cells * sizeof(double));
     L.atomic_end = off;
@@ -215,6 +217,7 @@ Colony carve(char* base, const Layout& L, const aco_params& p, bool with_delta, 
     col.cnn = reinterpret_cast<int64_t*>(base + L.cnn);
     col.tau0 = reinterpret_cast<float*>(base + L.tau0);
     col.iter_dev = reinterpret_cast<uint32_t*>(base + L.iter);
+    col.lists = reinterpret_cast<uint64_t*>(base + L.lists);
     col.delta = with_delta ? reinterpret_cast<double*>(base + L.delta) : nullptr;
     col.tile = tile;
     col.waves = waves;

@@ -10,12 +10,16 @@
 // (step, ant, iter, 1 + j / 4), key = seed: one Philox block serves four
 // consecutive cities.
 //
-// One wavefront per ant; in pass p lane l holds cities 512 p + 8 l .. +7 (two
-// 16-byte loads of the choice row, two Philox blocks).  All loads of a step
+// One wavefront per ant.  A step draws for the 63 largest entries of the row
+// first (one Philox block a lane, 512 bytes read): a winner above the largest
+// entry of the rest is the winner of the whole row, and nearly every step
+// ends there, bound by the latency of that chain.  Otherwise the wave reads
+// the whole row; in pass p lane l holds cities 512 p + 8 l .. +7 (two 16-byte
+// loads of the choice row, two Philox blocks).  All loads of such a step
 // are issued before the first Philox block is computed, so the row streams
-// while the vector unit generates the draws; per step the kernel does n / 4
-// Philox blocks per ant and reads 4n bytes, which makes it bound by integer
-// multiply throughput rather than by memory.  Each lane keeps only the
+// while the vector unit generates the draws; it does n / 4 Philox blocks and
+// reads 4n bytes, which makes it bound by integer multiply throughput rather
+// than by memory.  Each lane keeps only the
 // largest product key of each pass (one max per city); a DPP reduction gives
 // the wave's largest key, a ballot per pass finds the lowest pass and lane
 // holding it, and that lane's lowest position holding it gives the city.
@@ -24,6 +28,7 @@
 #include "aco_device.hpp"
 #include "aco_state.hpp"
 #include "product.hpp"
+#include "shortlist.hpp"
 
 namespace aco {
 namespace {
@@ -117,32 +122,23 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
 
-// Layout of a row over the W wavefronts of an ant: in pass p, lane l of wave
-// w holds cities 512 p + 64 GW w + GW l .. + GW - 1 with GW = 8 / W cities per
-// lane, so every 512-city pass is split evenly between the waves and each
-// lane's cities are GW / 4 whole Philox blocks.
-template <int W>
-struct Lay {
-    static_assert(W == 1 || W == 2, "one or two wavefronts per ant");
-    static constexpr int GW = kG / W;
-    __device__ static constexpr int city(int p, int w, int lane, int e) {
-        return kPass * p + 64 * GW * w + GW * lane + e;
-    }
-};
+// City e of lane `lane` in pass p; a lane's cities of a pass are whole Philox
+// blocks.
+__device__ constexpr int city_of(int p, int lane, int e) { return kPass * p + kG * lane + e; }
 
-// Draws of one step from Philox for lane `lane` of wave w: block 1 + q + b
+// Draws of one step from Philox for lane `lane`: block 1 + q + b
 // holds cities 4 (q + b) .. + 3 (q = first city / 4).
 struct PhiloxDraws {
     uint32_t k0, k1, step, ant, iter;
-    template <int P, int W>
-    __device__ __forceinline__ void get_all(int w, int lane, float (&r)[P][Lay<W>::GW]) const {
-        constexpr int B = Lay<W>::GW / 4;  // blocks per lane per pass
+    template <int P>
+    __device__ __forceinline__ void get_all(int lane, float (&r)[P][kG]) const {
+        constexpr int B = kG / 4;  // blocks per lane per pass
         uint32_t ctr[B * P];
 #pragma unroll
         for (int p = 0; p < P; ++p)
 #pragma unroll
             for (int b = 0; b < B; ++b)
-                ctr[B * p + b] = 1u + (uint32_t)Lay<W>::city(p, w, lane, 0) / 4u + (uint32_t)b;
+                ctr[B * p + b] = 1u + (uint32_t)city_of(p, lane, 0) / 4u + (uint32_t)b;
         u32x4 x[B * P];
         philox4_many<B * P>(k0, k1, step, ant, iter, ctr, x);
 #pragma unroll
@@ -158,13 +154,13 @@ struct PhiloxDraws {
 struct ArrayDraws {
     const float* u;
     int n;
-    template <int P, int W>
-    __device__ __forceinline__ void get_all(int w, int lane, float (&r)[P][Lay<W>::GW]) const {
+    template <int P>
+    __device__ __forceinline__ void get_all(int lane, float (&r)[P][kG]) const {
 #pragma unroll
         for (int p = 0; p < P; ++p)
 #pragma unroll
-            for (int e = 0; e < Lay<W>::GW; ++e) {
-                const int j = Lay<W>::city(p, w, lane, e);
+            for (int e = 0; e < kG; ++e) {
+                const int j = city_of(p, lane, e);
                 r[p][e] = j < n ? u[j] : 0.0f;
             }
     }
@@ -179,7 +175,7 @@ __device__ __forceinline__ uint32_t bit_mask(uint32_t bits, int e) {
     return m;
 }
 
-// One wave's share of the selection: bit GW p + e of `bits` says whether the
+// One selection over a whole row: bit kG p + e of `bits` says whether the
 // lane's city e of pass p may be chosen.  Products of finite non-negative
 // values are finite and non-negative, so their bit patterns order like the
 // values; a city that may not be chosen gets key 0.  Returns the wave's
@@ -190,11 +186,10 @@ struct Pick {
     uint32_t key, city;
 };
 
-template <int P, int W, typename Draws>
+template <int P, typename Draws>
 __device__ __forceinline__ Pick product_pick(const float* row, int n, uint64_t bits,
-                                             const Draws& draws, int w, int lane) {
-    constexpr int GW = Lay<W>::GW;
-    constexpr int L = GW / 4;  // 16-byte loads per lane per pass
+                                             const Draws& draws, int lane) {
+    constexpr int L = kG / 4;  // 16-byte loads per lane per pass
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float*>(row), (short)0, ((n + 3) & ~3) * 4, 0x00020000);
     u32x4 wv[P][L];
@@ -203,19 +198,19 @@ __device__ __forceinline__ Pick product_pick(const float* row, int n, uint64_t b
 #pragma unroll
         for (int b = 0; b < L; ++b)
             wv[p][b] = __builtin_amdgcn_raw_buffer_load_b128(
-                rs, (Lay<W>::city(p, w, lane, 0) + 4 * b) * 4, 0, 0);
+                rs, (city_of(p, lane, 0) + 4 * b) * 4, 0, 0);
     // every row load above is in flight before the first draw is computed
     __builtin_amdgcn_sched_barrier(0);
-    float r[P][GW];
-    draws.template get_all<P, W>(w, lane, r);
-    uint32_t key[P][GW], pmax[P];
+    float r[P][kG];
+    draws.template get_all<P>(lane, r);
+    uint32_t key[P][kG], pmax[P];
     uint32_t lmax = 0;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
-        const uint32_t pass_bits = (uint32_t)(bits >> (GW * p));
+        const uint32_t pass_bits = (uint32_t)(bits >> (kG * p));
         uint32_t m = 0;
 #pragma unroll
-        for (int e = 0; e < GW; ++e) {
+        for (int e = 0; e < kG; ++e) {
             const float prod = __uint_as_float(wv[p][e / 4][e % 4]) * r[p][e];
             key[p][e] = __float_as_uint(prod) & bit_mask(pass_bits, e);
             m = max(m, key[p][e]);
@@ -234,162 +229,152 @@ __device__ __forceinline__ Pick product_pick(const float* row, int n, uint64_t b
                 const int src = __builtin_ctzll(hold);
                 uint32_t first = 0;
 #pragma unroll
-                for (int e = GW - 1; e >= 0; --e) first = key[p][e] == top ? (uint32_t)e : first;
+                for (int e = kG - 1; e >= 0; --e) first = key[p][e] == top ? (uint32_t)e : first;
                 const int e = __builtin_amdgcn_readlane((int)first, src);
                 // wave-uniform; said so, or the next row's address is taken
                 // as per-lane and every load of it becomes a loop
-                const int city = __builtin_amdgcn_readfirstlane(Lay<W>::city(p, w, src, e));
+                const int city = __builtin_amdgcn_readfirstlane(city_of(p, src, e));
                 return Pick{top, (uint32_t)city};
             }
         }
     }
-    // No positive product: the lowest city that may be chosen.  Bit GW p + e
+    // No positive product: the lowest city that may be chosen.  Bit kG p + e
     // grows with the city inside a lane.
     uint32_t low = ~0u;
     if (bits) {
         const int b = __builtin_ctzll(bits);
-        low = (uint32_t)Lay<W>::city(b / GW, w, lane, b % GW);
+        low = (uint32_t)city_of(b / kG, lane, b % kG);
     }
     return Pick{0u, wave_min_u32(low)};
 }
 
+// The selection from the row's short list alone (v: the lane's entry), or -1
+// where it needs the whole row.  s_vis: visited bits of city j in bit j mod 32
+// of word j / 32.  A city off the list has a choice value of at most M, its
+// tail's largest, and draws r < 1, so its product, rounded, is at most M: a
+// listed unvisited city whose product exceeds M beats them all, and the list
+// is in city order, so the lowest lane holding the largest product is the
+// lowest city.  One Philox block a lane instead of two per pass.
+__device__ __forceinline__ int product_list_pick(u32x2 v, const uint32_t* s_vis, uint32_t k0,
+                                                 uint32_t k1, uint32_t step, uint32_t ant,
+                                                 uint32_t iter, int lane) {
+    const int city = list_city(v.y);
+    const uint32_t visited = s_vis[city >> 5];
+    const uint32_t ctr[1] = {1u + (uint32_t)city / 4u};
+    u32x4 x[1];
+    philox4_many<1>(k0, k1, step, ant, iter, ctr, x);
+    const uint32_t lo = city & 1 ? x[0].y : x[0].x, hi = city & 1 ? x[0].w : x[0].z;
+    const float prod = __uint_as_float(v.x) * unit24(city & 2 ? hi : lo);
+    const bool may = lane < kListEntries && ((visited >> (city & 31)) & 1u) == 0u;
+    const uint32_t key = may ? __float_as_uint(prod) : 0u;
+    const uint32_t top = wave_max_u32(key);
+    const uint32_t rest = (uint32_t)__builtin_amdgcn_readlane((int)v.x, kListEntries);
+    if (top <= rest) return -1;
+    const int src = __builtin_ctzll(ballot(key == top));
+    return __builtin_amdgcn_readlane(city, src);
+}
+
 // Feasibility bits of a fresh tour: cities < n.
-template <int P, int W>
-__device__ __forceinline__ uint64_t initial_bits(int n, int w, int lane) {
+template <int P>
+__device__ __forceinline__ uint64_t initial_bits(int n, int lane) {
     uint64_t bits = 0;
 #pragma unroll
     for (int p = 0; p < P; ++p)
 #pragma unroll
-        for (int e = 0; e < Lay<W>::GW; ++e)
-            if (Lay<W>::city(p, w, lane, e) < n) bits |= 1ull << (Lay<W>::GW * p + e);
+        for (int e = 0; e < kG; ++e)
+            if (city_of(p, lane, e) < n) bits |= 1ull << (kG * p + e);
     return bits;
 }
 
-// Clears city j's bit in the lane (of the wave) that holds it.
-template <int W>
-__device__ __forceinline__ void mark_visited(int j, int w, int lane, uint64_t& bits) {
-    constexpr uint32_t GW = Lay<W>::GW;
+// Clears city j's bit in the lane that holds it.
+__device__ __forceinline__ void mark_visited(int j, int lane, uint64_t& bits) {
     // j >= 0: unsigned, so the divisions are shifts and masks
     const uint32_t uj = (uint32_t)j;
-    const uint32_t p = uj / kPass, rem = uj - p * kPass;
-    const uint32_t jw = rem / (64 * GW), r2 = rem - jw * 64 * GW;
-    if ((int)jw == w && (int)(r2 / GW) == lane) bits &= ~(1ull << (GW * p + r2 % GW));
+    const uint32_t p = uj / kPass, rem = uj % kPass;
+    if ((int)(rem / kG) == lane) bits &= ~(1ull << (kG * p + rem % kG));
 }
 
-// Wavefronts per ant of the construction kernel (and of its verification
-// entry point).  Two waves per ant double the waves a SIMD can switch
-// between but measured no faster: the kernel is bound by the instructions
-// it issues (draws and per-city selection), which the split does not
-// reduce, so one wave per ant, without a per-step barrier, is the default.
-constexpr int kWaves = 1;
-
 template <int P>
-__global__ __launch_bounds__(64 * kWaves) void k_construct_product(Colony c, uint32_t iter) {
+__global__ __launch_bounds__(64) void k_construct_product(Colony c, uint32_t iter) {
     extern __shared__ __align__(16) unsigned char smem[];
     uint16_t* s_tour = reinterpret_cast<uint16_t*>(smem);
-    __shared__ uint32_t s_key[2][kWaves], s_city[2][kWaves];
-    __shared__ long long s_len[kWaves];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    __shared__ uint32_t s_vis[kMaxCities / 32];
+    const int lane = threadIdx.x;
     const int k = ant_of_block(blockIdx.x, c.m);
     const int n = c.n;
     const PhiloxKey key{(uint32_t)c.seed, (uint32_t)(c.seed >> 32)};
+    const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
 
-    uint64_t bits = initial_bits<P, kWaves>(n, w, lane);
+    uint64_t bits = initial_bits<P>(n, lane);
+    uint64_t block_bits = 0;  // visited cities of block `lane`, kept in s_vis for the lists
     const uint32_t x0 = draw(key, iter, (uint32_t)k, 0u);
     int cur = (int)(((uint64_t)x0 * (uint64_t)(uint32_t)n) >> 32);
-    if (tid == 0) s_tour[0] = (uint16_t)cur;
-    mark_visited<kWaves>(cur, w, lane, bits);
 
+    // A step reads its city's short list first and the whole row only where
+    // the list does not settle the selection.  Whole rows only -> lists, mean
+    // of 20 iterations with m = n: n = 2400 8.56 -> 1.41 ms, n = 1000 0.816 ->
+    // 0.403 ms, n = 333 0.177 -> 0.136 ms, n = 100 0.0546 -> 0.0472 ms (with
+    // the launch that builds the lists, 4 to 15 us).
     for (int step = 1; step < n; ++step) {
-        const PhiloxDraws draws{key.k0, key.k1, (uint32_t)step, (uint32_t)k, iter};
-        const Pick mine = product_pick<P, kWaves>(c.choice + (size_t)cur * c.ld, n, bits, draws,
-                                                  w, lane);
-        int next;
-        if constexpr (kWaves == 1) {
-            next = mine.city == ~0u ? -1 : (int)mine.city;
-        } else {
-            // winners of both waves, double-buffered by step parity: a wave
-            // can rewrite a slot only after passing the next barrier, which
-            // the other wave reaches only after reading it
-            const int par = step & 1;
-            if (lane == 0) {
-                s_key[par][w] = mine.key;
-                s_city[par][w] = mine.city;
-            }
-            __syncthreads();
-            const uint32_t k0 = s_key[par][0], k1 = s_key[par][1];
-            const uint32_t top = k0 > k1 ? k0 : k1;
-            const uint32_t c0 = k0 == top ? s_city[par][0] : ~0u;
-            const uint32_t c1 = k1 == top ? s_city[par][1] : ~0u;
-            const uint32_t j = c0 < c1 ? c0 : c1;
-            next = j == ~0u ? -1 : (int)j;
+        const u32x2 entry = load_list(lists, cur, lane);
+        if (lane == 0) s_tour[step - 1] = (uint16_t)cur;
+        mark_visited(cur, lane, bits);
+        if (lane == (cur >> 6)) block_bits |= 1ull << (cur & 63);
+        s_vis[2 * lane] = (uint32_t)block_bits;
+        s_vis[2 * lane + 1] = (uint32_t)(block_bits >> 32);
+        int next = product_list_pick(entry, s_vis, key.k0, key.k1, (uint32_t)step, (uint32_t)k,
+                                     iter, lane);
+        if (next < 0) {
+            const PhiloxDraws draws{key.k0, key.k1, (uint32_t)step, (uint32_t)k, iter};
+            const uint32_t j =
+                product_pick<P>(c.choice + (size_t)cur * c.ld, n, bits, draws, lane).city;
+            // n - step >= 1 cities are unvisited, so there is one; the clamp
+            // only keeps the LDS index in range should that ever break.
+            next = j == ~0u ? 0 : (int)j;
         }
-        // n - step >= 1 cities are unvisited, so next >= 0; the clamp only
-        // keeps the LDS index in range should that ever break.
-        next = next < 0 ? 0 : next;
-        if (tid == 0) s_tour[step] = (uint16_t)next;
-        mark_visited<kWaves>(next, w, lane, bits);
         cur = next;
     }
+    if (lane == 0) s_tour[n - 1] = (uint16_t)cur;
     __syncthreads();
-    if (tid == 0) s_tour[n] = s_tour[0];
+    if (lane == 0) s_tour[n] = s_tour[0];
     __syncthreads();
 
     // Tour length C^k (int64), deposit fl32(1/C^k), tour and neighbour tables.
     long long len = 0;
-    for (int s = tid; s < n; s += 64 * kWaves) {
+    for (int s = lane; s < n; s += 64) {
         const int i = s_tour[s], j = s_tour[s + 1];
         len += c.dist[(size_t)i * c.ld + j];
         c.succ[(size_t)i * c.mp + k] = (uint16_t)j;
         c.pred[(size_t)j * c.mp + k] = (uint16_t)i;
     }
     uint16_t* trow = c.tours + (size_t)k * c.tp;
-    for (int s = tid; s <= n; s += 64 * kWaves) trow[s] = s_tour[s];
+    for (int s = lane; s <= n; s += 64) trow[s] = s_tour[s];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) len += __shfl_xor(len, off);
-    if (lane == 0) s_len[w] = len;
-    __syncthreads();
-    if (tid == 0) {
-        long long total = 0;
-#pragma unroll
-        for (int v = 0; v < kWaves; ++v) total += s_len[v];
-        c.lens[k] = total;
-        c.dep[k] = (float)(1.0 / (double)total);
+    if (lane == 0) {
+        c.lens[k] = len;
+        c.dep[k] = (float)(1.0 / (double)len);
     }
 }
 
 template <int P>
-__global__ __launch_bounds__(64 * kWaves) void k_test_product_select(const float* rows, int ld,
-                                                                     int n,
-                                                                     const uint8_t* feasible,
-                                                                     const float* u, int32_t* out) {
-    __shared__ uint32_t s_key[kWaves], s_city[kWaves];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+__global__ __launch_bounds__(64) void k_test_product_select(const float* rows, int ld, int n,
+                                                            const uint8_t* feasible,
+                                                            const float* u, int32_t* out) {
+    const int lane = threadIdx.x;
     const int q = blockIdx.x;
     const uint8_t* f = feasible + (size_t)q * n;
     uint64_t bits = 0;
 #pragma unroll
     for (int p = 0; p < P; ++p)
 #pragma unroll
-        for (int e = 0; e < Lay<kWaves>::GW; ++e) {
-            const int j = Lay<kWaves>::city(p, w, lane, e);
-            if (j < n && f[j]) bits |= 1ull << (Lay<kWaves>::GW * p + e);
+        for (int e = 0; e < kG; ++e) {
+            const int j = city_of(p, lane, e);
+            if (j < n && f[j]) bits |= 1ull << (kG * p + e);
         }
     const ArrayDraws draws{u + (size_t)q * n, n};
-    const Pick mine = product_pick<P, kWaves>(rows + (size_t)q * ld, n, bits, draws, w, lane);
-    if (lane == 0) {
-        s_key[w] = mine.key;
-        s_city[w] = mine.city;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        uint32_t top = 0;
-        for (int v = 0; v < kWaves; ++v) top = s_key[v] > top ? s_key[v] : top;
-        uint32_t j = ~0u;
-        for (int v = 0; v < kWaves; ++v)
-            if (s_key[v] == top && s_city[v] < j) j = s_city[v];
-        out[q] = j == ~0u ? -1 : (int)j;
-    }
+    const Pick mine = product_pick<P>(rows + (size_t)q * ld, n, bits, draws, lane);
+    if (lane == 0) out[q] = mine.city == ~0u ? -1 : (int)mine.city;
 }
 
 // Philox throughput probe: the draws of `steps` steps of a 2400-city row
@@ -429,9 +414,11 @@ hipError_t dispatch_passes(int n, F&& f) {
 
 hipError_t launch_construct_product(const Colony& c, uint32_t iter, hipStream_t s) {
     if (c.n < 1 || c.n > kMaxCities) return hipErrorInvalidValue;
+    const hipError_t e = launch_short_lists(c, s);
+    if (e != hipSuccess) return e;
     return dispatch_passes(c.n, [&]<int P>() {
-        hipLaunchKernelGGL((k_construct_product<P>), dim3(c.m), dim3(64 * kWaves),
-                           tour_bytes(c.n), s, c, iter);
+        hipLaunchKernelGGL((k_construct_product<P>), dim3(c.m), dim3(64), tour_bytes(c.n), s, c,
+                           iter);
         return hipGetLastError();
     });
 }
@@ -450,7 +437,7 @@ hipError_t launch_test_product_select(int n, int count, const float* rows,
     if (n < 1 || n > kMaxCities) return hipErrorInvalidValue;
     const int ld = (n + 63) & ~63;
     return dispatch_passes(n, [&]<int P>() {
-        hipLaunchKernelGGL((k_test_product_select<P>), dim3(count), dim3(64 * kWaves), 0, s, rows,
+        hipLaunchKernelGGL((k_test_product_select<P>), dim3(count), dim3(64), 0, s, rows,
                            ld, n, feasible, u, out);
         return hipGetLastError();
     });
