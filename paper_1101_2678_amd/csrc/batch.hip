@@ -2,7 +2,8 @@
 // the construction-tile autotuner.
 //
 // A batch keeps every instance resident in one caller-owned workspace.  One
-// AS iteration of the whole batch is three launches: construction of every
+// AS iteration of the whole batch is four launches: the short lists of every
+// row, construction of every
 // ant of every instance (one workgroup per ant, instances ordered largest n
 // first so the longest tours start first), the best-so-far of every
 // instance, and the gather update of every row of every instance.  Each
@@ -23,6 +24,7 @@
 #include "aco.h"
 #include "aco_host.hpp"
 #include "aco_state.hpp"
+#include "shortlist.hpp"
 
 using aco::host::fail;
 
@@ -96,6 +98,8 @@ aco_status batch_device_fail(aco_batch* b, hipError_t e, const char* where) {
 hipError_t enqueue_iterations(aco_batch* b, uint32_t iters) {
     hipError_t e = hipSuccess;
     for (uint32_t i = 0; i < iters && e == hipSuccess; ++i) {
+        e = aco::launch_short_lists_batch(b->d_cols, b->d_rowmap, b->total_rows, b->max_n, b->stream);
+        if (e != hipSuccess) break;
         e = aco::launch_construct_batch(
             b->d_cols, b->d_antmap, b->total_ants, b->max_n,
             aco::batch_lds_bytes(b->max_n, b->config.wg_per_cu, b->lds_per_cu), b->stream);

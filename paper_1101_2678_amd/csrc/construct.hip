@@ -29,11 +29,15 @@
 //     test can be skipped without changing the result;
 //   * surviving blocks are rescanned one element per lane with the exact S64
 //     tree, in block order, until the first feasible prefix above the target.
+// Before any of that, once pheromone has gathered, a step reads only its row's
+// short list (shortlist.hpp) and takes the city it proves to be the rule's;
+// the steps above then run only where the list does not settle it.
 // Random numbers: Philox draws (seed, iter, ant, step), 64 steps at a time on
 // the vector unit.
 #include <type_traits>
 
 #include "r64_lanes.hpp"
+#include "shortlist.hpp"
 
 namespace aco {
 namespace {
@@ -132,6 +136,22 @@ __device__ __forceinline__ void load_row(const float* __restrict__ mat, int reco
 template <int G, int P>
 constexpr bool kWriteAllPasses = (P * Tile<G>::kPass <= 1024);
 
+// Two passes: both passes' masks and lane sums before either's sums across
+// lanes (left to itself, the compiler finishes one pass and waits for its
+// cross-lane read before the next: n = 1000 560 against 520 us).
+template <int P>
+constexpr bool kTogether = P == 2;
+
+// Lane b of T takes the total of block b of pass p from t, whose groups' last
+// lanes hold the pass's block totals.
+template <int G>
+__device__ __forceinline__ float to_blocks(float t, int p, float T, int lane) {
+    constexpr int LPB = Tile<G>::kLanesPerBlock;
+    const float x = __int_as_float(__builtin_amdgcn_ds_bpermute(
+        ((lane % G) * LPB + LPB - 1) * 4, __float_as_int(t)));
+    return lane / G == p ? x : T;
+}
+
 // One R64 roulette draw over a loaded row of P passes (wa/wb as load_row
 // leaves them; masked in place).  block_bits: the visited bits of block b in
 // lane b.  Returns the chosen city, or -1 if no city is feasible.
@@ -153,33 +173,38 @@ __device__ __forceinline__ int pick_loaded(u32x4 (&wa)[P], u32x4 (&wb)[P], int n
     constexpr bool kPermute = P >= 2;
     const int nb = (n + 63) >> 6;
     float T = 0.0f;
+    float part[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         const uint32_t bits = (uint32_t)(lane_bits >> (p * G));
         mask4<0>(wa[p], bits);
-        float t;
         if (G == 8) {
             mask4<4>(wb[p], bits);
-            t = pair_sum4(wa[p]) + pair_sum4(wb[p]);
+            part[p] = pair_sum4(wa[p]) + pair_sum4(wb[p]);
         } else {
-            t = pair_sum4(wa[p]);
+            part[p] = pair_sum4(wa[p]);
         }
-        if (kAll && !kPermute) {
-            u32x4* dst = reinterpret_cast<u32x4*>(s_w + p * Tile<G>::kPass + lane * G);
-            dst[0] = wa[p];
-            if (G == 8) dst[1] = wb[p];
-        }
-        t = group_pairwise<LPB>(t);
-        if (kPermute) {
-            // block b = pass p, group b mod G
-            const float x = __int_as_float(__builtin_amdgcn_ds_bpermute(
-                ((lane % G) * LPB + LPB - 1) * 4, __float_as_int(t)));
-            T = lane / G == p ? x : T;
-        } else if ((lane % LPB) == LPB - 1) {
-            s_T[p * G + lane / LPB] = t;
+        if (!kPermute) {
+            if (kAll) {
+                u32x4* dst = reinterpret_cast<u32x4*>(s_w + p * Tile<G>::kPass + lane * G);
+                dst[0] = wa[p];
+                if (G == 8) dst[1] = wb[p];
+            }
+            const float t = group_pairwise<LPB>(part[p]);
+            if ((lane % LPB) == LPB - 1) s_T[p * G + lane / LPB] = t;
+        } else if (!kTogether<P>) {
+            T = to_blocks<G>(group_pairwise<LPB>(part[p]), p, T, lane);
         }
     }
     if (kPermute) {
+        if (kTogether<P>) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int p = 0; p < P; ++p) part[p] = group_pairwise<LPB>(part[p]);
+#pragma unroll
+            for (int p = 0; p < P; ++p) T = to_blocks<G>(part[p], p, T, lane);
+            __builtin_amdgcn_sched_barrier(0x7F);  // no LDS store above the reads
+        }
         if (kAll) {
 #pragma unroll
             for (int p = 0; p < P; ++p) {
@@ -244,17 +269,74 @@ __device__ __forceinline__ int r64_pick(const float* __restrict__ mat, int recor
     return pick_loaded<G, P>(wa, wb, n, lane_bits, block_bits, s_T, s_w, u, lane);
 }
 
-// LDS a construction workgroup needs besides the tour.
+// LDS a construction workgroup needs besides the tour and the visited flags.
+template <int W>
 struct AntShared {
-    float w[1024];      // masked weights of rows up to 1024 cities, else a staged pass
-    float T[64];        // block totals in block order
+    float w[W];   // masked weights of rows up to 1024 cities, else a staged pass
+    float T[64];  // block totals in block order
 };
+
+// Staging of a kernel for rows of P passes: less for long rows, so that 12
+// ants of 3000 cities fit a compute unit.
+template <int G, int P>
+constexpr int kStaged = kWriteAllPasses<G, P> ? 1024 : Tile<G>::kPass;
+
+// Tiles whose colonies use the short lists: at tile 4 (n <= 256) a step from
+// the list takes longer than one from the row (n = 200: 0.41 against 0.37 us).
+template <int G>
+constexpr bool kUseLists = G == 8;
+
+// Visited flags: one byte a city of the row's passes, 1 = visited or beyond
+// n.  A visit is one byte store, and a listed city's flag one byte load at
+// the city itself.
+__host__ __device__ size_t seen_lds_bytes(int n) { return ((size_t)n + 511) & ~(size_t)511; }
+
+__host__ __device__ size_t ant_lds_bytes(int n) { return tour_lds_bytes(n) + seen_lds_bytes(n); }
+
+// The lane and block bits of the general step from the flags of the ant's P
+// passes.  s_bits: 64 P bytes of scratch.
+template <int P, typename B>
+__device__ __forceinline__ void bits_from_flags(const uint2* s_seen, uint8_t* s_bits, int lane,
+                                                B& lane_bits, uint64_t& block_bits) {
+    // four bytes of 0 or 1 to four bits
+    const auto four = [](uint32_t x) { return (x * 0x10204080u) >> 28; };
+    uint32_t seen[P];
+    lane_bits = 0;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const uint2 f = s_seen[64 * p + lane];  // cities 512 p + 8 lane .. + 7
+        seen[p] = four(f.x) | four(f.y) << 4;
+        lane_bits |= (B)(seen[p] ^ 0xFFu) << (8 * p);
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p) s_bits[64 * p + lane] = (uint8_t)seen[p];
+    // block b: the eight bytes from 8 b
+    block_bits = ~0ull;
+    if (lane < 8 * P) {
+        block_bits = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) block_bits |= (uint64_t)s_bits[8 * lane + e] << (8 * e);
+    }
+}
+
+// Whether the roulette of colony c starts its steps from the short lists:
+// where half of the rows have a list that covers them well.
+__device__ __forceinline__ bool starts_from_lists(const Colony& c, int lane) {
+    int rows = 0;
+    for (int j = 16 * lane; j < c.n; j += 16 * 64) {  // by_list is 0 past n
+        const uint4 v = *reinterpret_cast<const uint4*>(c.by_list + j);
+        rows += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) rows += __shfl_xor(rows, off);
+    return 2 * __builtin_amdgcn_readfirstlane(rows) >= c.n;
+}
 
 // The whole tour of ant k of colony c in iteration `iter`: placement, n - 1
 // roulette steps, then length, deposit, tour and neighbour tables.
-template <int G, int P, bool SKIP, bool LOAD_FIRST>
+template <int G, int P, bool SKIP, bool LOAD_FIRST, bool LIST, int W>
 __device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t iter,
-                                              uint16_t* s_tour, AntShared& sh) {
+                                              uint16_t* s_tour, AntShared<W>& sh) {
     const int lane = threadIdx.x;
     const int n = c.n;
     const int records = n * c.ld * 4;  // the whole n x ld choice matrix
@@ -279,7 +361,46 @@ __device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t i
     // with SKIP that only loads a quad once more, and masking (which sees
     // it) zeroes the city.
     float u64 = 0.0f;
-    if (LOAD_FIRST) {
+    bool by_list = false;
+    if constexpr (LIST) by_list = starts_from_lists(c, lane);
+    if (LIST && by_list) {
+        // A step reads its city's short list, and the whole row only where
+        // the list does not settle the selection.  The usual step keeps the
+        // flags only; the general step's bits are made from them.  m = n,
+        // construction with the lists' launch against whole rows only, in
+        // the 20th iteration: n = 500 0.154 / 0.197 ms, n = 1000 0.315 /
+        // 0.508, n = 1500 0.541 / 1.31, n = 2400 1.14 / 6.05, n = 3000 1.76 /
+        // 13.3; mean of the first 24: 0.177 / 0.198, 0.402 / 0.519, 0.868 /
+        // 1.32, 2.63 / 6.05, 5.19 / 13.2.
+        const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
+        uint8_t* s_seen = reinterpret_cast<uint8_t*>(s_tour) + tour_lds_bytes(n);
+        for (int w = lane; w < 128 * P; w += 64) {
+            uint32_t f = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) f |= (4 * w + e >= n ? 1u : 0u) << (8 * e);
+            reinterpret_cast<uint32_t*>(s_seen)[w] = f;
+        }
+        __syncthreads();
+        for (int step = 1; step < n; ++step) {
+            const u32x2 entry = load_list(lists, cur, lane);
+            if (lane == 0) {
+                s_tour[step - 1] = (uint16_t)cur;
+                s_seen[cur] = 1;
+            }
+            const int slot = (step - 1) & 63;
+            if (__builtin_expect(slot == 0, 0))
+                u64 = draws64(key, iter, (uint32_t)k, step, lane);
+            const float u = read_lane(u64, slot);
+            int j = roulette_list_pick(entry, s_seen, u, lane);
+            if (__builtin_expect(j < 0, 0)) {
+                bits_from_flags<P>(reinterpret_cast<const uint2*>(s_seen),
+                                   reinterpret_cast<uint8_t*>(sh.w), lane, lane_bits, block_bits);
+                j = r64_pick<G, P, SKIP>(c.choice, records, cur, row_bytes, n, lane_bits,
+                                         block_bits, sh.T, sh.w, u, lane);
+            }
+            cur = j < 0 ? 0 : j;
+        }
+    } else if (LOAD_FIRST) {
         for (int step = 1; step < n; ++step) {
             u32x4 wa[P], wb[P];
             load_row<G, P, SKIP>(c.choice, records, cur, row_bytes, lane_bits, lane, wa, wb);
@@ -334,9 +455,10 @@ __device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t i
 
 template <int G, int P>
 __global__ __launch_bounds__(64) void k_construct(Colony c, uint32_t iter) {
-    extern __shared__ uint16_t s_tour[];
-    __shared__ __align__(16) AntShared sh;
-    construct_ant<G, P, (P >= 3), (P < 4)>(c, ant_of_block(blockIdx.x, c.m), iter, s_tour, sh);
+    extern __shared__ __align__(16) uint16_t s_tour[];
+    __shared__ __align__(16) AntShared<kStaged<G, P>> sh;
+    construct_ant<G, P, (P >= 3), (P < 4), kUseLists<G>>(c, ant_of_block(blockIdx.x, c.m), iter,
+                                                         s_tour, sh);
 }
 
 // Batched construction: workgroup g builds ant (antmap[g] & 0xffff) of colony
@@ -359,21 +481,21 @@ constexpr bool kBatchLoadFirst = NP < 4;
 // 762 solves/s against one loop with run-time pass tests).
 template <int G, int NP, int PMAX>
 __device__ __forceinline__ void batch_ant(const Colony& c, int k, uint32_t iter, int np,
-                                          uint16_t* s_tour, AntShared& sh) {
+                                          uint16_t* s_tour, AntShared<1024>& sh) {
     if constexpr (NP < PMAX) {
         if (np != NP) {
             batch_ant<G, NP + 1, PMAX>(c, k, iter, np, s_tour, sh);
             return;
         }
     }
-    construct_ant<G, NP, true, kBatchLoadFirst<NP>>(c, k, iter, s_tour, sh);
+    construct_ant<G, NP, true, kBatchLoadFirst<NP>, kUseLists<G>>(c, k, iter, s_tour, sh);
 }
 
 template <int P8>
 __global__ __launch_bounds__(64) void k_construct_batch(const Colony* __restrict__ cols,
                                                         const uint32_t* __restrict__ antmap) {
-    extern __shared__ uint16_t s_tour[];
-    __shared__ __align__(16) AntShared sh;
+    extern __shared__ __align__(16) uint16_t s_tour[];
+    __shared__ __align__(16) AntShared<1024> sh;
     const uint32_t e = antmap[blockIdx.x];
     const Colony c = cols[e >> 16];
     // One value for the whole workgroup.  Read through a pointer the kernel
@@ -395,7 +517,7 @@ template <int G, int P>
 __global__ __launch_bounds__(64) void k_test_select(const float* rows, int ld, int n,
                                                      const uint8_t* feasible, const float* us,
                                                      int32_t* out) {
-    __shared__ __align__(16) AntShared sh;
+    __shared__ __align__(16) AntShared<kStaged<G, P>> sh;
     const int lane = threadIdx.x;
     const int q = blockIdx.x;
     const uint8_t* f = feasible + (size_t)q * n;
@@ -437,10 +559,10 @@ constexpr int kCapRounds = 8;
 }  // namespace
 
 size_t batch_lds_bytes(int max_n, int wg_per_cu, size_t lds_per_cu) {
-    const size_t tour = tour_lds_bytes(max_n);
+    const size_t tour = ant_lds_bytes(max_n);
     if (wg_per_cu <= 0 || lds_per_cu == 0) return tour;
     const size_t per_wg = lds_per_cu / (size_t)wg_per_cu;
-    const size_t fixed = sizeof(AntShared) + 64;  // static LDS and its alignment
+    const size_t fixed = sizeof(AntShared<1024>) + 64;  // static LDS and its alignment
     const size_t cap = per_wg > fixed ? (per_wg - fixed) & ~(size_t)255 : 0;
     return tour > cap ? tour : cap;
 }
@@ -489,7 +611,7 @@ int construct_occupancy(const Colony& c) {
     int blocks = -1;
     (void)dispatch_tile(c.tile, c.n, [&]<int G, int P>() {
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_construct<G, P>, 64,
-                                                         tour_lds_bytes(c.n)) != hipSuccess)
+                                                         ant_lds_bytes(c.n)) != hipSuccess)
             blocks = -1;
         return hipSuccess;
     });
@@ -499,8 +621,12 @@ int construct_occupancy(const Colony& c) {
 hipError_t launch_construct(const Colony& c, uint32_t iter, hipStream_t s) {
     if (c.waves > 1) return launch_construct_split(c, iter, s);
     if (!tile_supported(c.tile, c.n)) return hipErrorInvalidValue;
+    if (c.tile == 8) {
+        const hipError_t e = launch_short_lists(c, s);
+        if (e != hipSuccess) return e;
+    }
     return dispatch_tile(c.tile, c.n, [&]<int G, int P>() {
-        hipLaunchKernelGGL((k_construct<G, P>), dim3(c.m), dim3(64), tour_lds_bytes(c.n), s, c,
+        hipLaunchKernelGGL((k_construct<G, P>), dim3(c.m), dim3(64), ant_lds_bytes(c.n), s, c,
                            iter);
         return hipGetLastError();
     });
@@ -510,7 +636,7 @@ hipError_t launch_construct_batch(const Colony* cols, const uint32_t* antmap, in
                                   int max_n, size_t lds, hipStream_t s) {
     if (total_ants <= 0) return hipSuccess;
     if (max_n < 1 || max_n > kMaxCities) return hipErrorInvalidValue;
-    if (lds < tour_lds_bytes(max_n)) return hipErrorInvalidValue;
+    if (lds < ant_lds_bytes(max_n)) return hipErrorInvalidValue;
     const int passes = (max_n + 511) / 512;
     const dim3 grid(total_ants), block(64);
     if (passes <= 2)

@@ -29,6 +29,7 @@
 #include "aco.h"
 #include "aco_host.hpp"
 #include "aco_state.hpp"
+#include "shortlist.hpp"
 
 using aco::host::fail;
 
@@ -329,6 +330,8 @@ aco_status aco_server_step(aco_server* s, int32_t* running_out) {
         if (k.dirty) e = rebuild_class(s, (int)c);
         if (e != hipSuccess) return server_fail(s, e, "aco_server_step");
         if (k.running.empty()) continue;
+        e = aco::launch_short_lists_batch(k.d_cols, k.d_rowmap, k.total_rows, k.run_max_n, k.stream);
+        if (e != hipSuccess) return server_fail(s, e, "aco_server_step");
         e = aco::launch_construct_batch(
             k.d_cols, k.d_antmap, k.total_ants, k.run_max_n,
             aco::batch_lds_bytes(k.run_max_n, aco::batch_default_cap(k.total_ants, s->cus),

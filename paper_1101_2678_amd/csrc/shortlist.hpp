@@ -52,7 +52,51 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t list_rsrc(const Colony& c) {
                                              c.n * kListLanes * (int)sizeof(u32x2), 0x00020000);
 }
 
-// Lists of the n rows of colony c from its current choice matrix.
+// The roulette's selection from a row's short list alone (v: the lane's
+// entry, u: the step's draw), or -1 where it needs the whole row.  s_seen:
+// city j's visited flag in byte j.
+//
+// The rule over the whole row picks the lowest unvisited city j whose prefix
+// P_j exceeds target = fl32(u total).  With L_j the listed unvisited weight up
+// to and including j, A_j the tail's weight before j and R its whole weight
+// (both whether visited or not, so bounds from above), the exact sums obey
+//   L_j <= prefix of j,  prefix of any city before j <= L_j - w_j + A_j,
+//   L <= total <= L + R.
+// So j is the rule's city if L_j > u (L + R) and L_j - w_j + A_j <= u L.  Every
+// binary32 sum here and in the rule is a tree of non-negative terms of depth
+// at most 13, and so within a factor (1 +- 2^-24)^13 of the exact one; the
+// two sides of each test and their products together stay within 48 such
+// factors, which the margin 1 +- 2^-18 (64 of them) covers.  (Sums are exact where they are subnormal; L
+// above 2^-100 keeps the products normal, and build_list keeps every sum
+// below 2^101.)  Only one lane can pass both tests, and it is unvisited: with
+// w_j = 0 they contradict each other.
+__device__ __forceinline__ int roulette_list_pick(u32x2 v, const uint8_t* s_seen, float u,
+                                                  int lane) {
+    // u with the margin to either side, off the chain of the sums
+    const float u_over = u * (1.0f + 0x1.0p-18f), u_under = u * (1.0f - 0x1.0p-18f);
+    const int city = list_city(v.y);
+    const bool unvisited = s_seen[city] == 0;
+    const float above = list_tail(v.y);
+    const bool may = (lane < kListEntries) & unvisited;
+    const float w = may ? __uint_as_float(v.x) : 0.0f;
+    const float s = s64_scan(w);
+    const float listed = read_lane(s, 63), rest = read_lane(above, kListEntries);
+    const float before = wave_shift_up1(s) + above;
+    // two ballots and a scalar AND: the AND of the conditions would go
+    // through a vector register
+    uint64_t hit = ballot(s > u_over * (listed + rest)) & ballot(before <= u_under * listed);
+    // as bit patterns, on the scalar unit (listed >= +0)
+    hit = __float_as_uint(listed) > __float_as_uint(0x1.0p-100f) ? hit : 0ull;
+    if (__builtin_expect(hit == 0ull, 0)) return -1;
+    return __builtin_amdgcn_readlane(city, __builtin_ctzll(hit));
+}
+
+// Lists of the n rows of colony c from its current choice matrix, and the
+// rows the roulette starts from (c.by_list).
 hipError_t launch_short_lists(const Colony& c, hipStream_t s);
+// As above for the rows of a batch: (colony << 16) | row per entry of rowmap;
+// max_n: the largest n among the colonies.
+hipError_t launch_short_lists_batch(const Colony* cols, const uint32_t* rowmap, int total_rows,
+                                    int max_n, hipStream_t s);
 
 }  // namespace aco

@@ -15,7 +15,8 @@ from gpu_helpers import ORACLE_THREADS, assert_same_f32
 
 pytestmark = pytest.mark.gpu
 
-CONSTRUCT = {"product": (lambda c, it: c.construct_product(it), oracle.construct_product)}
+CONSTRUCT = {"product": (lambda c, it: c.construct_product(it), oracle.construct_product),
+             "r64": (lambda c, it: c.construct(it), oracle.construct)}
 
 
 def pheromone(kind, n, rng):
@@ -76,6 +77,14 @@ def test_sizes(rule, n):
 def test_weights(rule, kind, n, alpha, beta):
     _, d = tsp_inputs.instance(n, "uniform", side=20_000, seed=5)
     check(rule, d, 24, alpha, beta, kind)
+
+
+@pytest.mark.parametrize("n", [257, 511, 512, 513, 1025, 1537, 1999, 2000, 2049, 3073])
+def test_general_steps_between_list_steps(n):
+    """Rows that start every roulette step from the lists, at the pass bounds:
+    steps the list does not settle rebuild the visited bits."""
+    _, d = tsp_inputs.instance(n, "uniform", seed=n)
+    check("r64", d, 24 if n < 1024 else 8, 1, 2, "steep")
 
 
 @pytest.mark.parametrize("rule", sorted(CONSTRUCT))
