@@ -2,7 +2,8 @@
 // data-parallel design of Section III-A: one workgroup per ant, the ant's
 // candidate cities spread over the lanes).
 //
-// Layout of one step (ant at city `cur`, wavefront of 64 lanes, tile G = 4
+// Rows of at most 320 cities have a layout of their own (construct_flat.hpp).
+// Layout of one step of longer rows (ant at city `cur`, wavefront of 64 lanes, tile G = 4
 // or 8 cities per lane):
 //   * the choice row of `cur` is streamed with 16-byte loads; in pass p lane l
 //     holds cities 64Gp + Gl .. 64Gp + Gl + G-1, so one pass reads 256 G bytes
@@ -36,6 +37,7 @@
 // the vector unit.
 #include <type_traits>
 
+#include "construct_flat.hpp"
 #include "r64_lanes.hpp"
 #include "shortlist.hpp"
 
@@ -285,6 +287,7 @@ constexpr int kStaged = kWriteAllPasses<G, P> ? 1024 : Tile<G>::kPass;
 // the list takes longer than one from the row (n = 200: 0.41 against 0.37 us).
 template <int G>
 constexpr bool kUseLists = G == 8;
+constexpr int kMinListCities = 256;
 
 // Visited flags: one byte a city of the row's passes, 1 = visited or beyond
 // n.  A visit is one byte store, and a listed city's flag one byte load at
@@ -332,108 +335,16 @@ __device__ __forceinline__ bool starts_from_lists(const Colony& c, int lane) {
     return 2 * __builtin_amdgcn_readfirstlane(rows) >= c.n;
 }
 
-// The whole tour of ant k of colony c in iteration `iter`: placement, n - 1
-// roulette steps, then length, deposit, tour and neighbour tables.
-template <int G, int P, bool SKIP, bool LOAD_FIRST, bool LIST, int W>
-__device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t iter,
-                                              uint16_t* s_tour, AntShared<W>& sh) {
-    const int lane = threadIdx.x;
+// The end of a tour: its last city `cur`, then length, deposit, tour and
+// neighbour tables.
+__device__ __forceinline__ void finish_ant(const Colony& c, int k, int cur, uint16_t* s_tour,
+                                           int lane) {
     const int n = c.n;
-    const int records = n * c.ld * 4;  // the whole n x ld choice matrix
-    const PhiloxKey key{(uint32_t)c.seed, (uint32_t)(c.seed >> 32)};
-
-    const int row_bytes = c.ld * 4;
-    uint64_t block_bits = initial_block_bits(n, lane);
-    sh.T[lane] = 0.0f;
-    LaneBits<G, P> lane_bits = (LaneBits<G, P>)initial_lane_bits<G, P>(n, lane);
-    __syncthreads();
-
-    const uint32_t x0 = draw(key, iter, (uint32_t)k, 0u);
-    int cur = (int)(((uint64_t)x0 * (uint64_t)(uint32_t)n) >> 32);
-
-    // LOAD_FIRST: a step's row loads go out as soon as its city is known, and
-    // the bookkeeping of that city (tour entry, visited bits) is done while
-    // they are in flight.  That shortens launches of one to three passes
-    // (n = 100 14%, n = 1000 7%, n = 1500 4% faster) but made the
-    // bandwidth-bound four- and five-pass launches (n = 2048, 2400) no
-    // faster or up to 1% slower, which keep the bookkeeping first.  With
-    // LOAD_FIRST the loads see the visited bits without the step's own city;
-    // with SKIP that only loads a quad once more, and masking (which sees
-    // it) zeroes the city.
-    float u64 = 0.0f;
-    bool by_list = false;
-    if constexpr (LIST) by_list = starts_from_lists(c, lane);
-    if (LIST && by_list) {
-        // A step reads its city's short list, and the whole row only where
-        // the list does not settle the selection.  The usual step keeps the
-        // flags only; the general step's bits are made from them.  m = n,
-        // construction with the lists' launch against whole rows only, in
-        // the 20th iteration: n = 500 0.154 / 0.197 ms, n = 1000 0.315 /
-        // 0.508, n = 1500 0.541 / 1.31, n = 2400 1.14 / 6.05, n = 3000 1.76 /
-        // 13.3; mean of the first 24: 0.177 / 0.198, 0.402 / 0.519, 0.868 /
-        // 1.32, 2.63 / 6.05, 5.19 / 13.2.
-        const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
-        uint8_t* s_seen = reinterpret_cast<uint8_t*>(s_tour) + tour_lds_bytes(n);
-        for (int w = lane; w < 128 * P; w += 64) {
-            uint32_t f = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) f |= (4 * w + e >= n ? 1u : 0u) << (8 * e);
-            reinterpret_cast<uint32_t*>(s_seen)[w] = f;
-        }
-        __syncthreads();
-        for (int step = 1; step < n; ++step) {
-            const u32x2 entry = load_list(lists, cur, lane);
-            if (lane == 0) {
-                s_tour[step - 1] = (uint16_t)cur;
-                s_seen[cur] = 1;
-            }
-            const int slot = (step - 1) & 63;
-            if (__builtin_expect(slot == 0, 0))
-                u64 = draws64(key, iter, (uint32_t)k, step, lane);
-            const float u = read_lane(u64, slot);
-            int j = roulette_list_pick(entry, s_seen, u, lane);
-            if (__builtin_expect(j < 0, 0)) {
-                bits_from_flags<P>(reinterpret_cast<const uint2*>(s_seen),
-                                   reinterpret_cast<uint8_t*>(sh.w), lane, lane_bits, block_bits);
-                j = r64_pick<G, P, SKIP>(c.choice, records, cur, row_bytes, n, lane_bits,
-                                         block_bits, sh.T, sh.w, u, lane);
-            }
-            cur = j < 0 ? 0 : j;
-        }
-    } else if (LOAD_FIRST) {
-        for (int step = 1; step < n; ++step) {
-            u32x4 wa[P], wb[P];
-            load_row<G, P, SKIP>(c.choice, records, cur, row_bytes, lane_bits, lane, wa, wb);
-            if (lane == 0) s_tour[step - 1] = (uint16_t)cur;
-            mark_visited<G>(cur, lane, lane_bits, block_bits);
-            const int slot = (step - 1) & 63;
-            if (__builtin_expect(slot == 0, 0))
-                u64 = draws64(key, iter, (uint32_t)k, step, lane);
-            const float u = read_lane(u64, slot);
-            const int j = pick_loaded<G, P>(wa, wb, n, lane_bits, block_bits, sh.T, sh.w, u,
-                                            lane);
-            // At every step n - step >= 1 cities are unvisited, so j >= 0;
-            // the clamp only keeps the LDS indices in range should that
-            // ever break.
-            cur = j < 0 ? 0 : j;
-        }
-    } else {
-        for (int step = 1; step < n; ++step) {
-            if (lane == 0) s_tour[step - 1] = (uint16_t)cur;
-            mark_visited<G>(cur, lane, lane_bits, block_bits);
-            const int slot = (step - 1) & 63;
-            if (__builtin_expect(slot == 0, 0))
-                u64 = draws64(key, iter, (uint32_t)k, step, lane);
-            const float u = read_lane(u64, slot);
-            const int j = r64_pick<G, P, SKIP>(c.choice, records, cur, row_bytes, n, lane_bits,
-                                               block_bits, sh.T, sh.w, u, lane);
-            cur = j < 0 ? 0 : j;
-        }
-    }
+    // one wavefront's LDS operations execute in program order
     if (lane == 0) s_tour[n - 1] = (uint16_t)cur;
-    __syncthreads();
+    __builtin_amdgcn_wave_barrier();
     if (lane == 0) s_tour[n] = s_tour[0];
-    __syncthreads();
+    __builtin_amdgcn_wave_barrier();
 
     // Tour length C^k (int64), deposit fl32(1/C^k), tour and neighbour tables.
     long long len = 0;
@@ -451,6 +362,168 @@ __device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t i
         c.lens[k] = len;
         c.dep[k] = (float)(1.0 / (double)len);
     }
+}
+
+
+// The n - 1 selections of ant k from its start city: step(cur, u, i) is the
+// next city of the i-th (0 .. n - 2).  64 steps at a time: their draws come
+// from one Philox call on the vector unit, and with KEEP the cities left go
+// to a register, one lane a step, and from there to s_tour at once (three
+// instructions a step; a store by one lane takes six).  Returns the last city.
+template <bool KEEP, typename Step>
+__device__ __forceinline__ int walk(int n, PhiloxKey key, uint32_t iter, int k, uint16_t* s_tour,
+                                    int lane, Step&& step) {
+    const uint32_t x0 = draw(key, iter, (uint32_t)k, 0u);
+    int cur = (int)(((uint64_t)x0 * (uint64_t)(uint32_t)n) >> 32);
+    for (int base = 0; base < n - 1; base += 64) {
+        const float u64 = draws64(key, iter, (uint32_t)k, base + 1, lane);
+        const int count = __builtin_amdgcn_readfirstlane(n - 1 - base < 64 ? n - 1 - base : 64);
+        uint32_t left = 0;
+        int t = 0;
+        do {
+            if (KEEP) left = lane == t ? (uint32_t)cur : left;
+            // one city for the wavefront; taken as per-lane, every row load
+            // of the next step would become a loop over lanes
+            cur = __builtin_amdgcn_readfirstlane(step(cur, read_lane(u64, t), base + t));
+        } while (++t < count);
+        if (KEEP && lane < count) s_tour[base + lane] = (uint16_t)left;
+    }
+    return cur;
+}
+
+// Visited flags of the ant's first `cities` cities (a multiple of 512): 0, or
+// 1 beyond n.
+__device__ __forceinline__ uint8_t* clear_flags(uint16_t* s_tour, int n, int cities, int lane) {
+    uint8_t* s_seen = reinterpret_cast<uint8_t*>(s_tour) + tour_lds_bytes(n);
+    for (int w = lane; w < cities / 4; w += 64) {
+        uint32_t f = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f |= (4 * w + e >= n ? 1u : 0u) << (8 * e);
+        reinterpret_cast<uint32_t*>(s_seen)[w] = f;
+    }
+    __builtin_amdgcn_wave_barrier();
+    return s_seen;
+}
+
+// The whole tour of ant k for rows of at most B blocks of 64 cities.
+template <int B, bool LIST>
+__device__ __forceinline__ void construct_ant_flat(const Colony& c, int k, uint32_t iter,
+                                                   uint16_t* s_tour, int lane) {
+    const int n = c.n;
+    const int row_bytes = c.ld * 4, records = n * row_bytes;
+    const PhiloxKey key{(uint32_t)c.seed, (uint32_t)(c.seed >> 32)};
+    Unvisited<B> live(n);
+    int cur;
+    bool by_list = false;
+    if constexpr (LIST) by_list = starts_from_lists(c, lane);
+    if (LIST && by_list) {
+        // as in construct_ant
+        const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
+        uint8_t* s_seen = clear_flags(s_tour, n, 512, lane);
+        cur = walk<false>(n, key, iter, k, s_tour, lane, [&](int at, float u, int i) {
+            const u32x2 entry = load_list(lists, at, lane);
+            if (lane == 0) {
+                s_tour[i] = (uint16_t)at;
+                s_seen[at] = 1;
+            }
+            int j = roulette_list_pick(entry, s_seen, u, lane);
+            if (__builtin_expect(j < 0, 0)) {
+                uint32_t x[B];
+                load_flat<B>(c.choice, records, at, row_bytes, lane, x);
+                live.from_flags(s_seen, lane);
+                j = pick_flat<B>(x, live, u);
+            }
+            return j;
+        });
+    } else {
+        cur = walk<true>(n, key, iter, k, s_tour, lane, [&](int at, float u, int) {
+            uint32_t x[B];
+            load_flat<B>(c.choice, records, at, row_bytes, lane, x);
+            live.visit(at, lane);
+            return pick_flat<B>(x, live, u);
+        });
+    }
+    finish_ant(c, k, cur, s_tour, lane);
+}
+
+template <int B>
+__global__ __launch_bounds__(64) void k_construct_flat(Colony c, uint32_t iter) {
+    extern __shared__ __align__(16) uint16_t s_tour[];
+    construct_ant_flat<B, (64 * B > kMinListCities)>(c, ant_of_block(blockIdx.x, c.m), iter,
+                                                     s_tour, threadIdx.x);
+}
+
+// The whole tour of ant k of colony c in iteration `iter`: placement, n - 1
+// roulette steps, then length, deposit, tour and neighbour tables.
+template <int G, int P, bool SKIP, bool LOAD_FIRST, bool LIST, int W>
+__device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t iter,
+                                              uint16_t* s_tour, AntShared<W>& sh) {
+    const int lane = threadIdx.x;
+    const int n = c.n;
+    const int records = n * c.ld * 4;  // the whole n x ld choice matrix
+    const PhiloxKey key{(uint32_t)c.seed, (uint32_t)(c.seed >> 32)};
+
+    const int row_bytes = c.ld * 4;
+    uint64_t block_bits = initial_block_bits(n, lane);
+    sh.T[lane] = 0.0f;
+    LaneBits<G, P> lane_bits = (LaneBits<G, P>)initial_lane_bits<G, P>(n, lane);
+    __builtin_amdgcn_wave_barrier();
+
+    // LOAD_FIRST: a step's row loads go out as soon as its city is known, and
+    // the bookkeeping of that city (tour entry, visited bits) is done while
+    // they are in flight.  That shortens launches of one to three passes
+    // (n = 100 14%, n = 1000 7%, n = 1500 4% faster) but made the
+    // bandwidth-bound four- and five-pass launches (n = 2048, 2400) no
+    // faster or up to 1% slower, which keep the bookkeeping first.  With
+    // LOAD_FIRST the loads see the visited bits without the step's own city;
+    // with SKIP that only loads a quad once more, and masking (which sees
+    // it) zeroes the city.
+    int cur;
+    bool by_list = false;
+    if constexpr (LIST) by_list = starts_from_lists(c, lane);
+    if (LIST && by_list) {
+        // A step reads its city's short list, and the whole row only where
+        // the list does not settle the selection.  The usual step keeps the
+        // flags only; the general step's bits are made from them.  m = n,
+        // construction with the lists' launch against whole rows only, in
+        // the 20th iteration: n = 500 0.154 / 0.197 ms, n = 1000 0.315 /
+        // 0.508, n = 1500 0.541 / 1.31, n = 2400 1.14 / 6.05, n = 3000 1.76 /
+        // 13.3; mean of the first 24: 0.177 / 0.198, 0.402 / 0.519, 0.868 /
+        // 1.32, 2.63 / 6.05, 5.19 / 13.2.
+        const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
+        uint8_t* s_seen = clear_flags(s_tour, n, 512 * P, lane);
+        cur = walk<false>(n, key, iter, k, s_tour, lane, [&](int at, float u, int i) {
+            const u32x2 entry = load_list(lists, at, lane);
+            if (lane == 0) {
+                s_tour[i] = (uint16_t)at;
+                s_seen[at] = 1;
+            }
+            int j = roulette_list_pick(entry, s_seen, u, lane);
+            if (__builtin_expect(j < 0, 0)) {
+                bits_from_flags<P>(reinterpret_cast<const uint2*>(s_seen),
+                                   reinterpret_cast<uint8_t*>(sh.w), lane, lane_bits, block_bits);
+                j = r64_pick<G, P, SKIP>(c.choice, records, at, row_bytes, n, lane_bits,
+                                         block_bits, sh.T, sh.w, u, lane);
+            }
+            return j < 0 ? 0 : j;
+        });
+    } else {
+        cur = walk<true>(n, key, iter, k, s_tour, lane, [&](int at, float u, int) {
+            u32x4 wa[P], wb[P];
+            if (LOAD_FIRST)
+                load_row<G, P, SKIP>(c.choice, records, at, row_bytes, lane_bits, lane, wa, wb);
+            mark_visited<G>(at, lane, lane_bits, block_bits);
+            if (!LOAD_FIRST)
+                load_row<G, P, SKIP>(c.choice, records, at, row_bytes, lane_bits, lane, wa, wb);
+            const int j = pick_loaded<G, P>(wa, wb, n, lane_bits, block_bits, sh.T, sh.w, u,
+                                            lane);
+            // At every step at least one city is unvisited, so j >= 0; the
+            // clamp only keeps the LDS indices in range should that ever
+            // break.
+            return j < 0 ? 0 : j;
+        });
+    }
+    finish_ant(c, k, cur, s_tour, lane);
 }
 
 template <int G, int P>
@@ -491,6 +564,18 @@ __device__ __forceinline__ void batch_ant(const Colony& c, int k, uint32_t iter,
     construct_ant<G, NP, true, kBatchLoadFirst<NP>, kUseLists<G>>(c, k, iter, s_tour, sh);
 }
 
+template <int B>
+__device__ __forceinline__ void batch_ant_flat(const Colony& c, int k, uint32_t iter,
+                                               uint16_t* s_tour) {
+    if constexpr (B < kMaxFlatBlocks) {
+        if (__builtin_amdgcn_readfirstlane(c.n) > 64 * B) {
+            batch_ant_flat<B + 1>(c, k, iter, s_tour);
+            return;
+        }
+    }
+    construct_ant_flat<B, (64 * B > kMinListCities)>(c, k, iter, s_tour, threadIdx.x);
+}
+
 template <int P8>
 __global__ __launch_bounds__(64) void k_construct_batch(const Colony* __restrict__ cols,
                                                         const uint32_t* __restrict__ antmap) {
@@ -504,9 +589,11 @@ __global__ __launch_bounds__(64) void k_construct_batch(const Colony* __restrict
     // becomes a loop over lanes.
     const uint32_t iter = __builtin_amdgcn_readfirstlane(*c.iter_dev);
     const int k = (int)(e & 0xffffu);
-    if (c.tile == 4) {
+    if (c.n <= 64 * kMaxFlatBlocks) {
+        batch_ant_flat<1>(c, k, iter, s_tour);
+    } else if (c.tile == 4) {
         const int np = __builtin_amdgcn_readfirstlane((c.n + 255) / 256);
-        batch_ant<4, 1, 4>(c, k, iter, np, s_tour, sh);
+        batch_ant<4, 2, 4>(c, k, iter, np, s_tour, sh);
     } else {
         const int np = __builtin_amdgcn_readfirstlane((c.n + 511) / 512);
         batch_ant<8, 1, P8>(c, k, iter, np, s_tour, sh);
@@ -543,6 +630,25 @@ __global__ __launch_bounds__(64) void k_test_select(const float* rows, int ld, i
     if (lane == 0) out[q] = j;
 }
 
+template <int B>
+__global__ __launch_bounds__(64) void k_test_select_flat(const float* rows, int ld, int n,
+                                                         const uint8_t* feasible, const float* us,
+                                                         int32_t* out) {
+    const int lane = threadIdx.x;
+    const int q = blockIdx.x;
+    const uint8_t* f = feasible + (size_t)q * n;
+    Unvisited<B> live(n);
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+        const int j = 64 * b + lane;
+        live.word[b] = ballot(j < n && f[j] != 0);
+    }
+    uint32_t x[B];
+    load_flat<B>(rows + (size_t)q * ld, n * 4, 0, ld * 4, lane, x);
+    const int j = pick_flat<B>(x, live, us[q]);
+    if (lane == 0) out[q] = j;
+}
+
 // Batched launches can hold at most `wg_per_cu` workgroups on a compute unit
 // by asking for more dynamic LDS than the tour needs.  Each workgroup keeps
 // one choice row in flight; with more of them the rows evict one another
@@ -573,12 +679,43 @@ int batch_default_cap(int total_ants, int cus) {
 
 namespace {
 
-// Calls f.template operator()<G, P>() for the tile and pass count of n.
+// Calls f.template operator()<G, P>() for the tile and pass count of n, or
+// with G = 0 and the number of 64-city blocks for rows of the flat layout.
+template <int B = 1, typename F>
+hipError_t dispatch_flat(int n, F&& f) {
+    if constexpr (B > kMaxFlatBlocks) {
+        return hipErrorInvalidValue;
+    } else {
+        if (n > 64 * B) return dispatch_flat<B + 1>(n, f);
+        return f.template operator()<0, B>();
+    }
+}
+
+template <int G, int P>
+auto test_select_kernel() {
+    if constexpr (G == 0)
+        return k_test_select_flat<P>;
+    else
+        return k_test_select<G, P>;
+}
+
+template <int G, int P>
+auto construct_kernel() {
+    if constexpr (G == 0)
+        return k_construct_flat<P>;
+    else
+        return k_construct<G, P>;
+}
+
+bool uses_lists(const Colony& c) {
+    return c.n > kMinListCities && (c.n <= 64 * kMaxFlatBlocks || c.tile == 8);
+}
+
 template <typename F>
 hipError_t dispatch_tile(int tile, int n, F&& f) {
+    if (n <= 64 * kMaxFlatBlocks) return dispatch_flat(n, f);
     if (tile == 4) {
         switch ((n + 255) / 256) {
-            case 1: return f.template operator()<4, 1>();
             case 2: return f.template operator()<4, 2>();
             case 3: return f.template operator()<4, 3>();
             case 4: return f.template operator()<4, 4>();
@@ -610,7 +747,7 @@ int construct_occupancy(const Colony& c) {
     if (c.waves > 1) return construct_split_occupancy(c);
     int blocks = -1;
     (void)dispatch_tile(c.tile, c.n, [&]<int G, int P>() {
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k_construct<G, P>, 64,
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, construct_kernel<G, P>(), 64,
                                                          ant_lds_bytes(c.n)) != hipSuccess)
             blocks = -1;
         return hipSuccess;
@@ -621,13 +758,13 @@ int construct_occupancy(const Colony& c) {
 hipError_t launch_construct(const Colony& c, uint32_t iter, hipStream_t s) {
     if (c.waves > 1) return launch_construct_split(c, iter, s);
     if (!tile_supported(c.tile, c.n)) return hipErrorInvalidValue;
-    if (c.tile == 8) {
+    if (uses_lists(c)) {
         const hipError_t e = launch_short_lists(c, s);
         if (e != hipSuccess) return e;
     }
     return dispatch_tile(c.tile, c.n, [&]<int G, int P>() {
-        hipLaunchKernelGGL((k_construct<G, P>), dim3(c.m), dim3(64), ant_lds_bytes(c.n), s, c,
-                           iter);
+        hipLaunchKernelGGL((construct_kernel<G, P>()), dim3(c.m), dim3(64), ant_lds_bytes(c.n), s,
+                           c, iter);
         return hipGetLastError();
     });
 }
@@ -657,7 +794,7 @@ hipError_t launch_test_select(int tile, int n, int count, const float* rows,
     if (!tile_supported(tile, n)) return hipErrorInvalidValue;
     const int ld = (n + 63) & ~63;
     return dispatch_tile(tile, n, [&]<int G, int P>() {
-        hipLaunchKernelGGL((k_test_select<G, P>), dim3(count), dim3(64), 0, s, rows, ld, n,
+        hipLaunchKernelGGL((test_select_kernel<G, P>()), dim3(count), dim3(64), 0, s, rows, ld, n,
                            feasible, u, out);
         return hipGetLastError();
     });

@@ -1,0 +1,33 @@
+"""The roulette step of short rows (one city of every 64-city block per lane,
+construct_flat.hpp) at the edges of its blocks, against the oracle."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+import tsp_inputs
+from gpu_helpers import compare_run
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [2, 63, 64, 65, 127, 128, 129, 191, 192, 193, 256, 257, 319, 320, 321]
+
+
+@pytest.mark.parametrize("n", EDGES)
+def test_select(n):
+    import torch
+    from paper_1101_2678_amd import aco
+    from test_gpu_parity import _adversarial_rows
+
+    rows, feas, u = _adversarial_rows(n, 1500, np.random.default_rng(9000 + n))
+    feas[::97] = 0  # no feasible city
+    args = [torch.from_numpy(a).cuda() for a in (rows, feas, u)]
+    got = aco.test_select(*args).cpu().numpy()
+    assert (got == oracle.r64_select_batch(rows, feas, u)).all()
+
+
+@pytest.mark.parametrize("n", [n for n in EDGES if n > 2])
+def test_parity(n):
+    _, d = tsp_inputs.instance(n, "cluster" if n % 2 else "uniform", side=10_000, seed=n + 1)
+    compare_run(d, 70, 1, 2, 0.5, seed=n, iters=2, kinds=("gather",))
