@@ -206,11 +206,15 @@ aco_status aco_batch_init(aco_batch** out, int32_t count, const aco_params* para
     b->count = count;
     b->stream = static_cast<hipStream_t>(hip_stream);
     b->cols.resize(count);
-    hipError_t e = hipSuccess;
+    // every array cleared at once, then every instance's distances to its tau
+    // matrix, from where one launch spreads them all
+    hipError_t e = hipMemsetAsync(base, 0, B.cols_off, b->stream);
     for (int q = 0; q < count && e == hipSuccess; ++q) {
         b->cols[q] = aco::host::carve(base + B.inst_off[q], B.inst[q], params[q], false,
                                       dep_emin[q], aco::host::tile_for(params[q].n));
-        e = aco::host::upload_and_init(b->cols[q], dist_hosts[q], B.inst[q].base_end, b->stream);
+        e = hipMemcpyAsync(b->cols[q].tau, dist_hosts[q],
+                           (size_t)params[q].n * params[q].n * sizeof(int32_t),
+                           hipMemcpyHostToDevice, b->stream);
         b->max_n = std::max(b->max_n, params[q].n);
         b->max_ld = std::max(b->max_ld, B.inst[q].ld);
     }
@@ -243,6 +247,9 @@ aco_status aco_batch_init(aco_batch** out, int32_t count, const aco_params* para
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->d_rowmap, rowmap.data(), sizeof(uint32_t) * rowmap.size(),
                            hipMemcpyHostToDevice, b->stream);
+    if (e == hipSuccess)
+        e = aco::launch_init_batch(b->d_cols, count, b->d_rowmap, b->total_rows, b->max_n,
+                                   b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) {
         const aco_status s = batch_device_fail(b, e, "aco_batch_init");

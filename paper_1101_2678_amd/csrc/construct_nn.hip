@@ -33,7 +33,9 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 size_t round_up256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-size_t tour_bytes(int n) { return ((size_t)(n + 1) * sizeof(uint16_t) + 15) & ~(size_t)15; }
+__host__ __device__ size_t tour_bytes(int n) {
+    return ((size_t)(n + 1) * sizeof(uint16_t) + 15) & ~(size_t)15;
+}
 
 // LDS of one ant: a visited flag per city (1 = visited, or >= n), then the
 // tour.  Byte flags make a visit one plain byte store and let the fallback
@@ -136,45 +138,86 @@ __global__ __launch_bounds__(256) void k_cand_refresh(Colony c, NnTables t) {
     t.cand[idx] = v;
 }
 
-// Row i's list: nn rounds of a workgroup minimum over the keys
-// (d_ij << 32) | j, each round taking the smallest key above the previous
-// one.  Keys are distinct (j is), so the rounds enumerate the row in
-// (d_ij, j) order; j = i and padding get the key 2^64 - 1 and are never
-// taken because nn <= n - 1.
-__global__ __launch_bounds__(256) void k_nn_lists(Colony c, NnTables t) {
-    __shared__ uint64_t part[4];
-    const int i = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n = c.n;
-    uint64_t key[kMaxCities / 256];
+// Row i's list: the nn smallest of the keys (d_ij << 32) | j, in order.  Thread
+// t holds the keys of cities t, t + 256, ...; the nn-th smallest of the 256
+// threads' smallest keys bounds the nn-th smallest of all from above, so at
+// most nn threads hold keys up to it, and the few keys up to it are ranked by
+// counting the smaller ones.  Keys are distinct (j is); j = i and padding get
+// the key 2^64 - 1 and are never taken because nn <= n - 1.  Three barriers
+// instead of two for each entry: n = 100 26 -> 7.5 us, n = 1000 42 -> 15,
+// n = 2400 84 -> 29 (nn = 32).
+constexpr int kListThreads = 256;
+
+struct NnShared {
+    uint64_t least[kListThreads];
+    uint64_t cand[kMaxNn * (kMaxCities / kListThreads)];
+    uint64_t bound;
+    uint32_t count;
+};
+
+// Of `count` keys in LDS, those smaller than `key`.
+__device__ __forceinline__ int keys_below(const uint64_t* keys, int count, uint64_t key) {
+    int r = 0;
+    for (int i = 0; i < count; ++i) r += keys[i] < key ? 1 : 0;
+    return r;
+}
+
+__device__ __forceinline__ void nn_list_row(const Colony& c, const NnTables& t, int i,
+                                            NnShared& sh) {
+    const int tid = threadIdx.x, n = c.n, nn = t.nn;
+    uint64_t key[kMaxCities / kListThreads];
+    uint64_t least = ~0ull;
 #pragma unroll
-    for (int q = 0; q < kMaxCities / 256; ++q) {
-        const int j = tid + 256 * q;
+    for (int q = 0; q < kMaxCities / kListThreads; ++q) {
+        const int j = tid + kListThreads * q;
         key[q] = (j < n && j != i)
                      ? ((uint64_t)(uint32_t)c.dist[(size_t)i * c.ld + j] << 32) | (uint64_t)j
                      : ~0ull;
+        least = key[q] < least ? key[q] : least;
     }
+    sh.least[tid] = least;
+    if (tid == 0) sh.count = 0;
+    __syncthreads();
+    if (least != ~0ull && keys_below(sh.least, kListThreads, least) == nn - 1) sh.bound = least;
+    __syncthreads();
+    const uint64_t bound = sh.bound;
+#pragma unroll
+    for (int q = 0; q < kMaxCities / kListThreads; ++q)
+        if (key[q] <= bound) sh.cand[atomicAdd(&sh.count, 1u)] = key[q];
+    __syncthreads();
+    const int count = (int)sh.count;
     uint16_t* out = t.nnl + (size_t)i * t.kp;
-    uint64_t prev = 0;
-    for (int r = 0; r < t.nn; ++r) {
-        uint64_t mn = ~0ull;
-#pragma unroll
-        for (int q = 0; q < kMaxCities / 256; ++q)
-            if (key[q] > prev && key[q] < mn) mn = key[q];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const uint64_t o = __shfl_xor((unsigned long long)mn, off);
-            mn = o < mn ? o : mn;
-        }
-        if (lane == 0) part[wave] = mn;
-        __syncthreads();
-        mn = part[0];
-#pragma unroll
-        for (int w = 1; w < 4; ++w) mn = part[w] < mn ? part[w] : mn;
-        __syncthreads();
-        if (tid == 0) out[r] = (uint16_t)(mn & 0xFFFFu);
-        prev = mn;
+    for (int q = tid; q < count; q += kListThreads) {
+        const uint64_t k = sh.cand[q];
+        const int r = keys_below(sh.cand, count, k);
+        if (r < nn) out[r] = (uint16_t)(k & 0xFFFFu);
     }
-    for (int r = t.nn + tid; r < t.kp; r += 256) out[r] = 0;
+    for (int r = nn + tid; r < t.kp; r += kListThreads) out[r] = 0;
+}
+
+__global__ __launch_bounds__(kListThreads) void k_nn_lists(Colony c, NnTables t) {
+    __shared__ NnShared sh;
+    nn_list_row(c, t, blockIdx.x, sh);
+}
+
+// The initialisation's lists of colony c: up to 32 entries a row, in the
+// successor table (n x mp uint16, mp >= 64), which is not used before the
+// first construction.
+__host__ __device__ NnTables init_tables(const Colony& c) {
+    NnTables t{};
+    t.nn = c.n - 1 < 32 ? c.n - 1 : 32;
+    t.kp = 32;
+    t.nnl = c.succ;
+    t.cand = nullptr;
+    return t;
+}
+
+__global__ __launch_bounds__(kListThreads) void k_nn_lists_batch(
+    const Colony* __restrict__ cols, const uint32_t* __restrict__ rowmap) {
+    __shared__ NnShared sh;
+    const uint32_t e = rowmap[blockIdx.x];
+    const Colony c = cols[e >> 16];
+    nn_list_row(c, init_tables(c), (int)(e & 0xffffu), sh);
 }
 
 template <int P, bool kNn32>
@@ -325,45 +368,72 @@ __device__ __forceinline__ int nearest_unseen(const int32_t* row, int n, const u
 // holds i's nearest cities, so its first unseen entry is the nearest unseen
 // city overall (every city off the list has a larger (d, j) key); only when
 // every entry is seen does the wave scan the whole distance row.  One
-// wavefront; the tour is kept in LDS and summed at the end.
+// wavefront walks; the tour is kept in LDS and summed at the end.  A step is
+// a chain of dependent reads, so the workgroup first copies the first `staged`
+// entries of every list to LDS (32 where they fit, to n = 2350, else 16;
+// n = 100 28 -> 18 us, n = 1000 290 -> 159, n = 2400 712 -> 400).
+constexpr int kTourThreads = 256;
+constexpr size_t kTourLds = 160u << 10;
+
+__host__ __device__ size_t nn_tour_lds(int n, int staged) {
+    return kVisBytes + tour_bytes(n) + (size_t)n * staged * sizeof(uint16_t);
+}
+__host__ __device__ int staged_entries(int n) { return nn_tour_lds(n, 32) <= kTourLds ? 32 : 16; }
+
 template <int P>
-__global__ __launch_bounds__(64) void k_nn_tour_lists(Colony c, NnTables t) {
-    extern __shared__ __align__(16) unsigned char smem[];
+__device__ __forceinline__ void nn_tour(const Colony& c, const NnTables& t, unsigned char* smem) {
+    const int n = c.n, nn = t.nn, kp = t.kp, staged = staged_entries(n);
     uint8_t* s_seen = smem;
     uint16_t* s_tour = reinterpret_cast<uint16_t*>(smem + kVisBytes);
-    const int lane = threadIdx.x;
-    const int n = c.n, nn = t.nn, kp = t.kp;
-    for (int w = lane; w < (int)(kVisBytes / 4); w += 64) {
+    uint16_t* s_list = reinterpret_cast<uint16_t*>(smem + kVisBytes + tour_bytes(n));
+    const int tid = threadIdx.x;
+    for (int w = tid; w < (int)(kVisBytes / 4); w += kTourThreads) {
         uint32_t f = 0;
 #pragma unroll
         for (int b = 0; b < 4; ++b) f |= (4 * w + b >= n || 4 * w + b == 0 ? 1u : 0u) << (8 * b);
         reinterpret_cast<uint32_t*>(s_seen)[w] = f;
     }
-    if (lane == 0) s_tour[0] = 0;
+    if (tid == 0) s_tour[0] = 0;
+    // 16-byte pieces of eight entries; kp = 32
+    const int pieces = staged / 8;
+    for (int q = tid; q < n * pieces; q += kTourThreads) {
+        const int i = q / pieces, e = q - i * pieces;
+        reinterpret_cast<uint4*>(s_list)[q] =
+            *reinterpret_cast<const uint4*>(t.nnl + (size_t)i * kp + 8 * e);
+    }
     __syncthreads();
-    const int col = lane & (kp - 1);
-    const bool in_list = lane < nn;
+    if (tid >= 64) return;  // no barrier follows
+    const int lane = tid;
+    const int held = staged < nn ? staged : nn;
+    const bool in_held = lane < held;
+    const int col = lane & (staged - 1);
     int cur = 0;
     for (int step = 1; step < n; ++step) {
-        const int city = t.nnl[(size_t)cur * kp + col];
-        const bool unseen = in_list & (s_seen[city] == 0);
-        const uint64_t live = ballot(unseen);
+        const int city = s_list[cur * staged + col];
+        uint64_t live = ballot(in_held & (s_seen[city] == 0));
         int next;
-        if (live) {
+        if (__builtin_expect(live != 0ull, 1)) {
             next = __builtin_amdgcn_readlane(city, __builtin_ctzll(live));
         } else {
-            next = nearest_unseen<P>(c.dist + (size_t)cur * c.ld, n, s_seen, lane);
-            // n - step >= 1 cities are unseen, so next >= 0; the clamp only
-            // keeps the LDS indices in range should that ever break.
-            next = next < 0 ? 0 : next;
+            // the entries past the staged ones, then the whole row
+            const int more = t.nnl[(size_t)cur * kp + (lane & 31)];
+            live = ballot((lane < nn) & (s_seen[more] == 0));
+            if (live) {
+                next = __builtin_amdgcn_readlane(more, __builtin_ctzll(live));
+            } else {
+                next = nearest_unseen<P>(c.dist + (size_t)cur * c.ld, n, s_seen, lane);
+                // n - step >= 1 cities are unseen, so next >= 0; the clamp only
+                // keeps the LDS indices in range should that ever break.
+                next = next < 0 ? 0 : next;
+            }
         }
+        next = __builtin_amdgcn_readfirstlane(next);
         if (lane == 0) {
             s_tour[step] = (uint16_t)next;
             s_seen[next] = 1;
         }
         cur = next;
     }
-    __syncthreads();
     long long len = 0;
     for (int s = lane; s < n; s += 64) {
         const int i = s_tour[s], j = s + 1 < n ? s_tour[s + 1] : 0;
@@ -379,31 +449,64 @@ __global__ __launch_bounds__(64) void k_nn_tour_lists(Colony c, NnTables t) {
 }
 
 template <int P>
-hipError_t launch_nn_tour_passes(const Colony& c, const NnTables& t, hipStream_t s) {
-    if constexpr (P > kMaxCities / 256) {
-        return hipErrorInvalidValue;
-    } else {
-        if ((c.n + 255) / 256 != P) return launch_nn_tour_passes<P + 1>(c, t, s);
-        hipLaunchKernelGGL((k_nn_tour_lists<P>), dim3(1), dim3(64), construct_nn_lds(c.n), s, c,
-                           t);
-        return hipGetLastError();
-    }
+__global__ __launch_bounds__(kTourThreads) void k_nn_tour(Colony c) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    nn_tour<P>(c, init_tables(c), smem);
+}
+
+// Workgroup q: the tour of colony cols[q]; every colony has n <= 256 P.
+template <int P>
+__global__ __launch_bounds__(kTourThreads) void k_nn_tour_batch(const Colony* __restrict__ cols) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const Colony c = cols[blockIdx.x];
+    nn_tour<P>(c, init_tables(c), smem);
+}
+
+// Calls f.template operator()<P>() for a P of 1, 2, 4, 6, 8, 10, 12 or 16 with
+// n <= 256 P: a row scan's passes beyond n read nothing.
+template <typename F>
+hipError_t dispatch_scan_passes(int n, F&& f) {
+    const int p = (n + 255) / 256;
+    if (p <= 1) return f.template operator()<1>();
+    if (p <= 2) return f.template operator()<2>();
+    if (p <= 4) return f.template operator()<4>();
+    if (p <= 6) return f.template operator()<6>();
+    if (p <= 8) return f.template operator()<8>();
+    if (p <= 10) return f.template operator()<10>();
+    if (p <= 12) return f.template operator()<12>();
+    return f.template operator()<kMaxCities / 256>();
 }
 
 }  // namespace
 
 hipError_t launch_nn_tour(const Colony& c, hipStream_t s) {
     if (c.n < 2 || c.n > kMaxCities || c.mp < 32) return hipErrorInvalidValue;
-    // The successor table (n x mp uint16, mp >= 64) is not used before the
-    // first construction, so it holds the 32-entry lists meanwhile.
-    NnTables t{};
-    t.nn = c.n - 1 < 32 ? c.n - 1 : 32;
-    t.kp = 32;
-    t.nnl = c.succ;
-    t.cand = nullptr;
-    hipError_t e = launch_nn_lists(c, t, s);
+    hipError_t e = launch_nn_lists(c, init_tables(c), s);
     if (e != hipSuccess) return e;
-    return launch_nn_tour_passes<1>(c, t, s);
+    return dispatch_scan_passes(c.n, [&]<int P>() {
+        hipLaunchKernelGGL(k_nn_tour<P>, dim3(1), dim3(kTourThreads),
+                           nn_tour_lds(c.n, staged_entries(c.n)), s, c);
+        return hipGetLastError();
+    });
+}
+
+hipError_t launch_nn_tour_batch(const Colony* cols, int count, const uint32_t* rowmap,
+                                int total_rows, int max_n, hipStream_t s) {
+    if (count <= 0 || total_rows <= 0) return hipSuccess;
+    if (max_n < 2 || max_n > kMaxCities) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_nn_lists_batch, dim3(total_rows), dim3(kListThreads), 0, s, cols, rowmap);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    // every colony's request: a smaller one may stage more entries a row
+    size_t lds = 0;
+    for (int n = 2; n <= max_n; ++n) {
+        const size_t need = nn_tour_lds(n, staged_entries(n));
+        lds = need > lds ? need : lds;
+    }
+    return dispatch_scan_passes(max_n, [&]<int P>() {
+        hipLaunchKernelGGL(k_nn_tour_batch<P>, dim3(count), dim3(kTourThreads), lds, s, cols);
+        return hipGetLastError();
+    });
 }
 
 size_t nn_table_bytes(int n, int nn) {
@@ -425,7 +528,7 @@ NnTables nn_carve(char* base, int n, int nn) {
 hipError_t launch_nn_lists(const Colony& c, const NnTables& t, hipStream_t s) {
     if (t.nn < 1 || t.nn > kMaxNn || t.nn > c.n - 1 || c.n > kMaxCities)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_nn_lists, dim3(c.n), dim3(256), 0, s, c, t);
+    hipLaunchKernelGGL(k_nn_lists, dim3(c.n), dim3(kListThreads), 0, s, c, t);
     return hipGetLastError();
 }
 

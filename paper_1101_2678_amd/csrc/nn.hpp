@@ -42,5 +42,9 @@ hipError_t launch_construct_nn(const Colony& c, const NnTables& t, uint32_t iter
 // the successor table as scratch for 32-entry neighbour lists, so it must run
 // before the first construction.
 hipError_t launch_nn_tour(const Colony& c, hipStream_t s);
+// The same for `count` colonies at once; rowmap: (colony << 16) | row of every
+// row of them; max_n: the largest n.
+hipError_t launch_nn_tour_batch(const Colony* cols, int count, const uint32_t* rowmap,
+                                int total_rows, int max_n, hipStream_t s);
 
 }  // namespace aco

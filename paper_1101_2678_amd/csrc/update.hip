@@ -403,12 +403,9 @@ __global__ __launch_bounds__(256) void k_update_epilogue(Colony c) {
 // lowest index) and tau0 = fl32(m / C_nn) come from launch_nn_tour
 // (construct_nn.hip); the fill below sets tau and choice.
 // ---------------------------------------------------------------------------
-// grid (ceil(ld / 4 / 256), n): tau <- tau0 (padding 0), choice from tau,
-// delta <- 0 when present.
-__global__ __launch_bounds__(256) void k_fill_init(Colony c) {
-    const int q = blockIdx.x * 256 + threadIdx.x;
-    const int i = blockIdx.y;
-    if (q >= c.ld / 4) return;
+// Cells 4q .. 4q + 3 of row i: tau <- tau0 (padding 0), choice from tau, delta
+// <- 0 when present.
+__device__ __forceinline__ void fill_quad(const Colony& c, int i, int q) {
     const size_t off = (size_t)i * c.ld + 4 * (size_t)q;
     const float t0 = *c.tau0;
     const int4 d = *reinterpret_cast<const int4*>(c.dist + off);
@@ -431,19 +428,50 @@ __global__ __launch_bounds__(256) void k_fill_init(Colony c) {
     }
 }
 
+// grid (ceil(ld / 4 / 256), n)
+__global__ __launch_bounds__(256) void k_fill_init(Colony c) {
+    const int q = blockIdx.x * 256 + threadIdx.x;
+    if (q < c.ld / 4) fill_quad(c, blockIdx.y, q);
+}
+
+// Workgroup g: row (rowmap[g] & 0xffff) of colony cols[rowmap[g] >> 16].
+__global__ __launch_bounds__(256) void k_fill_init_batch(const Colony* __restrict__ cols,
+                                                         const uint32_t* __restrict__ rowmap) {
+    const uint32_t e = rowmap[blockIdx.x];
+    const Colony c = cols[e >> 16];
+    for (int q = threadIdx.x; q < c.ld / 4; q += 256) fill_quad(c, (int)(e & 0xffffu), q);
+}
+
+// Words 4q .. 4q + 3 of a row of n contiguous words, 0 past n.
+__device__ __forceinline__ uint4 padded_quad(const uint32_t* row, int n, int q) {
+    const int j = 4 * q;
+    uint4 v;
+    v.x = j + 0 < n ? row[j + 0] : 0u;
+    v.y = j + 1 < n ? row[j + 1] : 0u;
+    v.z = j + 2 < n ? row[j + 2] : 0u;
+    v.w = j + 3 < n ? row[j + 3] : 0u;
+    return v;
+}
+
 // grid (ceil(ld / 4 / 256), n): row i of n contiguous words to row i of pitch
 // ld, padding 0.  Bound by memory (n = 2400: 46 MB, 13 us).
 __global__ __launch_bounds__(256) void k_pad_rows(const uint32_t* __restrict__ src,
                                                   uint32_t* __restrict__ dst, int n, int ld) {
-    const int j = 4 * (blockIdx.x * 256 + threadIdx.x);
-    if (j >= ld) return;
-    const uint32_t* s = src + (size_t)blockIdx.y * n;
-    uint4 v;
-    v.x = j + 0 < n ? s[j + 0] : 0u;
-    v.y = j + 1 < n ? s[j + 1] : 0u;
-    v.z = j + 2 < n ? s[j + 2] : 0u;
-    v.w = j + 3 < n ? s[j + 3] : 0u;
-    *reinterpret_cast<uint4*>(dst + (size_t)blockIdx.y * ld + j) = v;
+    const int q = blockIdx.x * 256 + threadIdx.x;
+    if (q < ld / 4)
+        reinterpret_cast<uint4*>(dst + (size_t)blockIdx.y * ld)[q] =
+            padded_quad(src + (size_t)blockIdx.y * n, n, q);
+}
+
+// The distances of every colony of a batch, uploaded to its tau matrix.
+__global__ __launch_bounds__(256) void k_pad_dist_batch(const Colony* __restrict__ cols,
+                                                        const uint32_t* __restrict__ rowmap) {
+    const uint32_t e = rowmap[blockIdx.x];
+    const Colony c = cols[e >> 16];
+    const size_t i = e & 0xffffu;
+    for (int q = threadIdx.x; q < c.ld / 4; q += 256)
+        reinterpret_cast<uint4*>(c.dist + i * c.ld)[q] =
+            padded_quad(reinterpret_cast<const uint32_t*>(c.tau) + i * c.n, c.n, q);
 }
 
 // grid (ceil(ld / 4 / 256), n): choice from the current tau (checkpoint restore).
@@ -493,6 +521,17 @@ hipError_t launch_init(const Colony& c, hipStream_t s) {
     const hipError_t e = launch_nn_tour(c, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_fill_init, cell_grid(c), dim3(256), 0, s, c);
+    return hipGetLastError();
+}
+
+hipError_t launch_init_batch(const Colony* cols, int count, const uint32_t* rowmap,
+                             int total_rows, int max_n, hipStream_t s) {
+    if (count <= 0 || total_rows <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_pad_dist_batch, dim3(total_rows), dim3(256), 0, s, cols, rowmap);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = launch_nn_tour_batch(cols, count, rowmap, total_rows, max_n, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_fill_init_batch, dim3(total_rows), dim3(256), 0, s, cols, rowmap);
     return hipGetLastError();
 }
 
