@@ -38,6 +38,7 @@
 #include <type_traits>
 
 #include "construct_flat.hpp"
+#include "construct_masked.hpp"
 #include "r64_lanes.hpp"
 #include "shortlist.hpp"
 
@@ -294,7 +295,13 @@ constexpr int kMinListCities = 256;
 // the city itself.
 __host__ __device__ size_t seen_lds_bytes(int n) { return ((size_t)n + 511) & ~(size_t)511; }
 
+// Dynamic LDS of an ant: the tour, then the flags.
 __host__ __device__ size_t ant_lds_bytes(int n) { return tour_lds_bytes(n) + seen_lds_bytes(n); }
+
+// The same for an ant that keeps the visited set as factors.
+__host__ __device__ size_t masked_lds_bytes(int n) {
+    return tour_lds_bytes(n) + seen_lds_bytes(n) * sizeof(float);
+}
 
 // The lane and block bits of the general step from the flags of the ant's P
 // passes.  s_bits: 64 P bytes of scratch.
@@ -426,7 +433,7 @@ __device__ __forceinline__ void construct_ant_flat(const Colony& c, int k, uint3
                 s_tour[i] = (uint16_t)at;
                 s_seen[at] = 1;
             }
-            int j = roulette_list_pick(entry, s_seen, u, lane);
+            int j = roulette_list_pick(entry, s_seen[list_city(entry.y)] == 0, u, lane);
             if (__builtin_expect(j < 0, 0)) {
                 uint32_t x[B];
                 load_flat<B>(c.choice, records, at, row_bytes, lane, x);
@@ -444,6 +451,62 @@ __device__ __forceinline__ void construct_ant_flat(const Colony& c, int k, uint3
         });
     }
     finish_ant(c, k, cur, s_tour, lane);
+}
+
+// LDS of a masked ant: the row as loaded and its block totals.
+template <int P>
+struct MaskedShared {
+    float w[512 * P];
+    float T[64];
+};
+
+// The whole tour of ant k for rows of P passes of 512 cities, P <= 3.
+template <int P>
+__device__ __forceinline__ void construct_ant_masked(const Colony& c, int k, uint32_t iter,
+                                                     uint16_t* s_tour, float* s_w, float* s_T,
+                                                     int lane) {
+    const int n = c.n;
+    const int row_bytes = c.ld * 4, records = n * row_bytes;
+    const PhiloxKey key{(uint32_t)c.seed, (uint32_t)(c.seed >> 32)};
+    float* s_f = reinterpret_cast<float*>(reinterpret_cast<char*>(s_tour) + tour_lds_bytes(n));
+    init_factors<P>(s_f, n, lane);
+    s_T[lane] = 0.0f;
+    int cur;
+    if (starts_from_lists(c, lane)) {
+        // as in construct_ant
+        const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
+        cur = walk<false>(n, key, iter, k, s_tour, lane, [&](int at, float u, int i) {
+            const u32x2 entry = load_list(lists, at, lane);
+            if (lane == 0) {
+                s_tour[i] = (uint16_t)at;
+                s_f[at] = 0.0f;
+            }
+            int j = roulette_list_pick(entry, s_f[list_city(entry.y)] != 0.0f, u, lane);
+            if (__builtin_expect(j < 0, 0)) {
+                u32x4 wa[P], wb[P];
+                load_passes<P>(c.choice, records, at, row_bytes, lane, wa, wb);
+                j = pick_masked<P>(wa, wb, n, s_f, s_T, s_w, u, lane);
+            }
+            return j < 0 ? 0 : j;
+        });
+    } else {
+        cur = walk<true>(n, key, iter, k, s_tour, lane, [&](int at, float u, int) {
+            u32x4 wa[P], wb[P];
+            load_passes<P>(c.choice, records, at, row_bytes, lane, wa, wb);
+            if (lane == 0) s_f[at] = 0.0f;
+            const int j = pick_masked<P>(wa, wb, n, s_f, s_T, s_w, u, lane);
+            return j < 0 ? 0 : j;
+        });
+    }
+    finish_ant(c, k, cur, s_tour, lane);
+}
+
+template <int P>
+__global__ __launch_bounds__(64) void k_construct_masked(Colony c, uint32_t iter) {
+    extern __shared__ __align__(16) uint16_t s_tour[];
+    __shared__ __align__(16) MaskedShared<P> sh;
+    construct_ant_masked<P>(c, ant_of_block(blockIdx.x, c.m), iter, s_tour, sh.w, sh.T,
+                            threadIdx.x);
 }
 
 template <int B>
@@ -498,7 +561,7 @@ __device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t i
                 s_tour[i] = (uint16_t)at;
                 s_seen[at] = 1;
             }
-            int j = roulette_list_pick(entry, s_seen, u, lane);
+            int j = roulette_list_pick(entry, s_seen[list_city(entry.y)] == 0, u, lane);
             if (__builtin_expect(j < 0, 0)) {
                 bits_from_flags<P>(reinterpret_cast<const uint2*>(s_seen),
                                    reinterpret_cast<uint8_t*>(sh.w), lane, lane_bits, block_bits);
@@ -548,6 +611,11 @@ __global__ __launch_bounds__(64) void k_construct(Colony c, uint32_t iter) {
 template <int NP>
 constexpr bool kBatchLoadFirst = NP < 4;
 
+// Rows of one to three passes keep the bits here, which skip the loads of
+// visited quads, and not the factors of the single-instance launch: with
+// those, 64 instances of 50 to 1000 cities took 70.4 ms against 66.1, ten
+// served requests 243 against 229 (more LDS an ant, and no load skipped where
+// thousands of ants share the L2).
 // The ant's code for its colony's exact pass count NP (1 .. PMAX): each
 // instance runs a loop specialised for its row length, with no per-pass
 // test of the pass count inside the step (256 instances, n 50..1000: 757 ->
@@ -630,6 +698,24 @@ __global__ __launch_bounds__(64) void k_test_select(const float* rows, int ld, i
     if (lane == 0) out[q] = j;
 }
 
+template <int P>
+__global__ __launch_bounds__(64) void k_test_select_masked(const float* rows, int ld, int n,
+                                                           const uint8_t* feasible,
+                                                           const float* us, int32_t* out) {
+    __shared__ __align__(16) MaskedShared<P> sh;
+    __shared__ __align__(16) float s_f[512 * P];
+    const int lane = threadIdx.x;
+    const int q = blockIdx.x;
+    const uint8_t* f = feasible + (size_t)q * n;
+    for (int j = lane; j < 512 * P; j += 64) s_f[j] = j < n && f[j] ? 1.0f : 0.0f;
+    sh.T[lane] = 0.0f;
+    __syncthreads();
+    u32x4 wa[P], wb[P];
+    load_passes<P>(rows + (size_t)q * ld, ((n + 3) & ~3) * 4, 0, ld * 4, lane, wa, wb);
+    const int j = pick_masked<P>(wa, wb, n, s_f, sh.T, sh.w, us[q], lane);
+    if (lane == 0) out[q] = j;
+}
+
 template <int B>
 __global__ __launch_bounds__(64) void k_test_select_flat(const float* rows, int ld, int n,
                                                          const uint8_t* feasible, const float* us,
@@ -680,7 +766,8 @@ int batch_default_cap(int total_ants, int cus) {
 namespace {
 
 // Calls f.template operator()<G, P>() for the tile and pass count of n, or
-// with G = 0 and the number of 64-city blocks for rows of the flat layout.
+// with G = 0 and the number of 64-city blocks for rows of the flat layout, or
+// with G = 1 and the pass count for tile 8 with the visited set as factors.
 template <int B = 1, typename F>
 hipError_t dispatch_flat(int n, F&& f) {
     if constexpr (B > kMaxFlatBlocks) {
@@ -695,14 +782,23 @@ template <int G, int P>
 auto test_select_kernel() {
     if constexpr (G == 0)
         return k_test_select_flat<P>;
+    else if constexpr (G == 1)
+        return k_test_select_masked<P>;
     else
         return k_test_select<G, P>;
+}
+
+template <int G>
+size_t construct_lds_bytes(int n) {
+    return G == 1 ? masked_lds_bytes(n) : ant_lds_bytes(n);
 }
 
 template <int G, int P>
 auto construct_kernel() {
     if constexpr (G == 0)
         return k_construct_flat<P>;
+    else if constexpr (G == 1)
+        return k_construct_masked<P>;
     else
         return k_construct<G, P>;
 }
@@ -723,9 +819,9 @@ hipError_t dispatch_tile(int tile, int n, F&& f) {
         }
     }
     switch ((n + 511) / 512) {
-        case 1: return f.template operator()<8, 1>();
-        case 2: return f.template operator()<8, 2>();
-        case 3: return f.template operator()<8, 3>();
+        case 1: return f.template operator()<1, 1>();
+        case 2: return f.template operator()<1, 2>();
+        case 3: return f.template operator()<1, 3>();
         case 4: return f.template operator()<8, 4>();
         case 5: return f.template operator()<8, 5>();
         case 6: return f.template operator()<8, 6>();
@@ -748,7 +844,8 @@ int construct_occupancy(const Colony& c) {
     int blocks = -1;
     (void)dispatch_tile(c.tile, c.n, [&]<int G, int P>() {
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, construct_kernel<G, P>(), 64,
-                                                         ant_lds_bytes(c.n)) != hipSuccess)
+                                                         construct_lds_bytes<G>(c.n)) !=
+            hipSuccess)
             blocks = -1;
         return hipSuccess;
     });
@@ -763,8 +860,8 @@ hipError_t launch_construct(const Colony& c, uint32_t iter, hipStream_t s) {
         if (e != hipSuccess) return e;
     }
     return dispatch_tile(c.tile, c.n, [&]<int G, int P>() {
-        hipLaunchKernelGGL((construct_kernel<G, P>()), dim3(c.m), dim3(64), ant_lds_bytes(c.n), s,
-                           c, iter);
+        hipLaunchKernelGGL((construct_kernel<G, P>()), dim3(c.m), dim3(64),
+                           construct_lds_bytes<G>(c.n), s, c, iter);
         return hipGetLastError();
     });
 }

@@ -32,11 +32,12 @@ constexpr float kLargest = 0x1.0p100f;
 // iteration on (58% settled, 0.526 ms against 0.526 ms without; the sixth
 // 0.679 against 0.530, the eleventh 0.382 against 0.520), when half of the
 // rows leave 2% to the tail; rows of up to 512 cities, whose own step is
-// shorter, one iteration later (n = 300: the ninth).  Longer rows are bound by memory, and the short
+// shorter, two iterations later (n = 500: 0.183 against 0.184 ms in the
+// ninth).  Longer rows are bound by memory, and the short
 // reads leave room for the others from the first iteration (n = 2400: 5.9
 // against 6.1 ms, n = 2000 3.49 against 3.38 ms, n = 1800 3.00 against 2.37).
 __device__ __forceinline__ float by_list_share(int n) {
-    return n <= 512 ? 0.01f : n < 2000 ? 0.02f : 1.0f;
+    return n <= 512 ? 0.004f : n < 2000 ? 0.02f : 1.0f;
 }
 
 struct ListShared {

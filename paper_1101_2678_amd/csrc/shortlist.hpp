@@ -53,8 +53,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t list_rsrc(const Colony& c) {
 }
 
 // The roulette's selection from a row's short list alone (v: the lane's
-// entry, u: the step's draw), or -1 where it needs the whole row.  s_seen:
-// city j's visited flag in byte j.
+// entry, unvisited: whether its city is, u: the step's draw), or -1 where it
+// needs the whole row.
 //
 // The rule over the whole row picks the lowest unvisited city j whose prefix
 // P_j exceeds target = fl32(u total).  With L_j the listed unvisited weight up
@@ -70,12 +70,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t list_rsrc(const Colony& c) {
 // above 2^-100 keeps the products normal, and build_list keeps every sum
 // below 2^101.)  Only one lane can pass both tests, and it is unvisited: with
 // w_j = 0 they contradict each other.
-__device__ __forceinline__ int roulette_list_pick(u32x2 v, const uint8_t* s_seen, float u,
-                                                  int lane) {
+__device__ __forceinline__ int roulette_list_pick(u32x2 v, bool unvisited, float u, int lane) {
     // u with the margin to either side, off the chain of the sums
     const float u_over = u * (1.0f + 0x1.0p-18f), u_under = u * (1.0f - 0x1.0p-18f);
     const int city = list_city(v.y);
-    const bool unvisited = s_seen[city] == 0;
     const float above = list_tail(v.y);
     const bool may = (lane < kListEntries) & unvisited;
     const float w = may ? __uint_as_float(v.x) : 0.0f;

@@ -1,5 +1,7 @@
-"""The roulette step of short rows (one city of every 64-city block per lane,
-construct_flat.hpp) at the edges of its blocks, against the oracle."""
+"""The roulette steps of short rows (one city of every 64-city block per lane,
+construct_flat.hpp) and of rows of one to three passes (visited set as factors,
+construct_masked.hpp) at the edges of their blocks and passes, against the
+oracle."""
 from __future__ import annotations
 
 import numpy as np
@@ -12,9 +14,10 @@ from gpu_helpers import compare_run
 pytestmark = pytest.mark.gpu
 
 EDGES = [2, 63, 64, 65, 127, 128, 129, 191, 192, 193, 256, 257, 319, 320, 321]
+PASSES = [385, 511, 512, 513, 1023, 1024, 1025, 1535, 1536, 1537]
 
 
-@pytest.mark.parametrize("n", EDGES)
+@pytest.mark.parametrize("n", EDGES + PASSES)
 def test_select(n):
     import torch
     from paper_1101_2678_amd import aco
@@ -31,3 +34,9 @@ def test_select(n):
 def test_parity(n):
     _, d = tsp_inputs.instance(n, "cluster" if n % 2 else "uniform", side=10_000, seed=n + 1)
     compare_run(d, 70, 1, 2, 0.5, seed=n, iters=2, kinds=("gather",))
+
+
+@pytest.mark.parametrize("n", PASSES)
+def test_parity_passes(n):
+    _, d = tsp_inputs.instance(n, "uniform", seed=n + 2)
+    compare_run(d, 20, 1, 2, 0.5, seed=n, iters=2, kinds=("gather",))
