@@ -83,6 +83,36 @@ __device__ __forceinline__ float s64_scan(float x) {
     return x;
 }
 
+// S64 of B values a lane side by side, level by level, so that each one's steps
+// fill the others' wait states.  Stage B adds in place (rows masked off keep
+// their value): of s64_scan's the compiler makes a cleared register, a move
+// and an add each.
+template <int B>
+__device__ __forceinline__ void s64_scans(float (&s)[B]) {
+    const auto level = [&]<int kCtrl>() {
+#pragma unroll
+        for (int b = 0; b < B; ++b) s[b] = s[b] + dpp_move<kCtrl, 0xF>(s[b]);
+    };
+    level.template operator()<0x111>();
+    level.template operator()<0x112>();
+    level.template operator()<0x114>();
+    level.template operator()<0x118>();
+#pragma unroll
+    for (int b = 0; b < B; ++b)
+        asm("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf"
+            : "+v"(s[b]));
+#pragma unroll
+    for (int b = 0; b < B; ++b)
+        asm("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf"
+            : "+v"(s[b]));
+}
+
+__device__ __forceinline__ float s64_scan_in_place(float x) {
+    float s[1] = {x};
+    s64_scans<1>(s);
+    return s[0];
+}
+
 // The first L levels of stage A (L = 1..4).  On lanes 0 .. 2^L - 1 of
 // non-negative values this equals s64_scan (stage B leaves row 0 as it is,
 // and the later levels of stage A would add +0 there, their source lane

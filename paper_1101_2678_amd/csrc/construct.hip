@@ -40,6 +40,7 @@
 #include "construct_flat.hpp"
 #include "construct_masked.hpp"
 #include "r64_lanes.hpp"
+#include "seen.hpp"
 #include "shortlist.hpp"
 
 namespace aco {
@@ -290,43 +291,12 @@ template <int G>
 constexpr bool kUseLists = G == 8;
 constexpr int kMinListCities = 256;
 
-// Visited flags: one byte a city of the row's passes, 1 = visited or beyond
-// n.  A visit is one byte store, and a listed city's flag one byte load at
-// the city itself.
-__host__ __device__ size_t seen_lds_bytes(int n) { return ((size_t)n + 511) & ~(size_t)511; }
-
 // Dynamic LDS of an ant: the tour, then the flags.
 __host__ __device__ size_t ant_lds_bytes(int n) { return tour_lds_bytes(n) + seen_lds_bytes(n); }
 
 // The same for an ant that keeps the visited set as factors.
 __host__ __device__ size_t masked_lds_bytes(int n) {
     return tour_lds_bytes(n) + seen_lds_bytes(n) * sizeof(float);
-}
-
-// The lane and block bits of the general step from the flags of the ant's P
-// passes.  s_bits: 64 P bytes of scratch.
-template <int P, typename B>
-__device__ __forceinline__ void bits_from_flags(const uint2* s_seen, uint8_t* s_bits, int lane,
-                                                B& lane_bits, uint64_t& block_bits) {
-    // four bytes of 0 or 1 to four bits
-    const auto four = [](uint32_t x) { return (x * 0x10204080u) >> 28; };
-    uint32_t seen[P];
-    lane_bits = 0;
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-        const uint2 f = s_seen[64 * p + lane];  // cities 512 p + 8 lane .. + 7
-        seen[p] = four(f.x) | four(f.y) << 4;
-        lane_bits |= (B)(seen[p] ^ 0xFFu) << (8 * p);
-    }
-#pragma unroll
-    for (int p = 0; p < P; ++p) s_bits[64 * p + lane] = (uint8_t)seen[p];
-    // block b: the eight bytes from 8 b
-    block_bits = ~0ull;
-    if (lane < 8 * P) {
-        block_bits = 0;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) block_bits |= (uint64_t)s_bits[8 * lane + e] << (8 * e);
-    }
 }
 
 // Whether the roulette of colony c starts its steps from the short lists:
@@ -398,20 +368,6 @@ __device__ __forceinline__ int walk(int n, PhiloxKey key, uint32_t iter, int k, 
     return cur;
 }
 
-// Visited flags of the ant's first `cities` cities (a multiple of 512): 0, or
-// 1 beyond n.
-__device__ __forceinline__ uint8_t* clear_flags(uint16_t* s_tour, int n, int cities, int lane) {
-    uint8_t* s_seen = reinterpret_cast<uint8_t*>(s_tour) + tour_lds_bytes(n);
-    for (int w = lane; w < cities / 4; w += 64) {
-        uint32_t f = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) f |= (4 * w + e >= n ? 1u : 0u) << (8 * e);
-        reinterpret_cast<uint32_t*>(s_seen)[w] = f;
-    }
-    __builtin_amdgcn_wave_barrier();
-    return s_seen;
-}
-
 // The whole tour of ant k for rows of at most B blocks of 64 cities.
 template <int B, bool LIST>
 __device__ __forceinline__ void construct_ant_flat(const Colony& c, int k, uint32_t iter,
@@ -426,21 +382,20 @@ __device__ __forceinline__ void construct_ant_flat(const Colony& c, int k, uint3
     if (LIST && by_list) {
         // as in construct_ant
         const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
-        uint8_t* s_seen = clear_flags(s_tour, n, 512, lane);
+        uint8_t* s_seen = clear_flags(reinterpret_cast<uint8_t*>(s_tour) + tour_lds_bytes(n), n, 512, lane);
         cur = walk<false>(n, key, iter, k, s_tour, lane, [&](int at, float u, int i) {
             const u32x2 entry = load_list(lists, at, lane);
             if (lane == 0) {
                 s_tour[i] = (uint16_t)at;
                 s_seen[at] = 1;
             }
-            int j = roulette_list_pick(entry, s_seen[list_city(entry.y)] == 0, u, lane);
-            if (__builtin_expect(j < 0, 0)) {
-                uint32_t x[B];
-                load_flat<B>(c.choice, records, at, row_bytes, lane, x);
-                live.from_flags(s_seen, lane);
-                j = pick_flat<B>(x, live, u);
-            }
-            return j;
+            const bool unvisited = s_seen[list_city(entry.y)] == 0;
+            const uint64_t hit = roulette_list_hit(entry, list_weight(entry, unvisited, lane), u);
+            if (__builtin_expect(hit != 0, 1)) return hit_city(entry, hit);
+            uint32_t x[B];
+            load_flat<B>(c.choice, records, at, row_bytes, lane, x);
+            live.from_flags(s_seen, lane);
+            return pick_flat<B>(x, live, u);
         });
     } else {
         cur = walk<true>(n, key, iter, k, s_tour, lane, [&](int at, float u, int) {
@@ -481,12 +436,12 @@ __device__ __forceinline__ void construct_ant_masked(const Colony& c, int k, uin
                 s_tour[i] = (uint16_t)at;
                 s_f[at] = 0.0f;
             }
-            int j = roulette_list_pick(entry, s_f[list_city(entry.y)] != 0.0f, u, lane);
-            if (__builtin_expect(j < 0, 0)) {
-                u32x4 wa[P], wb[P];
-                load_passes<P>(c.choice, records, at, row_bytes, lane, wa, wb);
-                j = pick_masked<P>(wa, wb, n, s_f, s_T, s_w, u, lane);
-            }
+            const float w = __uint_as_float(entry.x) * s_f[list_city(entry.y)];
+            const uint64_t hit = roulette_list_hit(entry, lane < kListEntries ? w : 0.0f, u);
+            if (__builtin_expect(hit != 0, 1)) return hit_city(entry, hit);
+            u32x4 wa[P], wb[P];
+            load_passes<P>(c.choice, records, at, row_bytes, lane, wa, wb);
+            const int j = pick_masked<P>(wa, wb, n, s_f, s_T, s_w, u, lane);
             return j < 0 ? 0 : j;
         });
     } else {
@@ -549,25 +504,25 @@ __device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t i
         // the list does not settle the selection.  The usual step keeps the
         // flags only; the general step's bits are made from them.  m = n,
         // construction with the lists' launch against whole rows only, in
-        // the 20th iteration: n = 500 0.154 / 0.197 ms, n = 1000 0.315 /
-        // 0.508, n = 1500 0.541 / 1.31, n = 2400 1.14 / 6.05, n = 3000 1.76 /
-        // 13.3; mean of the first 24: 0.177 / 0.198, 0.402 / 0.519, 0.868 /
-        // 1.32, 2.63 / 6.05, 5.19 / 13.2.
+        // the 20th iteration: n = 500 0.136 / 0.197 ms, n = 1000 0.285 /
+        // 0.508, n = 1500 0.496 / 1.31, n = 2400 1.10 / 6.05, n = 3000 1.68 /
+        // 13.3; mean of the first 24: 0.157 / 0.198, 0.363 / 0.519, 0.791 /
+        // 1.32, 2.61 / 6.05, 5.10 / 13.2.
         const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
-        uint8_t* s_seen = clear_flags(s_tour, n, 512 * P, lane);
+        uint8_t* s_seen = clear_flags(reinterpret_cast<uint8_t*>(s_tour) + tour_lds_bytes(n), n, 512 * P, lane);
         cur = walk<false>(n, key, iter, k, s_tour, lane, [&](int at, float u, int i) {
             const u32x2 entry = load_list(lists, at, lane);
             if (lane == 0) {
                 s_tour[i] = (uint16_t)at;
                 s_seen[at] = 1;
             }
-            int j = roulette_list_pick(entry, s_seen[list_city(entry.y)] == 0, u, lane);
-            if (__builtin_expect(j < 0, 0)) {
-                bits_from_flags<P>(reinterpret_cast<const uint2*>(s_seen),
-                                   reinterpret_cast<uint8_t*>(sh.w), lane, lane_bits, block_bits);
-                j = r64_pick<G, P, SKIP>(c.choice, records, at, row_bytes, n, lane_bits,
-                                         block_bits, sh.T, sh.w, u, lane);
-            }
+            const bool unvisited = s_seen[list_city(entry.y)] == 0;
+            const uint64_t hit = roulette_list_hit(entry, list_weight(entry, unvisited, lane), u);
+            if (__builtin_expect(hit != 0, 1)) return hit_city(entry, hit);
+            bits_from_flags<P>(reinterpret_cast<const uint2*>(s_seen),
+                               reinterpret_cast<uint8_t*>(sh.w), lane, lane_bits, block_bits);
+            const int j = r64_pick<G, P, SKIP>(c.choice, records, at, row_bytes, n, lane_bits,
+                                               block_bits, sh.T, sh.w, u, lane);
             return j < 0 ? 0 : j;
         });
     } else {

@@ -84,26 +84,7 @@ __device__ __forceinline__ int pick_flat(const uint32_t (&x)[B], const Unvisited
     float s[B], t[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) s[b] = keep_lanes(__uint_as_float(x[b]), live.word[b]);
-    // the levels of S64 block by block, so that each block's steps fill the
-    // others' wait states
-    const auto level = [&]<int kCtrl, int kRowMask>() {
-#pragma unroll
-        for (int b = 0; b < B; ++b) s[b] = s[b] + dpp_move<kCtrl, kRowMask>(s[b]);
-    };
-    level.template operator()<0x111, 0xF>();
-    level.template operator()<0x112, 0xF>();
-    level.template operator()<0x114, 0xF>();
-    level.template operator()<0x118, 0xF>();
-    // stage B in place (rows masked off keep their value): the compiler makes
-    // a cleared register, a move and an add of each
-#pragma unroll
-    for (int b = 0; b < B; ++b)
-        asm("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf"
-            : "+v"(s[b]));
-#pragma unroll
-    for (int b = 0; b < B; ++b)
-        asm("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf"
-            : "+v"(s[b]));
+    s64_scans<B>(s);
     // S64 over the block totals, which lane 63 holds: a Kogge-Stone scan
 #pragma unroll
     for (int b = 0; b < B; ++b) t[b] = s[b];

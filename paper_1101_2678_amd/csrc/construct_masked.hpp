@@ -8,10 +8,9 @@
 // multiplications (exact: w * 1 = w, w * +0 = +0), one fused with the pair's
 // addition: fl(w0 f0 + w1 f1) with both products exact is fl(w0 + w1) of the
 // masked weights, so every block total has the same bits.  A visit is one
-// store.  Bits / factors, m = n, first iteration (whole rows) and 20th (lists):
-// n = 400 0.171 -> 0.149 ms, 0.123 both; n = 700 0.356 -> 0.325, 0.218 ->
-// 0.214; n = 1000 0.516 -> 0.485, 0.317 -> 0.309; n = 1500 1.37 -> 1.28, 0.541
-// -> 0.534.
+// store.  Bits / factors, m = n, first iteration (whole rows): n = 400
+// 0.171 -> 0.149 ms, n = 700 0.356 -> 0.325, n = 1000 0.516 -> 0.485, n =
+// 1500 1.37 -> 1.28.
 #pragma once
 
 #include "construct_flat.hpp"

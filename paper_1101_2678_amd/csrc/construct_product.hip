@@ -28,6 +28,7 @@
 #include "aco_device.hpp"
 #include "aco_state.hpp"
 #include "product.hpp"
+#include "seen.hpp"
 #include "shortlist.hpp"
 
 namespace aco {
@@ -39,7 +40,9 @@ constexpr int kG = 8;              // cities per lane per pass
 constexpr int kPass = 64 * kG;     // cities per pass
 constexpr int kMaxPasses = kMaxCities / kPass;
 
-size_t tour_bytes(int n) { return ((size_t)(n + 1) * sizeof(uint16_t) + 15) & ~(size_t)15; }
+__host__ __device__ size_t tour_bytes(int n) {
+    return ((size_t)(n + 1) * sizeof(uint16_t) + 15) & ~(size_t)15;
+}
 
 // a ^ b ^ k in one v_bitop3_b32 (truth table 0x96); k is wave-uniform.
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t k) {
@@ -248,92 +251,73 @@ __device__ __forceinline__ Pick product_pick(const float* row, int n, uint64_t b
     return Pick{0u, wave_min_u32(low)};
 }
 
-// The selection from the row's short list alone (v: the lane's entry), or -1
-// where it needs the whole row.  s_vis: visited bits of city j in bit j mod 32
-// of word j / 32.  A city off the list has a choice value of at most M, its
-// tail's largest, and draws r < 1, so its product, rounded, is at most M: a
-// listed unvisited city whose product exceeds M beats them all, and the list
-// is in city order, so the lowest lane holding the largest product is the
-// lowest city.  One Philox block a lane instead of two per pass.
-__device__ __forceinline__ int product_list_pick(u32x2 v, const uint32_t* s_vis, uint32_t k0,
-                                                 uint32_t k1, uint32_t step, uint32_t ant,
-                                                 uint32_t iter, int lane) {
+// The selection from the row's short list alone (v: the lane's entry,
+// unvisited: whether its city is): the lanes that hold the largest product, or
+// 0 where the step needs the whole row.  A city off the list has a choice
+// value of at most M, its tail's largest, and draws r < 1, so its product,
+// rounded, is at most M: a listed unvisited city whose product exceeds M beats
+// them all, and the list is in city order, so the lowest lane holding the
+// largest product is the lowest city.  One Philox block a lane instead of two
+// per pass.
+__device__ __forceinline__ uint64_t product_list_hit(u32x2 v, bool unvisited, uint32_t k0,
+                                                     uint32_t k1, uint32_t step, uint32_t ant,
+                                                     uint32_t iter, int lane) {
     const int city = list_city(v.y);
-    const uint32_t visited = s_vis[city >> 5];
     const uint32_t ctr[1] = {1u + (uint32_t)city / 4u};
     u32x4 x[1];
     philox4_many<1>(k0, k1, step, ant, iter, ctr, x);
     const uint32_t lo = city & 1 ? x[0].y : x[0].x, hi = city & 1 ? x[0].w : x[0].z;
     const float prod = __uint_as_float(v.x) * unit24(city & 2 ? hi : lo);
-    const bool may = lane < kListEntries && ((visited >> (city & 31)) & 1u) == 0u;
-    const uint32_t key = may ? __float_as_uint(prod) : 0u;
+    const uint32_t key = ((lane < kListEntries) & unvisited) ? __float_as_uint(prod) : 0u;
     const uint32_t top = wave_max_u32(key);
     const uint32_t rest = (uint32_t)__builtin_amdgcn_readlane((int)v.x, kListEntries);
-    if (top <= rest) return -1;
-    const int src = __builtin_ctzll(ballot(key == top));
-    return __builtin_amdgcn_readlane(city, src);
-}
-
-// Feasibility bits of a fresh tour: cities < n.
-template <int P>
-__device__ __forceinline__ uint64_t initial_bits(int n, int lane) {
-    uint64_t bits = 0;
-#pragma unroll
-    for (int p = 0; p < P; ++p)
-#pragma unroll
-        for (int e = 0; e < kG; ++e)
-            if (city_of(p, lane, e) < n) bits |= 1ull << (kG * p + e);
-    return bits;
-}
-
-// Clears city j's bit in the lane that holds it.
-__device__ __forceinline__ void mark_visited(int j, int lane, uint64_t& bits) {
-    // j >= 0: unsigned, so the divisions are shifts and masks
-    const uint32_t uj = (uint32_t)j;
-    const uint32_t p = uj / kPass, rem = uj % kPass;
-    if ((int)(rem / kG) == lane) bits &= ~(1ull << (kG * p + rem % kG));
+    return top > rest ? ballot(key == top) : 0ull;
 }
 
 template <int P>
 __global__ __launch_bounds__(64) void k_construct_product(Colony c, uint32_t iter) {
     extern __shared__ __align__(16) unsigned char smem[];
-    uint16_t* s_tour = reinterpret_cast<uint16_t*>(smem);
-    __shared__ uint32_t s_vis[kMaxCities / 32];
+    __shared__ uint8_t s_bits[64 * P];
     const int lane = threadIdx.x;
     const int k = ant_of_block(blockIdx.x, c.m);
     const int n = c.n;
+    uint16_t* s_tour = reinterpret_cast<uint16_t*>(smem);
+    uint8_t* s_seen = clear_flags(smem + tour_bytes(n), n, 512 * P, lane);
     const PhiloxKey key{(uint32_t)c.seed, (uint32_t)(c.seed >> 32)};
     const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
-
-    uint64_t bits = initial_bits<P>(n, lane);
-    uint64_t block_bits = 0;  // visited cities of block `lane`, kept in s_vis for the lists
     const uint32_t x0 = draw(key, iter, (uint32_t)k, 0u);
     int cur = (int)(((uint64_t)x0 * (uint64_t)(uint32_t)n) >> 32);
 
     // A step reads its city's short list first and the whole row only where
     // the list does not settle the selection.  Whole rows only -> lists, mean
-    // of 20 iterations with m = n: n = 2400 8.56 -> 1.41 ms, n = 1000 0.816 ->
-    // 0.403 ms, n = 333 0.177 -> 0.136 ms, n = 100 0.0546 -> 0.0472 ms (with
+    // of 20 iterations with m = n: n = 2400 8.56 -> 1.30 ms, n = 1000 0.816 ->
+    // 0.400 ms, n = 333 0.177 -> 0.130 ms, n = 100 0.0546 -> 0.0459 ms (with
     // the launch that builds the lists, 4 to 15 us).
-    for (int step = 1; step < n; ++step) {
+    int step = 1;
+    do {
         const u32x2 entry = load_list(lists, cur, lane);
-        if (lane == 0) s_tour[step - 1] = (uint16_t)cur;
-        mark_visited(cur, lane, bits);
-        if (lane == (cur >> 6)) block_bits |= 1ull << (cur & 63);
-        s_vis[2 * lane] = (uint32_t)block_bits;
-        s_vis[2 * lane + 1] = (uint32_t)(block_bits >> 32);
-        int next = product_list_pick(entry, s_vis, key.k0, key.k1, (uint32_t)step, (uint32_t)k,
-                                     iter, lane);
-        if (next < 0) {
+        if (lane == 0) {
+            s_tour[step - 1] = (uint16_t)cur;
+            s_seen[cur] = 1;
+        }
+        const uint64_t hit =
+            product_list_hit(entry, s_seen[list_city(entry.y)] == 0, key.k0, key.k1,
+                             (uint32_t)step, (uint32_t)k, iter, lane);
+        if (__builtin_expect(hit != 0, 1)) {
+            cur = list_city(__builtin_amdgcn_readlane(entry.y, __builtin_ctzll(hit)));
+        } else {
+            uint64_t bits, blocks;
+            bits_from_flags<P>(reinterpret_cast<const uint2*>(s_seen), s_bits, lane, bits, blocks);
             const PhiloxDraws draws{key.k0, key.k1, (uint32_t)step, (uint32_t)k, iter};
             const uint32_t j =
                 product_pick<P>(c.choice + (size_t)cur * c.ld, n, bits, draws, lane).city;
             // n - step >= 1 cities are unvisited, so there is one; the clamp
             // only keeps the LDS index in range should that ever break.
-            next = j == ~0u ? 0 : (int)j;
+            cur = j == ~0u ? 0 : (int)j;
         }
-        cur = next;
-    }
+        // one city for the wavefront
+        cur = __builtin_amdgcn_readfirstlane(cur);
+    } while (++step < n);
     if (lane == 0) s_tour[n - 1] = (uint16_t)cur;
     __syncthreads();
     if (lane == 0) s_tour[n] = s_tour[0];
@@ -417,8 +401,8 @@ hipError_t launch_construct_product(const Colony& c, uint32_t iter, hipStream_t 
     const hipError_t e = launch_short_lists(c, s);
     if (e != hipSuccess) return e;
     return dispatch_passes(c.n, [&]<int P>() {
-        hipLaunchKernelGGL((k_construct_product<P>), dim3(c.m), dim3(64), tour_bytes(c.n), s, c,
-                           iter);
+        hipLaunchKernelGGL((k_construct_product<P>), dim3(c.m), dim3(64),
+                           tour_bytes(c.n) + seen_lds_bytes(c.n), s, c, iter);
         return hipGetLastError();
     });
 }

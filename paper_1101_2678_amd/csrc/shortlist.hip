@@ -23,19 +23,22 @@ constexpr float kUp = 1.0f + 0x1.0p-17f;
 // Rows whose weights sum to this much are not selected from by list, so no
 // sum or product of a step can overflow.
 constexpr float kLargest = 0x1.0p100f;
+// Weights below 2^-99 stay in the tail, so that the sums of a list's weights
+// are 0 or far from underflow.
+constexpr uint32_t kLeast = (127u - 99u) << 23;
 
 // A row counts for starting the roulette's steps from the lists where the
 // tail holds at most this share of it; a launch does so where half of the
 // rows count.  A step the list does not settle reads the whole row after it,
 // so where rows come from the L2 (n below about 2000) the lists have to
 // settle more than half of the steps: at n = 1000 they do from the eighth
-// iteration on (58% settled, 0.526 ms against 0.526 ms without; the sixth
-// 0.679 against 0.530, the eleventh 0.382 against 0.520), when half of the
-// rows leave 2% to the tail; rows of up to 512 cities, whose own step is
-// shorter, two iterations later (n = 500: 0.183 against 0.184 ms in the
-// ninth).  Longer rows are bound by memory, and the short
-// reads leave room for the others from the first iteration (n = 2400: 5.9
-// against 6.1 ms, n = 2000 3.49 against 3.38 ms, n = 1800 3.00 against 2.37).
+// iteration on (58% settled, 0.445 ms against 0.485 on whole rows; the first
+// 0.81 against 0.48, the eleventh 0.331 against 0.48), when half of the rows
+// leave 2% to the tail; rows of up to 512 cities, whose own step is shorter,
+// two iterations later (n = 500: 0.168 against 0.184 ms in the ninth).  Longer
+// rows are bound by memory, and the short reads leave room for the others
+// from the first iteration (n = 2400: 5.9 against 6.1 ms, n = 2000 3.42 against
+// 3.38 and from the second on less, n = 1800 3.00 against 2.37).
 __device__ __forceinline__ float by_list_share(int n) {
     return n <= 512 ? 0.004f : n < 2000 ? 0.02f : 1.0f;
 }
@@ -102,7 +105,7 @@ __device__ __forceinline__ void short_list_row(const Colony& c, int i, ListShare
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         const uint32_t b = __float_as_uint(w[q]), bin = edge - (b >> kBinShift);
-        if (b != 0u && bin < (uint32_t)kBins) atomicAdd(&sh.bins[bin], 1u);
+        if (b >= kLeast && bin < (uint32_t)kBins) atomicAdd(&sh.bins[bin], 1u);
     }
     __syncthreads();
     // bins 0 .. taken - 1 together hold at most 63 entries
@@ -126,7 +129,7 @@ __device__ __forceinline__ void short_list_row(const Colony& c, int i, ListShare
     for (int q = 0; q < Q; ++q) {
         const int b = wave + kWaves * q;
         const uint32_t bits = __float_as_uint(w[q]);
-        const bool in = bits != 0u && edge - (bits >> kBinShift) < taken;
+        const bool in = bits >= kLeast && edge - (bits >> kBinShift) < taken;
         const uint64_t mask = ballot(in);
         const float t = in ? 0.0f : w[q];
         tail_max = in || bits < tail_max ? tail_max : bits;
@@ -161,7 +164,7 @@ __device__ __forceinline__ void short_list_row(const Colony& c, int i, ListShare
         const int b = wave + kWaves * q;
         if (b >= blocks) break;
         const uint32_t bits = __float_as_uint(w[q]);
-        const bool in = bits != 0u && edge - (bits >> kBinShift) < taken;
+        const bool in = bits >= kLeast && edge - (bits >> kBinShift) < taken;
         const uint64_t mask = ballot(in);
         if (mask == 0ull) continue;
         const float in_block = wave_shift_up1(s64_scan(in ? 0.0f : w[q]));

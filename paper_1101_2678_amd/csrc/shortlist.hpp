@@ -53,7 +53,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t list_rsrc(const Colony& c) {
 }
 
 // The roulette's selection from a row's short list alone (v: the lane's
-// entry, unvisited: whether its city is, u: the step's draw), or -1 where it
+// entry, w: its weight if its city is unvisited and the lane below 63, else 0,
+// u: the step's draw): the bit of the chosen city's lane, or 0 where the step
 // needs the whole row.
 //
 // The rule over the whole row picks the lowest unvisited city j whose prefix
@@ -66,27 +67,31 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t list_rsrc(const Colony& c) {
 // binary32 sum here and in the rule is a tree of non-negative terms of depth
 // at most 13, and so within a factor (1 +- 2^-24)^13 of the exact one; the
 // two sides of each test and their products together stay within 48 such
-// factors, which the margin 1 +- 2^-18 (64 of them) covers.  (Sums are exact where they are subnormal; L
-// above 2^-100 keeps the products normal, and build_list keeps every sum
-// below 2^101.)  Only one lane can pass both tests, and it is unvisited: with
-// w_j = 0 they contradict each other.
-__device__ __forceinline__ int roulette_list_pick(u32x2 v, bool unvisited, float u, int lane) {
+// factors, which the margin 1 +- 2^-18 (64 of them) covers.  (Sums are exact
+// where they are subnormal; a list holds no weight below 2^-99, so L is 0,
+// which passes no test, or keeps the products normal; and rows whose sums
+// could pass 2^100 have R = +inf.)  Only one lane can pass both tests, and it
+// is unvisited: with w_j = 0 they contradict each other.
+__device__ __forceinline__ uint64_t roulette_list_hit(u32x2 v, float w, float u) {
     // u with the margin to either side, off the chain of the sums
     const float u_over = u * (1.0f + 0x1.0p-18f), u_under = u * (1.0f - 0x1.0p-18f);
-    const int city = list_city(v.y);
     const float above = list_tail(v.y);
-    const bool may = (lane < kListEntries) & unvisited;
-    const float w = may ? __uint_as_float(v.x) : 0.0f;
-    const float s = s64_scan(w);
+    const float s = s64_scan_in_place(w);
     const float listed = read_lane(s, 63), rest = read_lane(above, kListEntries);
     const float before = wave_shift_up1(s) + above;
     // two ballots and a scalar AND: the AND of the conditions would go
     // through a vector register
-    uint64_t hit = ballot(s > u_over * (listed + rest)) & ballot(before <= u_under * listed);
-    // as bit patterns, on the scalar unit (listed >= +0)
-    hit = __float_as_uint(listed) > __float_as_uint(0x1.0p-100f) ? hit : 0ull;
-    if (__builtin_expect(hit == 0ull, 0)) return -1;
-    return __builtin_amdgcn_readlane(city, __builtin_ctzll(hit));
+    return ballot(s > u_over * (listed + rest)) & ballot(before <= u_under * listed);
+}
+
+// The entry's weight where `unvisited` holds.
+__device__ __forceinline__ float list_weight(u32x2 v, bool unvisited, int lane) {
+    return ((lane < kListEntries) & unvisited) ? __uint_as_float(v.x) : 0.0f;
+}
+
+// The city of the lane that roulette_list_hit found.
+__device__ __forceinline__ int hit_city(u32x2 v, uint64_t hit) {
+    return list_city(__builtin_amdgcn_readlane(v.y, __builtin_ctzll(hit)));
 }
 
 // Lists of the n rows of colony c from its current choice matrix, and the
