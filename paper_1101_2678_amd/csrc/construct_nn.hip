@@ -17,7 +17,9 @@
 // candidate table (8 bytes per candidate, in L2 for every instance size the
 // library accepts), so the kernel is bound by the latency of that dependent
 // load and of the selection that follows it, not by bandwidth; the rare
-// fallback issues all loads of the 4n-byte choice row at once.  The kernel
+// fallback takes the largest unvisited entry of the row's short list where
+// rows are long, and otherwise, or where that holds none, issues all loads of
+// the 4n-byte choice row at once.  The kernel
 // is specialised on the number of 256-city passes of the fallback and on
 // whether the list fits the low 32 lanes.
 #include <hip/hip_runtime.h>
@@ -25,6 +27,7 @@
 #include "aco_device.hpp"
 #include "aco_state.hpp"
 #include "nn.hpp"
+#include "shortlist.hpp"
 
 namespace aco {
 namespace {
@@ -53,7 +56,8 @@ __device__ __forceinline__ float s64_scan_lo32(float x) {
     x = x + dpp_move<0x112, 0xF>(x);
     x = x + dpp_move<0x114, 0xF>(x);
     x = x + dpp_move<0x118, 0xF>(x);
-    x = x + dpp_move<0x142, 0xA>(x);
+    // in place, as in s64_scans
+    asm("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf" : "+v"(x));
     return x;
 }
 
@@ -123,6 +127,23 @@ __device__ __forceinline__ int fallback_argmax(const float* row, int n, const ui
     const uint32_t top = wave_max_u32(best);
     const uint32_t j = wave_min_u32(best == top && best != 0u ? best_j : ~0u);
     return top == 0u ? -1 : (int)j;
+}
+
+// The unvisited city with the largest choice value, from the row's short list,
+// or -1 where the list holds none: it holds every city whose value is not
+// below its smallest, in city order, so its largest unvisited value is the
+// row's, on its lowest lane.
+__device__ __forceinline__ int largest_listed(__amdgpu_buffer_rsrc_t lists, int row,
+                                              const uint8_t* vis, int lane) {
+    const u32x2 v = load_list(lists, row, lane);
+    const int city = list_city(v.y);
+    const bool may = (lane < kListEntries) & (vis[city] == 0);
+    const uint32_t key = may ? v.x : 0u;
+    const uint32_t top = wave_max_u32(key);
+    // lane 63 holds +inf where the row must not be selected from by list
+    const bool usable = (uint32_t)__builtin_amdgcn_readlane((int)v.x, kListEntries) < 0x7F800000u;
+    if (top == 0u || !usable) return -1;
+    return __builtin_amdgcn_readlane(city, __builtin_ctzll(ballot(key == top)));
 }
 
 // Packed candidate table from the current choice matrix.
@@ -220,6 +241,15 @@ __global__ __launch_bounds__(kListThreads) void k_nn_lists_batch(
     nn_list_row(c, init_tables(c), (int)(e & 0xffffu), sh);
 }
 
+// Rows of more than 1280 cities have their short lists built: a step that
+// leaves its candidate list (2% of them) then reads 512 bytes instead of 4n.
+// With the launch for the lists, construction with nn = 30, mean of 20
+// iterations: n = 3000 1.26 -> 1.13 ms, n = 2400 0.836 -> 0.790, n = 1500
+// 0.442 -> 0.439, n = 1000 0.265 both, n = 100 0.0346 -> 0.0390.
+constexpr int kMinNnListPasses = 6;
+template <int P>
+constexpr bool kNnLists = P >= kMinNnListPasses;
+
 template <int P, bool kNn32>
 __global__ __launch_bounds__(64) void k_construct_nn(Colony c, NnTables t, uint32_t iter) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -250,44 +280,52 @@ __global__ __launch_bounds__(64) void k_construct_nn(Colony c, NnTables t, uint3
     // between the selected city and the next load (every access is in range)
     const __amdgpu_buffer_rsrc_t crs = __builtin_amdgcn_make_buffer_rsrc(
         t.cand, (short)0, n * kp * (int)sizeof(uint64_t), 0x00020000);
+    const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
     // A step's candidate row is loaded as soon as its city is known; the
     // city's bookkeeping (tour entry, visited flag) follows the load, before
-    // the flags are read (one wavefront: its LDS accesses stay in order).
-    float u64 = 0.0f;
-    for (int step = 1; step < n; ++step) {
-        typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(
-            crs, col * (int)sizeof(uint64_t), cur * kp * (int)sizeof(uint64_t), 0);
-        if (lane == 0) {
-            s_tour[step - 1] = (uint16_t)cur;
-            s_vis[cur] = 1;
-        }
-        const int slot = (step - 1) & 63;
-        if (__builtin_expect(slot == 0, 0))
-            u64 = uniform24(draw(key, iter, (uint32_t)k, (uint32_t)(step + lane)));
-        const float u = read_lane(u64, slot);
-
-        const int city = (int)v.y;
-        // every lane reads its flag (a valid index on every lane), so the
-        // read needs no branch; `&` keeps it unconditional
-        const bool unvisited = s_vis[city] == 0;
-        const bool feas = in_list & unvisited;
-        const float w = feas ? __uint_as_float(v.x) : 0.0f;
-        const float s = kNn32 ? s64_scan_lo32(w) : s64_scan(w);
-        const float target = u * read_lane(s, kNn32 ? 31 : 63);
-        const uint64_t live = ballot(unvisited) & list_mask;
-        int next;
-        if (__builtin_expect(live != 0, 1)) {
-            const uint64_t hit = ballot(s > target) & live;
-            const int r = hit ? __builtin_ctzll(hit) : 63 - __builtin_clzll(live);
-            next = __builtin_amdgcn_readlane(city, r);
-        } else {
-            next = fallback_argmax<P>(c.choice + (size_t)cur * c.ld, n, s_vis, lane);
-            // n - step >= 1 cities are unvisited, so next >= 0; the clamp only
-            // keeps the LDS indices in range should that ever break.
-            next = next < 0 ? 0 : next;
-        }
-        cur = next;
+    // the flags are read (one wavefront: its LDS accesses stay in order).  64
+    // steps at a time, with their draws.
+    for (int base = 0; base < n - 1; base += 64) {
+        const float u64 = uniform24(draw(key, iter, (uint32_t)k, (uint32_t)(base + 1 + lane)));
+        const int count = __builtin_amdgcn_readfirstlane(n - 1 - base < 64 ? n - 1 - base : 64);
+        int i = 0;
+        do {
+            const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(
+                crs, col * (int)sizeof(uint64_t), cur * kp * (int)sizeof(uint64_t), 0);
+            if (lane == 0) {
+                s_tour[base + i] = (uint16_t)cur;
+                s_vis[cur] = 1;
+            }
+            const float u = read_lane(u64, i);
+            const int city = (int)v.y;
+            // every lane reads its flag (a valid index on every lane), so the
+            // read needs no branch; `&` keeps it unconditional
+            const bool unvisited = s_vis[city] == 0;
+            const bool feas = in_list & unvisited;
+            const float w = feas ? __uint_as_float(v.x) : 0.0f;
+            const float s = kNn32 ? s64_scan_lo32(w) : s64_scan_in_place(w);
+            // opaque, or the product becomes a scalar read, a move and a product
+            float goal = u * s;
+            asm("" : "+v"(goal));
+            const float target = read_lane(goal, kNn32 ? 31 : 63);
+            const uint64_t live = ballot(unvisited) & list_mask;
+            int next;
+            if (__builtin_expect(live != 0, 1)) {
+                const uint64_t hit = ballot(s > target) & live;
+                const int r = hit ? __builtin_ctzll(hit) : 63 - __builtin_clzll(live);
+                next = __builtin_amdgcn_readlane(city, r);
+            } else {
+                next = kNnLists<P> ? largest_listed(lists, cur, s_vis, lane) : -1;
+                if (next < 0) {
+                    next = fallback_argmax<P>(c.choice + (size_t)cur * c.ld, n, s_vis, lane);
+                    // at least one city is unvisited, so next >= 0; the clamp
+                    // only keeps the LDS indices in range should that ever
+                    // break.
+                    next = next < 0 ? 0 : next;
+                }
+            }
+            cur = __builtin_amdgcn_readfirstlane(next);
+        } while (++i < count);
     }
     if (lane == 0) s_tour[n - 1] = (uint16_t)cur;
     __syncthreads();
@@ -538,6 +576,7 @@ hipError_t launch_construct_nn(const Colony& c, const NnTables& t, uint32_t iter
     const int cells = c.n * t.kp;
     hipLaunchKernelGGL(k_cand_refresh, dim3((cells + 255) / 256), dim3(256), 0, s, c, t);
     hipError_t e = hipGetLastError();
+    if (e == hipSuccess && c.n > 256 * (kMinNnListPasses - 1)) e = launch_short_lists(c, s);
     if (e != hipSuccess) return e;
     return launch_nn_passes<1>(c, t, iter, s);
 }
