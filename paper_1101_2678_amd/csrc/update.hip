@@ -463,6 +463,18 @@ __global__ __launch_bounds__(256) void k_pad_rows(const uint32_t* __restrict__ s
             padded_quad(src + (size_t)blockIdx.y * n, n, q);
 }
 
+// grid (ceil(n / 1024), n): row i of pitch ld to n contiguous words.
+__global__ __launch_bounds__(256) void k_unpad_rows(const uint32_t* __restrict__ src,
+                                                    uint32_t* __restrict__ dst, int n, int ld) {
+    const uint32_t* s = src + (size_t)blockIdx.y * ld;
+    uint32_t* d = dst + (size_t)blockIdx.y * n;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int j = blockIdx.x * 1024 + 256 * e + threadIdx.x;
+        if (j < n) d[j] = s[j];
+    }
+}
+
 // The distances of every colony of a batch, uploaded to its tau matrix.
 __global__ __launch_bounds__(256) void k_pad_dist_batch(const Colony* __restrict__ cols,
                                                         const uint32_t* __restrict__ rowmap) {
@@ -537,6 +549,11 @@ hipError_t launch_init_batch(const Colony* cols, int count, const uint32_t* rowm
 
 hipError_t launch_pad_rows(const uint32_t* src, uint32_t* dst, int n, int ld, hipStream_t s) {
     hipLaunchKernelGGL(k_pad_rows, dim3((ld / 4 + 255) / 256, n), dim3(256), 0, s, src, dst, n, ld);
+    return hipGetLastError();
+}
+
+hipError_t launch_unpad_rows(const uint32_t* src, uint32_t* dst, int n, int ld, hipStream_t s) {
+    hipLaunchKernelGGL(k_unpad_rows, dim3((n + 1023) / 1024, n), dim3(256), 0, s, src, dst, n, ld);
     return hipGetLastError();
 }
 

@@ -1,0 +1,50 @@
+"""Matrices read back through the neighbour tables (large, no construction
+pending) and by rows (small, or with one pending): the read changes nothing
+that a later call sees."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+import tsp_inputs
+from gpu_helpers import ORACLE_THREADS, assert_same_f32
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,m", [(511, 511), (513, 513), (700, 3), (700, 700), (1000, 1024),
+                                 (1100, 1101)])
+def test_reads_between_calls(n, m):
+    from paper_1101_2678_amd.aco import Colony
+
+    _, d = tsp_inputs.instance(n, "uniform", seed=n)
+    ref = oracle.init(d, m, 1, 2, 0.5, 1)
+    col = Colony(d, m, 1, 2, 0.5, 1)
+    for it in range(2):
+        assert_same_f32(col.tau(), ref.tau, "tau before")
+        assert_same_f32(col.choice(), ref.choice, "choice before")
+        col.construct(it)
+        assert_same_f32(col.tau(), ref.tau, "tau, construction pending")
+        tours, lens = oracle.construct(ref.choice, d, m, 1, it, threads=ORACLE_THREADS)
+        ref.tau, ref.choice = oracle.update(ref.tau, tours, lens, d, 0.5, 1, 2)
+        col.update("gather" if it else "atomic")
+        assert_same_f32(col.tau(), ref.tau, "tau after")
+        assert_same_f32(col.choice(), ref.choice, "choice after")
+        got, got_lens = col.tours()
+        assert np.array_equal(got, tours) and np.array_equal(got_lens, lens)
+
+
+def test_batch_reads_between_runs():
+    from paper_1101_2678_amd.aco import Batch
+
+    dists = [tsp_inputs.instance(n, "uniform", seed=n)[1] for n in (700, 64)]
+    params = [dict(m=700), dict(m=20)]
+    read, alone = Batch(dists, params), Batch(dists, params)
+    for _ in range(2):
+        read.run(1)
+        read.tau(0), read.tau(1)
+        alone.run(1)
+    for q in (0, 1):
+        assert_same_f32(read.tau(q), alone.tau(q), f"instance {q}")
+        assert np.array_equal(read.best(q)[0], alone.best(q)[0])
