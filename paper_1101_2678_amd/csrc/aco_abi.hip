@@ -99,6 +99,7 @@ Layout make_layout(const aco_params& p) {
     L.tau0 = take(sizeof(float));
     L.iter = take(sizeof(uint32_t));
     L.lists = take((size_t)p.n * kListLanes * sizeof(uint64_t));
+    L.wide = take(p.n > kMinWideCities ? (size_t)p.n * kWideBytes : 0);
     L.by_list = take((size_t)L.ld);
     L.base_end = off;
     L.delta = take(cells * sizeof(double));
@@ -219,6 +220,7 @@ Colony carve(char* base, const Layout& L, const aco_params& p, bool with_delta, 
     col.tau0 = reinterpret_cast<float*>(base + L.tau0);
     col.iter_dev = reinterpret_cast<uint32_t*>(base + L.iter);
     col.lists = reinterpret_cast<uint64_t*>(base + L.lists);
+    col.wide = p.n > kMinWideCities ? reinterpret_cast<uint8_t*>(base + L.wide) : nullptr;
     col.by_list = reinterpret_cast<uint8_t*>(base + L.by_list);
     col.delta = with_delta ? reinterpret_cast<double*>(base + L.delta) : nullptr;
     col.tile = tile;

@@ -18,7 +18,8 @@ constexpr size_t kAlign = 256;
 struct Layout {
     int32_t ld, tp, mp;
     size_t tau, choice, dist, tours, succ, pred, lens, dep, best_len, best_tour, cnn, tau0, iter,
-        lists, by_list, delta, base_end, atomic_end;
+        lists, wide, by_list,
+        delta, base_end, atomic_end;
 };
 
 extern thread_local std::string g_error;

@@ -36,9 +36,11 @@ struct Colony {
     int32_t tile;        // construction tile: cities per lane per pass (4 or 8)
     int32_t waves;       // construction wavefronts per ant (1, or 2 / 4 for n <= 1024)
     int32_t dep_emin;    // every deposit fl32(1/C^k) has a binary32 exponent field >= this
+    uint8_t* wide;       // n wide lists (shortlist.hpp), or null (n <= kMinWideCities)
 };
 
 constexpr int kMaxCities = 4096;
+constexpr int kMinWideCities = 2560;  // longer rows have a wide list too (shortlist.hip)
 constexpr int kMaxTile4Cities = 1024;  // tile 4 holds 16 passes of 256 cities at most
 // Largest n aco_update_atomic_noalloc takes (its static deposit matrix holds
 // n * ld binary64 cells, ld = n rounded up to 64).

@@ -291,6 +291,10 @@ template <int G>
 constexpr bool kUseLists = G == 8;
 constexpr int kMinListCities = 256;
 
+// Whether every row of P passes has a wide list.
+template <int G, int P>
+constexpr bool kWideLists = 64 * G * (P - 1) >= kMinWideCities;
+
 // Dynamic LDS of an ant: the tour, then the flags.
 __host__ __device__ size_t ant_lds_bytes(int n) { return tour_lds_bytes(n) + seen_lds_bytes(n); }
 
@@ -509,7 +513,8 @@ __device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t i
         // 13.3; mean of the first 24: 0.157 / 0.198, 0.363 / 0.519, 0.791 /
         // 1.32, 2.61 / 6.05, 5.10 / 13.2.
         const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
-        uint8_t* s_seen = clear_flags(reinterpret_cast<uint8_t*>(s_tour) + tour_lds_bytes(n), n, 512 * P, lane);
+        uint8_t* s_seen = clear_flags(reinterpret_cast<uint8_t*>(s_tour) + tour_lds_bytes(n), n,
+                                      512 * P, lane);
         cur = walk<false>(n, key, iter, k, s_tour, lane, [&](int at, float u, int i) {
             const u32x2 entry = load_list(lists, at, lane);
             if (lane == 0) {
@@ -519,6 +524,12 @@ __device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t i
             const bool unvisited = s_seen[list_city(entry.y)] == 0;
             const uint64_t hit = roulette_list_hit(entry, list_weight(entry, unvisited, lane), u);
             if (__builtin_expect(hit != 0, 1)) return hit_city(entry, hit);
+            if constexpr (kWideLists<G, P>) {
+                if (wide_tried(entry)) {
+                    const int j = roulette_wide_pick(load_wide(wide_rsrc(c), at, lane), s_seen, u, lane);
+                    if (j >= 0) return j;
+                }
+            }
             bits_from_flags<P>(reinterpret_cast<const uint2*>(s_seen),
                                reinterpret_cast<uint8_t*>(sh.w), lane, lane_bits, block_bits);
             const int j = r64_pick<G, P, SKIP>(c.choice, records, at, row_bytes, n, lane_bits,

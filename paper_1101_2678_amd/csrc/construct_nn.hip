@@ -576,7 +576,11 @@ hipError_t launch_construct_nn(const Colony& c, const NnTables& t, uint32_t iter
     const int cells = c.n * t.kp;
     hipLaunchKernelGGL(k_cand_refresh, dim3((cells + 255) / 256), dim3(256), 0, s, c, t);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess && c.n > 256 * (kMinNnListPasses - 1)) e = launch_short_lists(c, s);
+    if (e == hipSuccess && c.n > 256 * (kMinNnListPasses - 1)) {
+        Colony short_only = c;
+        short_only.wide = nullptr;
+        e = launch_short_lists(short_only, s);
+    }
     if (e != hipSuccess) return e;
     return launch_nn_passes<1>(c, t, iter, s);
 }

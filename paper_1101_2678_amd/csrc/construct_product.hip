@@ -274,6 +274,35 @@ __device__ __forceinline__ uint64_t product_list_hit(u32x2 v, bool unvisited, ui
     return top > rest ? ballot(key == top) : 0ull;
 }
 
+// The same from the row's wide list, or -1: four Philox blocks a lane.
+__device__ __forceinline__ int product_wide_pick(const WideEntries& v, const uint8_t* s_seen,
+                                                 uint32_t k0, uint32_t k1, uint32_t step,
+                                                 uint32_t ant, uint32_t iter, int lane) {
+    uint32_t ctr[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ctr[e] = 1u + (uint32_t)v.city(e) / 4u;
+    u32x4 x[4];
+    philox4_many<4>(k0, k1, step, ant, iter, ctr, x);
+    uint32_t key[4], largest = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int city = v.city(e);
+        const uint32_t lo = city & 1 ? x[e].y : x[e].x, hi = city & 1 ? x[e].w : x[e].z;
+        const float prod = v.w[e] * unit24(city & 2 ? hi : lo);
+        const bool may = (4 * lane + e < kWideEntries) & (s_seen[city] == 0);
+        key[e] = may ? __float_as_uint(prod) : 0u;
+        largest = max(largest, key[e]);
+    }
+    const uint32_t top = wave_max_u32(largest);
+    const uint32_t rest = (uint32_t)__builtin_amdgcn_readlane(__float_as_int(v.w[3]), 63);
+    if (top <= rest) return -1;
+    // cities grow with (lane, position)
+    int city = 0;
+#pragma unroll
+    for (int e = 3; e >= 0; --e) city = key[e] == top ? v.city(e) : city;
+    return __builtin_amdgcn_readlane(city, __builtin_ctzll(ballot(largest == top)));
+}
+
 template <int P>
 __global__ __launch_bounds__(64) void k_construct_product(Colony c, uint32_t iter) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -288,11 +317,23 @@ __global__ __launch_bounds__(64) void k_construct_product(Colony c, uint32_t ite
     const uint32_t x0 = draw(key, iter, (uint32_t)k, 0u);
     int cur = (int)(((uint64_t)x0 * (uint64_t)(uint32_t)n) >> 32);
 
-    // A step reads its city's short list first and the whole row only where
-    // the list does not settle the selection.  Whole rows only -> lists, mean
-    // of 20 iterations with m = n: n = 2400 8.56 -> 1.30 ms, n = 1000 0.816 ->
-    // 0.400 ms, n = 333 0.177 -> 0.130 ms, n = 100 0.0546 -> 0.0459 ms (with
-    // the launch that builds the lists, 4 to 15 us).
+    const auto whole_row = [&](int at, int step) {
+        uint64_t bits, blocks;
+        bits_from_flags<P>(reinterpret_cast<const uint2*>(s_seen), s_bits, lane, bits, blocks);
+        const PhiloxDraws draws{key.k0, key.k1, (uint32_t)step, (uint32_t)k, iter};
+        const uint32_t j =
+            product_pick<P>(c.choice + (size_t)at * c.ld, n, bits, draws, lane).city;
+        // n - step >= 1 cities are unvisited, so there is one; the clamp only
+        // keeps the LDS index in range should that ever break.
+        return j == ~0u ? 0 : (int)j;
+    };
+
+    // A step reads its city's short list first, for long rows the wide list
+    // where that does not settle the selection, and then the whole row.
+    // Whole rows only -> lists, mean of 20 iterations with m = n: n = 2400
+    // 8.56 -> 1.30 ms, n = 1000 0.816 -> 0.400 ms, n = 333 0.177 -> 0.130 ms,
+    // n = 100 0.0546 -> 0.0459 ms (with the launch that builds the lists, 4 to
+    // 15 us).
     int step = 1;
     do {
         const u32x2 entry = load_list(lists, cur, lane);
@@ -306,14 +347,12 @@ __global__ __launch_bounds__(64) void k_construct_product(Colony c, uint32_t ite
         if (__builtin_expect(hit != 0, 1)) {
             cur = list_city(__builtin_amdgcn_readlane(entry.y, __builtin_ctzll(hit)));
         } else {
-            uint64_t bits, blocks;
-            bits_from_flags<P>(reinterpret_cast<const uint2*>(s_seen), s_bits, lane, bits, blocks);
-            const PhiloxDraws draws{key.k0, key.k1, (uint32_t)step, (uint32_t)k, iter};
-            const uint32_t j =
-                product_pick<P>(c.choice + (size_t)cur * c.ld, n, bits, draws, lane).city;
-            // n - step >= 1 cities are unvisited, so there is one; the clamp
-            // only keeps the LDS index in range should that ever break.
-            cur = j == ~0u ? 0 : (int)j;
+            int next = -1;
+            if constexpr (kPass * (P - 1) >= kMinWideCities)
+                next = product_wide_pick(load_wide(wide_rsrc(c), cur, lane), s_seen, key.k0, key.k1,
+                                         (uint32_t)step, (uint32_t)k, iter, lane);
+            if (next < 0) next = whole_row(cur, step);
+            cur = next;
         }
         // one city for the wavefront
         cur = __builtin_amdgcn_readfirstlane(cur);

@@ -43,12 +43,32 @@ __device__ __forceinline__ float by_list_share(int n) {
     return n <= 512 ? 0.004f : n < 2000 ? 0.02f : 1.0f;
 }
 
-struct ListShared {
-    uint32_t bins[kBins];
+// Wide lists: construction with m = n, without and with them, n = 3000 by
+// iteration: 12.3 and 12.3 ms in the second (uniform cities), 2.10 and 2.16 in
+// the 13th, 1.64 and 1.34 in the 24th; clustered cities 11.3 and 10.8, 1.95 and
+// 1.86, 1.69 (20th) and 1.41.  Shorter rows gain the same in the end but lose
+// on the way, where a whole row costs little more than the wide list that does
+// not settle the step (n = 2400, 13th: 1.37 against 1.45; n = 2000: 0.92
+// against 1.08).  The roulette tries the list of a row that leaves little to
+// the tail: with 2% or 6% n = 3000 takes 122.1 and 122.8 ms for 24 iterations,
+// clustered 20 in 89.0 and 87.9, with 0.1% 121.9 and 92.8, with all tried
+// 135.6 and 89.1.
+constexpr float kWideShare = 0.06f;
+
+// One selection of a row's entries: those in the list, what is left of each
+// block, and the largest left.
+struct Selected {
     uint64_t mask[kMaxBlocks];
     float tail[kMaxBlocks];
+    uint32_t tail_max[kWaves];
+};
+
+template <int TIERS>
+struct ListShared {
+    uint32_t bins[kBins];
+    Selected tier[TIERS];
     float sum[kWaves];
-    uint32_t max[kWaves], tail_max[kWaves];
+    uint32_t max[kWaves];
 };
 
 __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
@@ -66,9 +86,81 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
     return v;
 }
 
-// The list of row i.  Q: blocks of a wavefront, at least ceil(n / 256).
+// The entries of tier `t` and what they leave, from the weights w of the
+// wavefront's blocks.
 template <int Q>
-__device__ __forceinline__ void short_list_row(const Colony& c, int i, ListShared& sh) {
+__device__ __forceinline__ void select_entries(const float (&w)[Q], uint32_t edge, uint32_t taken,
+                                               int wave, int lane, Selected& t) {
+    uint32_t tail_max = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int b = wave + kWaves * q;
+        const uint32_t bits = __float_as_uint(w[q]);
+        const bool in = bits >= kLeast && edge - (bits >> kBinShift) < taken;
+        const uint64_t mask = ballot(in);
+        tail_max = in || bits < tail_max ? tail_max : bits;
+        const float s = s64_scan(in ? 0.0f : w[q]);
+        if (lane == 63 && b < kMaxBlocks) {
+            t.mask[b] = mask;
+            t.tail[b] = s;
+        }
+    }
+    tail_max = wave_max(tail_max);
+    if (lane == 0) t.tail_max[wave] = tail_max;
+}
+
+// Calls out(rank, bits, city, tail before it) for every entry of the tier;
+// returns their number, and the tail's weight in `rest`.
+template <int Q, typename Out>
+__device__ __forceinline__ int emit_entries(const float (&w)[Q], uint32_t edge, uint32_t taken,
+                                            int blocks, int wave, int lane, const Selected& t,
+                                            float& rest, Out&& out) {
+    // block b's entries start at rank `first` of lane b, after a tail of
+    // weight `weight` of lane b
+    const uint32_t own = lane < blocks ? (uint32_t)__popcll(t.mask[lane]) : 0u;
+    uint32_t first = own;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t o = __shfl_up(first, off);
+        first += lane >= off ? o : 0u;
+    }
+    const int entries = __builtin_amdgcn_readlane((int)first, 63);
+    first -= own;
+    const float weights = s64_scan(lane < blocks ? t.tail[lane] : 0.0f);
+    const float weight = wave_shift_up1(weights);
+    rest = read_lane(weights, 63) * kUp;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int b = wave + kWaves * q;
+        if (b >= blocks) break;
+        const uint32_t bits = __float_as_uint(w[q]);
+        const bool in = bits >= kLeast && edge - (bits >> kBinShift) < taken;
+        const uint64_t mask = ballot(in);
+        if (mask == 0ull) continue;
+        const float in_block = wave_shift_up1(s64_scan(in ? 0.0f : w[q]));
+        const float above = (read_lane(weight, b) + in_block) * kUp;
+        const int rank = __builtin_amdgcn_readlane((int)first, b) +
+                         (int)__builtin_amdgcn_mbcnt_hi(
+                             (uint32_t)(mask >> 32),
+                             __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+        if (in) out(rank, bits, 64 * b + lane, above, entries);
+    }
+    return entries;
+}
+
+__device__ __forceinline__ uint32_t max_of(const uint32_t (&v)[kWaves]) {
+    uint32_t m = 0;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) m = v[i] > m ? v[i] : m;
+    return m;
+}
+
+// The lists of row i, with WIDE the wide one too: 256 threads, one pass over
+// the row, held in registers.  Q: blocks of a wavefront,
+// at least ceil(n / 256).
+template <int Q, bool WIDE>
+__device__ __forceinline__ void short_list_row(const Colony& c, int i,
+                                               ListShared<WIDE ? 2 : 1>& sh) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = c.n;
@@ -98,8 +190,7 @@ __device__ __forceinline__ void short_list_row(const Colony& c, int i, ListShare
         sh.sum[wave] = sum;
     }
     __syncthreads();
-#pragma unroll
-    for (int v = 0; v < kWaves; ++v) top = sh.max[v] > top ? sh.max[v] : top;
+    top = max_of(sh.max);
     const float total = (sh.sum[0] + sh.sum[1]) + (sh.sum[2] + sh.sum[3]);
     const uint32_t edge = top >> kBinShift;
 #pragma unroll
@@ -108,7 +199,7 @@ __device__ __forceinline__ void short_list_row(const Colony& c, int i, ListShare
         if (b >= kLeast && bin < (uint32_t)kBins) atomicAdd(&sh.bins[bin], 1u);
     }
     __syncthreads();
-    // bins 0 .. taken - 1 together hold at most 63 entries
+    // bins 0 .. taken - 1 together hold at most 63 (wide: 255) entries
     uint32_t below = 0, cum[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) cum[e] = below += sh.bins[4 * lane + e];
@@ -119,90 +210,85 @@ __device__ __forceinline__ void short_list_row(const Colony& c, int i, ListShare
         before += lane >= off ? o : 0u;
     }
     before -= below;
-    uint32_t taken = 0;
+    const auto bins_up_to = [&](uint32_t limit) {
+        uint32_t bins = 0;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) taken += before + cum[e] <= (uint32_t)kListEntries ? 1u : 0u;
-    taken = __builtin_amdgcn_readfirstlane(wave_sum(taken));
-
-    uint32_t tail_max = 0;
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int b = wave + kWaves * q;
-        const uint32_t bits = __float_as_uint(w[q]);
-        const bool in = bits >= kLeast && edge - (bits >> kBinShift) < taken;
-        const uint64_t mask = ballot(in);
-        const float t = in ? 0.0f : w[q];
-        tail_max = in || bits < tail_max ? tail_max : bits;
-        const float s = s64_scan(t);
-        if (lane == 63 && b < kMaxBlocks) {
-            sh.mask[b] = mask;
-            sh.tail[b] = s;
-        }
-    }
-    tail_max = wave_max(tail_max);
-    if (lane == 0) sh.tail_max[wave] = tail_max;
+        for (int e = 0; e < 4; ++e) bins += before + cum[e] <= limit ? 1u : 0u;
+        return (uint32_t)__builtin_amdgcn_readfirstlane(wave_sum(bins));
+    };
+    const uint32_t taken = bins_up_to(kListEntries);
+    const uint32_t wide_taken = WIDE ? bins_up_to(kWideEntries) : 0u;
+    select_entries<Q>(w, edge, taken, wave, lane, sh.tier[0]);
+    if constexpr (WIDE) select_entries<Q>(w, edge, wide_taken, wave, lane, sh.tier[1]);
     __syncthreads();
-    // block b's entries start at rank `first` of lane b, after a tail of
-    // weight `weight` of lane b
+
+    // not selected from by list: sums that could overflow, and weights that are
+    // not finite or not above -0
+    const bool bad = !(total < kLargest) || top >= 0x7F800000u;
+    const float inf = __uint_as_float(0x7F800000u);
     const int blocks = (n + 63) >> 6;
-    const uint32_t own = lane < blocks ? (uint32_t)__popcll(sh.mask[lane]) : 0u;
-    uint32_t first = own;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t o = __shfl_up(first, off);
-        first += lane >= off ? o : 0u;
-    }
-    const int entries = __builtin_amdgcn_readlane((int)first, 63);
-    first -= own;
-    const float weights = s64_scan(lane < blocks ? sh.tail[lane] : 0.0f);
-    const float weight = wave_shift_up1(weights);
-    const float rest = read_lane(weights, 63) * kUp;
-
     u32x2* out = reinterpret_cast<u32x2*>(c.lists) + (size_t)i * kListLanes;
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int b = wave + kWaves * q;
-        if (b >= blocks) break;
-        const uint32_t bits = __float_as_uint(w[q]);
-        const bool in = bits >= kLeast && edge - (bits >> kBinShift) < taken;
-        const uint64_t mask = ballot(in);
-        if (mask == 0ull) continue;
-        const float in_block = wave_shift_up1(s64_scan(in ? 0.0f : w[q]));
-        const float above = (read_lane(weight, b) + in_block) * kUp;
-        const int rank = __builtin_amdgcn_readlane((int)first, b) +
-                         (int)__builtin_amdgcn_mbcnt_hi(
-                             (uint32_t)(mask >> 32),
-                             __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-        if (in) out[rank] = u32x2{bits, list_meta(64 * b + lane, above)};
-    }
+    float rest;
+    const int entries = emit_entries<Q>(
+        w, edge, taken, blocks, wave, lane, sh.tier[0], rest,
+        [&](int rank, uint32_t bits, int city, float above, int) {
+            out[rank] = u32x2{bits, list_meta(city, above)};
+        });
     if (tid == 0) c.by_list[i] = entries > 0 && rest <= total * by_list_share(n) ? 1 : 0;
-    if (wave == 0) {
-        // not selected from by list: sums that could overflow, and weights
-        // that are not finite or not above -0
-        const bool bad = !(total < kLargest) || top >= 0x7F800000u;
-        uint32_t m = 0;
-#pragma unroll
-        for (int v = 0; v < kWaves; ++v) m = sh.tail_max[v] > m ? sh.tail_max[v] : m;
-        if (lane >= entries && lane < kListEntries) out[lane] = u32x2{0u, 0u};
-        if (lane == kListEntries)
-            out[lane] = u32x2{bad ? 0x7F800000u : m,
-                              list_meta(0, bad ? __uint_as_float(0x7F800000u) : rest)};
+    if (wave == 0 && lane >= entries && lane < kListEntries) out[lane] = u32x2{0u, 0u};
+    const float short_rest = rest;
+    int wide_tried = 0;
+    if constexpr (WIDE) {
+        uint8_t* base = c.wide + (size_t)i * kWideBytes;
+        uint32_t* ww = reinterpret_cast<uint32_t*>(base);
+        uint16_t* wc = reinterpret_cast<uint16_t*>(base + kWideCities);
+        float* wt = reinterpret_cast<float*>(base + kWideTails);
+        const int wide = emit_entries<Q>(
+            w, edge, wide_taken, blocks, wave, lane, sh.tier[1], rest,
+            [&](int rank, uint32_t bits, int city, float above, int count) {
+                ww[rank] = bits;
+                wc[rank] = (uint16_t)city;
+                if (((rank & 3) == 3 || rank == count - 1) && rank < 4 * 63) wt[rank >> 2] = above;
+            });
+        // what no entry has written
+        if (tid >= wide && tid < kWideEntries) {
+            ww[tid] = 0u;
+            wc[tid] = 0;
+        }
+        if (tid == kWideEntries) {
+            ww[tid] = bad ? 0x7F800000u : max_of(sh.tier[1].tail_max);
+            wc[tid] = 0;
+        }
+        if (tid < 64 && (4 * tid >= wide || tid == 63)) wt[tid] = bad ? inf : rest;
+        wide_tried = rest <= total * kWideShare ? 1 : 0;
     }
+    if (tid == kListEntries)
+        out[kListEntries] = u32x2{bad ? 0x7F800000u : max_of(sh.tier[0].tail_max),
+                                  list_meta(wide_tried, bad ? inf : short_rest)};
 }
 
-template <int Q>
+template <int Q, bool WIDE>
 __global__ __launch_bounds__(kThreads) void k_short_lists(Colony c) {
-    __shared__ ListShared sh;
-    short_list_row<Q>(c, blockIdx.x, sh);
+    __shared__ ListShared<(WIDE ? 2 : 1)> sh;
+    short_list_row<Q, WIDE>(c, blockIdx.x, sh);
 }
 
+// Q > 10: some colonies have wide lists.
 template <int Q>
 __global__ __launch_bounds__(kThreads) void k_short_lists_batch(
     const Colony* __restrict__ cols, const uint32_t* __restrict__ rowmap) {
-    __shared__ ListShared sh;
+    __shared__ ListShared<1> sh;
     const uint32_t e = rowmap[blockIdx.x];
     const Colony c = cols[e >> 16];
-    short_list_row<Q>(c, (int)(e & 0xffffu), sh);
+    const int i = (int)(e & 0xffffu);
+    if constexpr (Q > 10) {
+        if (c.wide) {
+            __shared__ ListShared<2> wide;
+            short_list_row<Q, true>(c, i, wide);
+            return;
+        }
+    }
+    short_list_row<Q, false>(c, i, sh);
 }
 
 }  // namespace
@@ -225,11 +311,14 @@ hipError_t launch_short_lists(const Colony& c, hipStream_t s) {
     if (c.n < 1 || c.n > kMaxCities) return hipErrorInvalidValue;
     const dim3 grid(c.n), block(kThreads);
     if (c.n <= 1024)
-        hipLaunchKernelGGL(k_short_lists<4>, grid, block, 0, s, c);
+        hipLaunchKernelGGL((k_short_lists<4, false>), grid, block, 0, s, c);
     else if (c.n <= 2560)
-        hipLaunchKernelGGL(k_short_lists<10>, grid, block, 0, s, c);
+        hipLaunchKernelGGL((k_short_lists<10, false>), grid, block, 0, s, c);
+    else if (!c.wide)
+        hipLaunchKernelGGL((k_short_lists<16, false>), grid, block, 0, s, c);
     else
-        hipLaunchKernelGGL(k_short_lists<16>, grid, block, 0, s, c);
+        hipLaunchKernelGGL((k_short_lists<16, true>), grid, block, 0, s, c);
+    static_assert(kMinWideCities == 2560, "the rows of k_short_lists<16>");
     return hipGetLastError();
 }
 

@@ -11,6 +11,10 @@
 // the list first; where the bounds prove which city the rule over the whole
 // row picks, that city is taken, else the whole row is read.  Either way the
 // result is the rule's own, bit for bit; the list decides only what is read.
+//
+// Rows of more than 2560 cities have a wide list too, of up to 255 of the
+// largest entries, four a lane: a step the short list does not settle tries
+// it before the whole row, which for those rows comes from beyond the L2.
 #pragma once
 
 #include "aco_device.hpp"
@@ -28,6 +32,43 @@ constexpr int kListEntries = kListLanes - 1;
 static_assert(kMaxCities <= 1 << 12, "a city takes 12 bits of an entry");
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+// A wide list: the weights of entries 4 l .. 4 l + 3 at 16 l, their cities
+// (uint16) at 1024 + 8 l, and at 1536 + 4 l the tail's weight before the last
+// of them, an upper bound for all four.  Entry 255 is the tail's largest
+// weight, lane 63's bound the tail's whole weight (+inf: not to be used).
+// Past the entries: weight 0.
+constexpr int kWideEntries = 255;
+constexpr int kWideCities = 1024, kWideTails = 1536, kWideBytes = 1792;
+
+struct WideEntries {
+    float w[4];
+    uint32_t cities[2];
+    float tail;
+    __device__ __forceinline__ int city(int e) const {
+        return (int)((cities[e / 2] >> (16 * (e % 2))) & 0xFFFFu);
+    }
+};
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t wide_rsrc(const Colony& c) {
+    return __builtin_amdgcn_make_buffer_rsrc(c.wide, (short)0, c.n * kWideBytes, 0x00020000);
+}
+__device__ __forceinline__ WideEntries load_wide(__amdgpu_buffer_rsrc_t wide, int row, int lane) {
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    const int soff = row * kWideBytes;
+    const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(wide, 16 * lane, soff, 0);
+    const u32x2 c = __builtin_amdgcn_raw_buffer_load_b64(wide, kWideCities + 8 * lane, soff, 0);
+    const uint32_t t = __builtin_amdgcn_raw_buffer_load_b32(wide, kWideTails + 4 * lane, soff, 0);
+    WideEntries v;
+    v.w[0] = __uint_as_float(w.x);
+    v.w[1] = __uint_as_float(w.y);
+    v.w[2] = __uint_as_float(w.z);
+    v.w[3] = __uint_as_float(w.w);
+    v.cities[0] = c.x;
+    v.cities[1] = c.y;
+    v.tail = __uint_as_float(t);
+    return v;
+}
 
 __device__ __forceinline__ uint32_t list_meta(int city, float tail_above) {
     // tail_above >= +0; the next multiple of 2^11 in its bit pattern is not
@@ -94,8 +135,45 @@ __device__ __forceinline__ int hit_city(u32x2 v, uint64_t hit) {
     return list_city(__builtin_amdgcn_readlane(v.y, __builtin_ctzll(hit)));
 }
 
+// Whether the roulette tries the row's wide list: the city of entry 63.
+__device__ __forceinline__ bool wide_tried(u32x2 v) {
+    return list_city(__builtin_amdgcn_readlane(v.y, kListEntries)) != 0;
+}
+
+// The roulette's selection from a wide list, or -1: the tests of
+// roulette_list_hit with four entries a lane (two additions more in a sum).
+// s_seen: city j's visited flag in byte j.
+__device__ __forceinline__ int roulette_wide_pick(const WideEntries& v, const uint8_t* s_seen,
+                                                  float u, int lane) {
+    const float u_over = u * (1.0f + 0x1.0p-18f), u_under = u * (1.0f - 0x1.0p-18f);
+    float w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const bool may = (4 * lane + e < kWideEntries) & (s_seen[v.city(e)] == 0);
+        w[e] = may ? v.w[e] : 0.0f;
+    }
+    float in[4];  // prefixes inside the lane
+    in[0] = w[0];
+    in[1] = w[0] + w[1];
+    in[2] = in[1] + w[2];
+    in[3] = in[2] + w[3];
+    const float s = s64_scan_in_place(in[3]);
+    const float before = wave_shift_up1(s);
+    const float listed = read_lane(s, 63), rest = read_lane(v.tail, 63);
+    const float over = u_over * (listed + rest), under = u_under * listed;
+    int j = -1;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float prior = e ? before + in[e - 1] : before;
+        const uint64_t hit = ballot(before + in[e] > over) & ballot(prior + v.tail <= under);
+        if (hit) j = __builtin_amdgcn_readlane(v.city(e), __builtin_ctzll(hit));
+    }
+    return j;
+}
+
 // Lists of the n rows of colony c from its current choice matrix, and the
-// rows the roulette starts from (c.by_list).
+// rows the roulette starts from (c.by_list); wide lists where c.wide is
+// not null.
 hipError_t launch_short_lists(const Colony& c, hipStream_t s);
 // As above for the rows of a batch: (colony << 16) | row per entry of rowmap;
 // max_n: the largest n among the colonies.

@@ -88,6 +88,14 @@ def test_general_steps_between_list_steps(n):
 
 
 @pytest.mark.parametrize("rule", sorted(CONSTRUCT))
+@pytest.mark.parametrize("kind", ["own", "zero", "sparse", "wide", "steep", "huge"])
+@pytest.mark.parametrize("n", [2560, 2561, 3001, 3585])
+def test_wide_lists(rule, kind, n):
+    _, d = tsp_inputs.instance(n, "cluster", seed=n)
+    check(rule, d, 8, 1, 2, kind, iters=1)
+
+
+@pytest.mark.parametrize("rule", sorted(CONSTRUCT))
 @pytest.mark.parametrize("side,beta", [(8, 2), (20, 2), (33, 0)])
 def test_equal_weights(rule, side, beta):
     xy = np.array([(x, y) for x in range(side) for y in range(side)], np.int64) * 10
