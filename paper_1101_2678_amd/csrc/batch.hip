@@ -95,14 +95,20 @@ aco_status batch_device_fail(aco_batch* b, hipError_t e, const char* where) {
     return aco::host::device_fail(b ? &b->poisoned : nullptr, e, where);
 }
 
+// One construction of every instance: the lists, then the ants.
+hipError_t enqueue_construction(aco_batch* b) {
+    hipError_t e = aco::launch_short_lists_batch(b->d_cols, b->d_rowmap, b->total_rows, b->max_n,
+                                                 b->stream);
+    if (e != hipSuccess) return e;
+    return aco::launch_construct_batch(
+        b->d_cols, b->d_antmap, b->total_ants, b->max_n,
+        aco::batch_lds_bytes(b->max_n, b->config.wg_per_cu, b->lds_per_cu), b->stream);
+}
+
 hipError_t enqueue_iterations(aco_batch* b, uint32_t iters) {
     hipError_t e = hipSuccess;
     for (uint32_t i = 0; i < iters && e == hipSuccess; ++i) {
-        e = aco::launch_short_lists_batch(b->d_cols, b->d_rowmap, b->total_rows, b->max_n, b->stream);
-        if (e != hipSuccess) break;
-        e = aco::launch_construct_batch(
-            b->d_cols, b->d_antmap, b->total_ants, b->max_n,
-            aco::batch_lds_bytes(b->max_n, b->config.wg_per_cu, b->lds_per_cu), b->stream);
+        e = enqueue_construction(b);
         if (e == hipSuccess) e = aco::launch_best_batch(b->d_cols, b->count, b->stream);
         if (e == hipSuccess)
             e = aco::launch_update_gather_batch(b->d_cols, b->d_rowmap, b->total_rows, b->max_ld,
@@ -402,29 +408,36 @@ aco_status aco_batch_autotune(aco_batch* b, const aco_batch_config* cands, int32
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
-    int best = 0;
-    float t_best = 1e30f;
-    for (int i = 0; i < count && e == hipSuccess; ++i) {
-        if (aco_status s = aco_batch_set_config(b, &cands[i])) {
-            (void)hipEventDestroy(e0);
-            (void)hipEventDestroy(e1);
-            return s;
-        }
-        e = enqueue_iterations(b, 1);  // warm-up at this shape
-        if (e == hipSuccess) e = hipEventRecord(e0, b->stream);
-        if (e == hipSuccess) e = enqueue_iterations(b, iters);
-        if (e == hipSuccess) e = hipEventRecord(e1, b->stream);
-        if (e == hipSuccess) e = hipEventSynchronize(e1);
-        float ms = 0.0f;
-        if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-        if (e != hipSuccess) break;
-        ms /= (float)iters;
-        if (ms_per_iter) ms_per_iter[i] = ms;
-        if (ms < t_best) {
-            t_best = ms;
-            best = i;
+    // A construction takes several times as long on a new colony as on a
+    // converged one, so candidates are compared on the same state: each
+    // repeats the construction of the iteration at hand (its tours are not
+    // used), half of them before and half after the iterations that the batch
+    // advances by; the last of these comes at the end and leaves its tours.
+    const uint32_t reps[2] = {(iters + 1) / 2, iters > 1 ? iters / 2 : 1u};
+    std::vector<float> ms(count, 0.0f);
+    for (int half = 0; half < 2 && e == hipSuccess; ++half) {
+        if (half == 1)
+            for (int i = 0; i < count && e == hipSuccess; ++i)
+                e = enqueue_iterations(b, i < count - 1 ? iters + 1 : iters);
+        for (int i = 0; i < count && e == hipSuccess; ++i) {
+            if (aco_status s = aco_batch_set_config(b, &cands[i])) {
+                (void)hipEventDestroy(e0);
+                (void)hipEventDestroy(e1);
+                return s;
+            }
+            if (i == 0) e = enqueue_construction(b);  // warm-up
+            if (e == hipSuccess) e = hipEventRecord(e0, b->stream);
+            for (uint32_t r = 0; r < reps[half] && e == hipSuccess; ++r) e = enqueue_construction(b);
+            if (e == hipSuccess) e = hipEventRecord(e1, b->stream);
+            if (e == hipSuccess) e = hipEventSynchronize(e1);
+            float t = 0.0f;
+            if (e == hipSuccess) e = hipEventElapsedTime(&t, e0, e1);
+            ms[i] += 0.5f * t / (float)reps[half];
         }
     }
+    if (e == hipSuccess) e = enqueue_iterations(b, 1);
+    const int best = (int)(std::min_element(ms.begin(), ms.end()) - ms.begin());
+    if (ms_per_iter && e == hipSuccess) std::copy(ms.begin(), ms.end(), ms_per_iter);
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     if (e != hipSuccess) return batch_device_fail(b, e, "aco_batch_autotune");

@@ -48,3 +48,24 @@ def test_batch_reads_between_runs():
     for q in (0, 1):
         assert_same_f32(read.tau(q), alone.tau(q), f"instance {q}")
         assert np.array_equal(read.best(q)[0], alone.best(q)[0])
+
+
+def test_tours_after_autotune():
+    """The batch tuner repeats constructions of one state; what it leaves are
+    the tours of the last iteration that it advances by."""
+    from paper_1101_2678_amd import aco
+
+    sizes = (70, 333, 600)
+    dists = [tsp_inputs.instance(n, "uniform", seed=n)[1] for n in sizes]
+    params = [dict(m=n, alpha=1, beta=2, rho=0.5, seed=n) for n in sizes]
+    tuned, plain = aco.Batch(dists, params), aco.Batch(dists, params)
+    tuned.autotune([(0, -1), (8, 0), (16, 1024)], iters=2)
+    plain.run(9, graph=False)
+    plain.sync()
+    for q in range(len(sizes)):
+        assert tuned.iteration(q) == plain.iteration(q) == 9
+        for a, b in zip(tuned.tours(q), plain.tours(q)):
+            assert np.array_equal(a, b)
+        assert_same_f32(tuned.tau(q), plain.tau(q), f"instance {q}")
+    tuned.close()
+    plain.close()
