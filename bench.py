@@ -60,7 +60,11 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "construct_n2400_traffic.json")
 # of its device code, and (of the state header, which also declares host
 # launchers) the colony struct it takes as its argument.
 KERNEL_SOURCES = ["paper_1101_2678_amd/csrc/construct.hip", "paper_1101_2678_amd/csrc/r64_lanes.hpp",
-                  "paper_1101_2678_amd/csrc/aco_device.hpp"]
+                  "paper_1101_2678_amd/csrc/aco_device.hpp",
+                  "paper_1101_2678_amd/csrc/construct_flat.hpp",
+                  "paper_1101_2678_amd/csrc/construct_masked.hpp",
+                  "paper_1101_2678_amd/csrc/seen.hpp", "paper_1101_2678_amd/csrc/shortlist.hpp",
+                  "paper_1101_2678_amd/csrc/shortlist.hip"]
 KERNEL_STRUCT = ("paper_1101_2678_amd/csrc/aco_state.hpp", "struct Colony {", "};")
 
 
@@ -344,8 +348,9 @@ def random_rows_ceiling(torch, aco, n: int, m: int, waves_factors=(1, 2, 4, 8),
 
 
 def requested_bytes(tours: np.ndarray, n: int, skip: bool) -> int:
-    """Bytes the construction kernel asks the memory system for in one launch
-    (16-byte loads of 4-city groups).  With the skip path a group is loaded
+    """Bytes a construction that reads a row at every step asks the memory
+    system for in one launch (16-byte loads of 4-city groups); steps that a
+    short list settles ask for 512 bytes instead.  With the skip path a group is loaded
     at step s only if one of its cities is still unvisited, i.e. at steps
     1 .. (last position of the group's cities in the tour); without it every
     group of the row is loaded at all n - 1 steps."""
@@ -360,6 +365,16 @@ def requested_bytes(tours: np.ndarray, n: int, skip: bool) -> int:
         np.put_along_axis(pos, t, np.arange(n, dtype=np.int64)[None, :], axis=1)
         total += int(pos.reshape(t.shape[0], groups, 4).max(axis=2).sum())
     return 16 * total
+
+
+def construct_kernel(n: int, tile: int) -> str:
+    """The construction kernel a single-instance launch of n cities runs."""
+    if n <= 320:
+        return f"k_construct_flat<{(n + 63) // 64}>"
+    passes = (n + 64 * tile - 1) // (64 * tile)
+    if tile == 8 and passes <= 3:
+        return f"k_construct_masked<{passes}>"
+    return f"k_construct<{tile},{passes}>"
 
 
 SYNC_LAUNCHES = False
@@ -549,6 +564,9 @@ def bench_product(torch, aco, d, m: int, steps: int, warmup: int, update: str, c
                      "frac": round(blocks / (t_con * 1e-3) / ceiling[0], 4),
                      "peak_note": "measured: aco_probe_philox, the same Philox formulation with "
                                   "no loads or selection, 16 wavefronts per SIMD",
+                     "frac_note": "achieved counts the draws of every city at every step; a step "
+                                  "that the row's short list settles computes those of its 63 "
+                                  "entries only, so the fraction can pass 1",
                      "ceiling_at_m_wavefronts": ceiling[1],
                      "kernel": "k_construct_product"},
     }
@@ -592,7 +610,7 @@ def bench_batch(args, torch, aco):
     # timed on this batch (each candidate advances it by 3 iterations)
     cands = [(w, t) for t in (-1, 0, 1024) for w in (0, 8, 12, 16, 20, 24, 32)]
     best, cand_ms = b.autotune(cands, iters=2)
-    log(f"bench batch: launch autotune chose {cands[best]} ({cand_ms[best]:.3f} ms/iteration; "
+    log(f"bench batch: launch autotune chose {cands[best]} ({cand_ms[best]:.3f} ms/construction; "
         f"default {default_cfg})")
     b.run(iters, graph=True)  # captures the graph and runs 25 iterations
     b.sync()
@@ -600,8 +618,8 @@ def bench_batch(args, torch, aco):
     b.run(iters, graph=True)  # replays it: iterations 25..49
     b.sync()
     t_batch = time.perf_counter() - t0
-    # bytes the batched construction asks for (it skips 4-city groups once all
-    # are visited), estimated from each instance's last tours
+    # bytes of a construction that reads a row at every step (4-city groups
+    # once all are visited left out), from each instance's last tours
     req_iter = sum(requested_bytes(b.tours(q)[0], int(n), skip=True)
                    for q, n in enumerate(sizes))
     choice_footprint = sum(int(n) * ((int(n) + 63) // 64 * 64) * 4 for n in sizes)
@@ -650,7 +668,7 @@ def bench_batch(args, torch, aco):
                            "batched launch takes only the tile; -1 = shape does not support "
                            "the size"},
         "launch_autotune": {
-            "candidates": [{"wg_per_cu": w, "tile4_max_n": t, "ms_per_iteration": round(float(x), 4)}
+            "candidates": [{"wg_per_cu": w, "tile4_max_n": t, "ms_per_construction": round(float(x), 4)}
                            for (w, t), x in zip(cands, cand_ms)],
             "chosen": {"wg_per_cu": cands[best][0], "tile4_max_n": cands[best][1]},
             "default": default_cfg,
@@ -662,16 +680,15 @@ def bench_batch(args, torch, aco):
     }
     rf = rec["roofline"]
     rf["requested_bytes"] = int(req_iter) * iters
-    rf["requested_GBps"] = round(req_iter * iters / t_batch / 1e9, 1)
-    rf["frac_requested"] = round(rf["requested_GBps"] / HBM_PEAK_GBPS, 4)
     rf["choice_footprint_bytes"] = choice_footprint
     rf["frac_note"] = (
-        f"achieved counts every ant-step's whole choice row; the batched kernel asks for "
-        f"{req_iter * iters / rf['algorithmic_bytes']:.3f} of those bytes (it skips 4-city groups "
-        f"once all are visited; estimated from each instance's last tours), and the "
-        f"construction reads only the choice matrices, {choice_footprint / 1e6:.0f} MB "
-        f"together, which the Infinity Cache holds and of which the small instances' sit in "
-        f"L2, so the whole-job rate can pass the HBM figure")
+        f"achieved counts every ant-step's whole choice row; steps that read it ask for "
+        f"{req_iter * iters / rf['algorithmic_bytes']:.3f} of those bytes (4-city groups are "
+        f"skipped once all are visited; from each instance's last tours), steps that the row's "
+        f"short list settles for 512 bytes, and the construction reads only the choice "
+        f"matrices, {choice_footprint / 1e6:.0f} MB together, which the Infinity Cache holds "
+        f"and of which the small instances' sit in L2, so the whole-job rate can pass the HBM "
+        f"figure")
     aco.reset_tiles()
     return rec
 
@@ -746,34 +763,36 @@ def bench_served(args, torch, aco):
 ISOLATED_ANTS = 256  # one wavefront per compute unit, one per SIMD
 
 
-def latency_floor(torch, aco, d, n: int, m_iso: int, con_ms: float) -> dict:
-    """The construction step's latency with nothing to overlap it: the same
-    instance with m_iso ants (at most one wavefront per compute unit), mean
-    of 5 constructions after 2 iterations.  frac = that per-step time over
-    the workload's own, i.e. how close the workload comes to the chain of
-    dependent operations one step is."""
-    col = aco.Colony(d, m_iso, ALPHA, BETA, RHO, seed=1)
+def latency_floor(torch, aco, d, n: int, m: int, m_iso: int) -> dict:
+    """The construction step's latency with nothing to overlap it: from the
+    state of a colony of m ants after 20 iterations, constructions by m ants
+    and by m_iso (at most one wavefront per compute unit), mean of 5 each.
+    frac = the latter's time per step over the former's, i.e. how close the
+    workload comes to the chain of dependent operations one step is."""
     stream = torch.cuda.current_stream()
-    for it in range(2):
-        col.construct(it)
-        col.update("gather")
-    e0, e1 = _events(torch)
-    torch.cuda.synchronize()
-    e0.record(stream)
-    for it in range(2, 7):
-        col.construct(it)
-    e1.record(stream)
-    torch.cuda.synchronize()
-    col.close()
-    iso_ns = e0.elapsed_time(e1) / 5 * 1e6 / (n - 1)
-    act_ns = con_ms * 1e6 / (n - 1)
-    return {"ns_per_step_isolated": round(iso_ns, 1), "ants_isolated": m_iso,
-            "ns_per_step": round(act_ns, 1), "frac": round(iso_ns / act_ns, 4),
-            "note": (f"one construction step is a chain of dependent operations (row load, "
-                     f"block sums, scans, pick); with {m_iso} ants no two wavefronts share a "
+    full = aco.Colony(d, m, ALPHA, BETA, RHO, seed=1)
+    full.solve(20, "gather")
+    few = aco.Colony(d, m_iso, ALPHA, BETA, RHO, seed=1)
+    few.restore(full.tau(), 20)
+    ns = []
+    for col in (full, few):
+        col.construct(20)
+        e0, e1 = _events(torch)
+        torch.cuda.synchronize()
+        e0.record(stream)
+        for it in range(21, 26):
+            col.construct(it)
+        e1.record(stream)
+        torch.cuda.synchronize()
+        col.close()
+        ns.append(e0.elapsed_time(e1) / 5 * 1e6 / (n - 1))
+    return {"ns_per_step_isolated": round(ns[1], 1), "ants_isolated": m_iso,
+            "ns_per_step": round(ns[0], 1), "frac": round(ns[1] / ns[0], 4),
+            "note": (f"one construction step is a chain of dependent operations (list load, "
+                     f"flag read, scan, pick); with {m_iso} ants no two wavefronts share a "
                      f"SIMD, so their per-step time is the chain's own latency, the bound "
-                     f"of this latency-bound size; frac = that over this workload's "
-                     f"per-step time")}
+                     f"of this latency-bound size; frac = that over the per-step time of "
+                     f"{m} ants, both from the state after 20 iterations")}
 
 
 def run_single(args, torch, aco, name: str, steps: int, warmup: int, main: bool) -> dict:
@@ -856,7 +875,7 @@ def run_single(args, torch, aco, name: str, steps: int, warmup: int, main: bool)
     peak = max(ceil["GBps"], rows_ceil["GBps"])
     roofline = {"bound": "mall" if foot > (4 << 20) else "l2", "achieved": round(achieved, 1),
                 "peak": peak, "unit": "GB/s", "frac": round(achieved / peak, 4),
-                "traffic": None, "kernel": f"k_construct<{tile},{passes}>",
+                "traffic": None, "kernel": construct_kernel(n, tile),
                 "algorithmic_bytes_per_launch": alg,
                 "peak_note": (f"measured at the choice matrix's {foot / 1e6:.1f} MB footprint, "
                               f"the better of two reads of it: a streaming read, every XCD "
@@ -875,16 +894,14 @@ def run_single(args, torch, aco, name: str, steps: int, warmup: int, main: bool)
                 "peak_random_rows_GBps": rows_ceil["GBps"],
                 "peak_random_rows_by_shape_GBps": rows_ceil["by_shape_GBps"],
                 "hbm_peak": HBM_PEAK_GBPS, "frac_of_hbm_peak": round(achieved / HBM_PEAK_GBPS, 4),
-                "requested_bytes_per_launch": req,
-                "requested_GBps": round(req / (con_ms * 1e-3) / 1e9, 1),
-                "frac_requested": round(req / (con_ms * 1e-3) / 1e9 / peak, 4)}
-    if passes >= 3:
+                "requested_bytes_per_launch": req}
+    if n > 256:
         roofline["frac_note"] = (
-            f"achieved counts the whole {n}-city row per ant-step (4n bytes), but the kernel "
-            f"does not load a 16-byte group of cities once all four are visited, so it requests "
-            f"only {req / alg:.3f} of those bytes: frac can reach 1 while the bytes it moves "
-            f"(frac_requested, and the counter bytes past L2 in frac_traffic_of_stream) stay "
-            f"below the measured ceiling")
+            f"achieved counts the whole {n}-city row per ant-step (4n bytes); a step that its "
+            f"row's short list settles reads 512 bytes instead, the more steps the further the "
+            f"colony has converged, so frac can pass 1.  requested_bytes_per_launch is what the "
+            f"same tours would ask for with a row read at every step ({req / alg:.3f} of the "
+            f"algorithmic bytes); the counter bytes past L2 are in traffic, where recorded")
     if main:
         traffic, traffic_note = traffic_from_profile()
         roofline["traffic"] = traffic
@@ -928,7 +945,7 @@ def run_single(args, torch, aco, name: str, steps: int, warmup: int, main: bool)
     if roofline["bound"] == "l2" and m > ISOLATED_ANTS and not args.no_latency_floor:
         # latency-bound sizes (the matrix within one XCD's L2): the step chain's
         # own latency, measured with few enough ants that no two share a SIMD
-        rec["latency_floor"] = latency_floor(torch, aco, d, n, ISOLATED_ANTS, con_ms)
+        rec["latency_floor"] = latency_floor(torch, aco, d, n, m, ISOLATED_ANTS)
     if main:
         # each update kernel against a copy of its own footprint (one launch)
         for kind in upd:

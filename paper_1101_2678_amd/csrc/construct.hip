@@ -707,8 +707,10 @@ __global__ __launch_bounds__(64) void k_test_select_flat(const float* rows, int 
 // from the L2 of each XCD, with fewer the latency of a step is no longer
 // covered.  The cap is part of a batch's launch configuration, chosen by the
 // batch autotuner; the default (used by the server) caps at 16 per CU, the
-// best of a manual sweep on a 256-instance batch (n 50..1000: 18 and 20 were
-// 0.7% and 0.6% slower, 24 2.5%, no cap 8.7%, 14 2.1%, 12 13.5%), and only
+// best on a 256-instance batch (n 50..1000; mean of a new and a converged
+// state 9.28 ms, 20 to 32 and no cap 9.30 to 9.34, 12 9.49, 8 11.0; where
+// whole rows are read alone, 18 and 20 were 0.7% slower, 24 2.5%, no cap
+// 8.7%), and only
 // launches of at least kCapRounds rounds at the cap: one that fits the
 // device in a round or two would only gain a tail.
 constexpr int kBatchWgPerCu = 16;

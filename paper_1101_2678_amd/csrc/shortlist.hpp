@@ -141,7 +141,8 @@ __device__ __forceinline__ bool wide_tried(u32x2 v) {
 }
 
 // The roulette's selection from a wide list, or -1: the tests of
-// roulette_list_hit with four entries a lane (two additions more in a sum).
+// roulette_list_hit with four entries a lane (a sum is up to four additions
+// deeper, so the sides of a test stay within 56 factors of the margin's 64).
 // s_seen: city j's visited flag in byte j.
 __device__ __forceinline__ int roulette_wide_pick(const WideEntries& v, const uint8_t* s_seen,
                                                   float u, int lane) {
