@@ -3,8 +3,8 @@
 // candidate cities spread over the lanes).
 //
 // Rows of at most 320 cities have a layout of their own (construct_flat.hpp).
-// Layout of one step of longer rows (ant at city `cur`, wavefront of 64 lanes, tile G = 4
-// or 8 cities per lane):
+// Layout of one step of longer rows (ant at city `cur`, wavefront of 64 lanes,
+// tile G = 4 or 8 cities per lane):
 //   * the choice row of `cur` is streamed with 16-byte loads; in pass p lane l
 //     holds cities 64Gp + Gl .. 64Gp + Gl + G-1, so one pass reads 256 G bytes
 //     contiguously and every 64-city block sits in 64/G neighbouring lanes;
@@ -13,10 +13,10 @@
 //     n) is sent to an out-of-range offset instead, which returns zeros
 //     without a memory access, so late in a tour the lines of the row that
 //     hold no unvisited city are not fetched at all.  That saves bandwidth
-//     where the launch is bandwidth-bound (rows of three or more passes, and
-//     the batched launch) but lengthens a step where it is latency-bound
-//     (one or two passes with about one wavefront per SIMD), so it is on
-//     only in the former;
+//     where the launch is bandwidth-bound (rows of four or more passes at
+//     tile 8, and the batched launch) but lengthens a step where it is
+//     latency-bound (shorter rows with about one wavefront per SIMD; tile 8
+//     takes construct_masked.hpp there), so it is on only in the former;
 //   * the total T_b of each 64-city block is a balanced pairwise sum: log2 G
 //     levels inside the lane, log2(64/G) DPP levels across the lanes.  That
 //     is exactly the last entry of the 64-wide S64 prefix tree, so every T_b
@@ -493,8 +493,8 @@ __device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t i
 
     // LOAD_FIRST: a step's row loads go out as soon as its city is known, and
     // the bookkeeping of that city (tour entry, visited bits) is done while
-    // they are in flight.  That shortens launches of one to three passes
-    // (n = 100 14%, n = 1000 7%, n = 1500 4% faster) but made the
+    // they are in flight.  That shortens steps of one to three passes (with
+    // this layout alone: n = 1000 7%, n = 1500 4% faster) but made the
     // bandwidth-bound four- and five-pass launches (n = 2048, 2400) no
     // faster or up to 1% slower, which keep the bookkeeping first.  With
     // LOAD_FIRST the loads see the visited bits without the step's own city;
