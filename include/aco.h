@@ -224,7 +224,9 @@ aco_status aco_read_nn_lists(aco_ctx* c, uint16_t* lists_host);
 
 /* Copies of the device state into host memory.  Synchronous.
  *   tours: m*(n+1) uint16 of the last construction; lens: m int64 (either may
- *   be NULL); tau, choice: n*n float row-major; best_tour: n+1 uint16. */
+ *   be NULL); tau, choice: n*n float row-major; best_tour: n+1 uint16.
+ * A read changes nothing that another call sees, whether that call is queued,
+ * made later, or captured before the read and replayed after it. */
 aco_status aco_read_tours(aco_ctx* c, uint16_t* tours_host, int64_t* lens_host);
 aco_status aco_read_tau(aco_ctx* c, float* tau_host);
 aco_status aco_read_choice(aco_ctx* c, float* choice_host);

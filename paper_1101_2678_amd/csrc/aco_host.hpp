@@ -45,12 +45,11 @@ hipError_t upload_and_init(const Colony& col, const int32_t* dist_host, size_t b
 // `rows` rows of row_bytes bytes, `pitch` bytes apart on the device, to dst
 // (host, contiguous).  Blocking.
 hipError_t read_rows(void* dst, size_t row_bytes, const void* src, size_t pitch, size_t rows);
-// The n x n matrix `src` (tau or choice) of colony c to dst (host).  `scratch`:
-// the neighbour tables are not in use (no construction awaits its update), so
-// the matrix may be packed there.  Work before it on `stream` must have
-// finished.  Blocking.
-hipError_t read_matrix(const Colony& c, const float* src, float* dst, bool scratch,
-                       hipStream_t stream);
+// The n x n matrix `src` (tau or choice) of colony c to dst (host).  Work before
+// it on `stream` must have finished.  Of the workspace it writes the short
+// lists only.  Blocking.
+constexpr size_t kPackedReadBytes = 8u << 20;  // smaller matrices come down by read_rows
+hipError_t read_matrix(const Colony& c, const float* src, float* dst, hipStream_t stream);
 // Best-so-far tour (n + 1 cities) and length; either pointer may be null.
 hipError_t read_best(const Colony& col, uint16_t* tour_host, int64_t* len_host);
 // Compute units and LDS bytes per compute unit of the current device.

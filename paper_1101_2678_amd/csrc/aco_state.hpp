@@ -89,8 +89,9 @@ hipError_t launch_init_batch(const Colony* cols, int count, const uint32_t* rowm
 // n rows of n 4-byte words (contiguous at src) to rows of pitch ld at dst; the
 // padding columns become 0.  src and dst must not overlap.
 hipError_t launch_pad_rows(const uint32_t* src, uint32_t* dst, int n, int ld, hipStream_t s);
-// The reverse: n rows of pitch ld at src to n x n contiguous words at dst.
-hipError_t launch_unpad_rows(const uint32_t* src, uint32_t* dst, int n, int ld, hipStream_t s);
+// The reverse: `rows` rows of pitch ld at src to rows of n contiguous words at dst.
+hipError_t launch_unpad_rows(const uint32_t* src, uint32_t* dst, int rows, int n, int ld,
+                             hipStream_t s);
 hipError_t launch_refresh_choice(const Colony& c, hipStream_t s);
 hipError_t launch_test_select(int tile, int n, int count, const float* rows,
                               const uint8_t* feasible, const float* u, int32_t* out,

@@ -463,7 +463,7 @@ __global__ __launch_bounds__(256) void k_pad_rows(const uint32_t* __restrict__ s
             padded_quad(src + (size_t)blockIdx.y * n, n, q);
 }
 
-// grid (ceil(n / 1024), n): row i of pitch ld to n contiguous words.
+// grid (ceil(n / 1024), rows): row i of pitch ld to n contiguous words.
 __global__ __launch_bounds__(256) void k_unpad_rows(const uint32_t* __restrict__ src,
                                                     uint32_t* __restrict__ dst, int n, int ld) {
     const uint32_t* s = src + (size_t)blockIdx.y * ld;
@@ -552,8 +552,10 @@ hipError_t launch_pad_rows(const uint32_t* src, uint32_t* dst, int n, int ld, hi
     return hipGetLastError();
 }
 
-hipError_t launch_unpad_rows(const uint32_t* src, uint32_t* dst, int n, int ld, hipStream_t s) {
-    hipLaunchKernelGGL(k_unpad_rows, dim3((n + 1023) / 1024, n), dim3(256), 0, s, src, dst, n, ld);
+hipError_t launch_unpad_rows(const uint32_t* src, uint32_t* dst, int rows, int n, int ld,
+                             hipStream_t s) {
+    hipLaunchKernelGGL(k_unpad_rows, dim3((n + 1023) / 1024, rows), dim3(256), 0, s, src, dst, n,
+                       ld);
     return hipGetLastError();
 }
 

@@ -1,6 +1,5 @@
-"""Matrices read back through the neighbour tables (large, no construction
-pending) and by rows (small, or with one pending): the read changes nothing
-that a later call sees."""
+"""Matrices read back in packed pieces (large) and by rows (small): the read
+changes nothing that a later call sees, replays of captured calls among them."""
 from __future__ import annotations
 
 import numpy as np
@@ -69,3 +68,50 @@ def test_tours_after_autotune():
         assert_same_f32(tuned.tau(q), plain.tau(q), f"instance {q}")
     tuned.close()
     plain.close()
+
+
+@pytest.mark.parametrize("kind,n,m", [("gather", 513, 600), ("atomic", 1500, 1500),
+                                      ("noalloc", 1000, 1024), ("gather", 2600, 2600)])
+def test_read_between_capture_and_replay(kind, n, m):
+    """A captured update uses the neighbour tables of the construction before
+    it whenever it is replayed: matrices read after the capture, and between
+    replays of a captured construction and a captured update, leave them."""
+    import torch
+    from paper_1101_2678_amd.aco import Colony
+
+    _, d = tsp_inputs.instance(n, "uniform", seed=n)
+    stream = torch.cuda.Stream()
+    ref = oracle.init(d, m, 1, 2, 0.5, 1)
+    col = Colony(d, m, 1, 2, 0.5, 1, atomic=kind == "atomic", stream=stream)
+    update = col.update_atomic_noalloc if kind == "noalloc" else lambda: col.update(kind)
+
+    def capture(call):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream, capture_error_mode="thread_local"):
+            call()
+        return graph
+
+    def replay(graph):
+        with torch.cuda.stream(stream):
+            graph.replay()
+        stream.synchronize()
+
+    def check(what):
+        assert_same_f32(col.tau(), ref.tau, f"tau {what}")
+        assert_same_f32(col.choice(), ref.choice, f"choice {what}")
+
+    col.construct(0)
+    captured_update = capture(update)
+    captured_construct = capture(lambda: col.construct(1))
+    for it in range(2 if n < 2000 else 1):
+        check(f"before replay {it}")
+        if it:
+            replay(captured_construct)
+            check("between replays")
+        tours, lens = oracle.construct(ref.choice, d, m, 1, it, threads=ORACLE_THREADS)
+        got, got_lens = col.tours()
+        assert np.array_equal(got, tours) and np.array_equal(got_lens, lens)
+        ref.tau, ref.choice = oracle.update(ref.tau, tours, lens, d, 0.5, 1, 2)
+        replay(captured_update)
+        check(f"after replay {it}")
+    col.close()
