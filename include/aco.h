@@ -302,7 +302,7 @@ aco_status aco_test_product_select(int32_t n, int32_t count, const float* rows_d
  * 64 * cities_per_lane cities, and `waves_per_ant` wavefronts per ant that
  * share the passes (wave w takes passes w, w + W, ...).  The shape changes
  * speed only, never results.  Supported shapes:
- *   1 wavefront:  tile 8 for any n; tile 4 for n <= 1024 (rows of at most 320
+ *   1 wavefront:  tile 8 for any n; tile 4 for n <= 1024 (rows of at most 256
  *                 cities have one layout, whatever the tile);
  *   2 wavefronts: n <= 1024 with at least 2 passes (tile 8: n >= 513;
  *                 tile 4: n >= 257);

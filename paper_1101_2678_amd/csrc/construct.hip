@@ -2,7 +2,8 @@
 // data-parallel design of Section III-A: one workgroup per ant, the ant's
 // candidate cities spread over the lanes).
 //
-// Rows of at most 320 cities have a layout of their own (construct_flat.hpp).
+// Rows of at most 256 cities (320 at tile 4 and in the batched launch) have a
+// layout of their own (construct_flat.hpp).
 // Layout of one step of longer rows (ant at city `cur`, wavefront of 64 lanes,
 // tile G = 4 or 8 cities per lane):
 //   * the choice row of `cur` is streamed with 16-byte loads; in pass p lane l
@@ -733,9 +734,21 @@ int batch_default_cap(int total_ants, int cus) {
 
 namespace {
 
-// Calls f.template operator()<G, P>() for the tile and pass count of n, or
-// with G = 0 and the number of 64-city blocks for rows of the flat layout, or
-// with G = 1 and the pass count for tile 8 with the visited set as factors.
+// Whether rows of n cities at tile 8 keep the visited set as factors
+// (construct_masked.hpp) in a launch of m ants: where the ants fit the device
+// in one round.  An ant of P passes then holds 4 KB of LDS a pass beside its
+// tour, so that 16 (P = 1, 2) or 9 (P = 3) fit a compute unit, against 24 and
+// more with the bits.  First iteration, factors / bits: n = 1000, m = 1000 0.492 /
+// 0.511 ms, 2560 0.704 / 0.733, 3072 0.799 / 0.778, 3840 1.23 / 0.91, 16384 3.94 /
+// 3.47; n = 1500, m = 1500 1.22 / 1.37, 2048 1.42 / 1.48, 2560 2.44 / 1.73.  Rows
+// of one pass are shorter with factors at any m (n = 512, m = 512 0.188 / 0.218,
+// 32768 2.02 / 2.08).
+constexpr int kComputeUnits = 256;
+bool masked_rows(int n, int m) {
+    const int passes = (n + 511) / 512;
+    return passes == 1 || (passes <= kMaxMaskedPasses && m <= 24 / passes * kComputeUnits);
+}
+
 template <int B = 1, typename F>
 hipError_t dispatch_flat(int n, F&& f) {
     if constexpr (B > kMaxFlatBlocks) {
@@ -775,9 +788,14 @@ bool uses_lists(const Colony& c) {
     return c.n > kMinListCities && (c.n <= 64 * kMaxFlatBlocks || c.tile == 8);
 }
 
+// Calls f.template operator()<G, P>() for the tile and pass count of n, or
+// with G = 0 and the number of 64-city blocks for rows of the flat layout, or
+// with G = 1 and the pass count for tile 8 with the visited set as factors
+// (`masked`).  Rows of five blocks at tile 8 take the factors: m = n = 320 0.119
+// against 0.121 ms flat (converged 0.092 / 0.097), m = 65535 2.18 / 2.38.
 template <typename F>
-hipError_t dispatch_tile(int tile, int n, F&& f) {
-    if (n <= 64 * kMaxFlatBlocks) return dispatch_flat(n, f);
+hipError_t dispatch_tile(int tile, int n, bool masked, F&& f) {
+    if (n <= 64 * (masked && tile == 8 ? 4 : kMaxFlatBlocks)) return dispatch_flat(n, f);
     if (tile == 4) {
         switch ((n + 255) / 256) {
             case 2: return f.template operator()<4, 2>();
@@ -786,10 +804,19 @@ hipError_t dispatch_tile(int tile, int n, F&& f) {
             default: return hipErrorInvalidValue;
         }
     }
-    switch ((n + 511) / 512) {
-        case 1: return f.template operator()<1, 1>();
-        case 2: return f.template operator()<1, 2>();
-        case 3: return f.template operator()<1, 3>();
+    const int passes = (n + 511) / 512;
+    if (masked) {
+        switch (passes) {
+            case 1: return f.template operator()<1, 1>();
+            case 2: return f.template operator()<1, 2>();
+            case 3: return f.template operator()<1, 3>();
+            default: break;
+        }
+    }
+    switch (passes) {
+        case 1: return f.template operator()<8, 1>();
+        case 2: return f.template operator()<8, 2>();
+        case 3: return f.template operator()<8, 3>();
         case 4: return f.template operator()<8, 4>();
         case 5: return f.template operator()<8, 5>();
         case 6: return f.template operator()<8, 6>();
@@ -810,7 +837,7 @@ bool tile_supported(int tile, int n) {
 int construct_occupancy(const Colony& c) {
     if (c.waves > 1) return construct_split_occupancy(c);
     int blocks = -1;
-    (void)dispatch_tile(c.tile, c.n, [&]<int G, int P>() {
+    (void)dispatch_tile(c.tile, c.n, masked_rows(c.n, c.m), [&]<int G, int P>() {
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, construct_kernel<G, P>(), 64,
                                                          construct_lds_bytes<G>(c.n)) !=
             hipSuccess)
@@ -827,7 +854,7 @@ hipError_t launch_construct(const Colony& c, uint32_t iter, hipStream_t s) {
         const hipError_t e = launch_short_lists(c, s);
         if (e != hipSuccess) return e;
     }
-    return dispatch_tile(c.tile, c.n, [&]<int G, int P>() {
+    return dispatch_tile(c.tile, c.n, masked_rows(c.n, c.m), [&]<int G, int P>() {
         hipLaunchKernelGGL((construct_kernel<G, P>()), dim3(c.m), dim3(64),
                            construct_lds_bytes<G>(c.n), s, c, iter);
         return hipGetLastError();
@@ -858,7 +885,7 @@ hipError_t launch_test_select(int tile, int n, int count, const float* rows,
     if (count <= 0) return hipSuccess;
     if (!tile_supported(tile, n)) return hipErrorInvalidValue;
     const int ld = (n + 63) & ~63;
-    return dispatch_tile(tile, n, [&]<int G, int P>() {
+    return dispatch_tile(tile, n, true, [&]<int G, int P>() {
         hipLaunchKernelGGL((test_select_kernel<G, P>()), dim3(count), dim3(64), 0, s, rows, ld, n,
                            feasible, u, out);
         return hipGetLastError();

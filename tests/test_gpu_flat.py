@@ -40,3 +40,30 @@ def test_parity(n):
 def test_parity_passes(n):
     _, d = tsp_inputs.instance(n, "uniform", seed=n + 2)
     compare_run(d, 20, 1, 2, 0.5, seed=n, iters=2, kinds=("gather",))
+
+
+@pytest.mark.parametrize("kind", ["own", "steep"])
+@pytest.mark.parametrize("n,m", [(520, 3072), (520, 3073), (1030, 2048), (1030, 2049)])
+def test_many_ants(kind, n, m):
+    """The ant counts on each side of the line between factors and bits, on
+    whole rows and from the lists."""
+    from test_gpu_shortlist import check
+
+    _, d = tsp_inputs.instance(n, "uniform", seed=n + m)
+    check("r64", d, m, 1, 2, kind, iters=1)
+
+
+@pytest.mark.parametrize("n", [600, 1000, 1100, 1500])
+def test_many_ants_stay_resident(n):
+    """A launch of more ants than fit one round with the factors keeps as many
+    on a compute unit as the bits allow."""
+    from paper_1101_2678_amd.aco import Colony
+
+    def ants_per_cu(m):
+        c = Colony(tsp_inputs.instance(n, "uniform", seed=n)[1], m, 1, 2, 0.5, 1, atomic=False)
+        text = c.describe()
+        c.close()
+        return int(text.split("ants_per_cu=")[1].split()[0])
+
+    assert ants_per_cu(n) * 256 >= n
+    assert ants_per_cu(16384) >= 20
