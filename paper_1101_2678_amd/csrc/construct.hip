@@ -286,11 +286,9 @@ struct AntShared {
 template <int G, int P>
 constexpr int kStaged = kWriteAllPasses<G, P> ? 1024 : Tile<G>::kPass;
 
-// Tiles whose colonies use the short lists: at tile 4 (n <= 256) a step from
-// the list takes longer than one from the row (n = 200: 0.41 against 0.37 us).
+// Tiles whose colonies use the short lists (uses_lists).
 template <int G>
 constexpr bool kUseLists = G == 8;
-constexpr int kMinListCities = 256;
 
 // Whether every row of P passes has a wide list.
 template <int G, int P>
@@ -307,6 +305,7 @@ __host__ __device__ size_t masked_lds_bytes(int n) {
 // Whether the roulette of colony c starts its steps from the short lists:
 // where half of the rows have a list that covers them well.
 __device__ __forceinline__ bool starts_from_lists(const Colony& c, int lane) {
+    if (!uses_lists(c)) return false;
     int rows = 0;
     for (int j = 16 * lane; j < c.n; j += 16 * 64) {  // by_list is 0 past n
         const uint4 v = *reinterpret_cast<const uint4*>(c.by_list + j);
@@ -784,10 +783,6 @@ auto construct_kernel() {
         return k_construct<G, P>;
 }
 
-bool uses_lists(const Colony& c) {
-    return c.n > kMinListCities && (c.n <= 64 * kMaxFlatBlocks || c.tile == 8);
-}
-
 // Calls f.template operator()<G, P>() for the tile and pass count of n, or
 // with G = 0 and the number of 64-city blocks for rows of the flat layout, or
 // with G = 1 and the pass count for tile 8 with the visited set as factors
@@ -795,6 +790,7 @@ bool uses_lists(const Colony& c) {
 // against 0.121 ms flat (converged 0.092 / 0.097), m = 65535 2.18 / 2.38.
 template <typename F>
 hipError_t dispatch_tile(int tile, int n, bool masked, F&& f) {
+    static_assert(64 * kMaxFlatBlocks == kMaxFlatCities, "uses_lists");
     if (n <= 64 * (masked && tile == 8 ? 4 : kMaxFlatBlocks)) return dispatch_flat(n, f);
     if (tile == 4) {
         switch ((n + 255) / 256) {

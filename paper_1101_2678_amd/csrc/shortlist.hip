@@ -30,17 +30,23 @@ constexpr uint32_t kLeast = (127u - 99u) << 23;
 // A row counts for starting the roulette's steps from the lists where the
 // tail holds at most this share of it; a launch does so where half of the
 // rows count.  A step the list does not settle reads the whole row after it,
-// so where rows come from the L2 (n below about 2000) the lists have to
-// settle more than half of the steps: at n = 1000 they do from the eighth
-// iteration on (58% settled, 0.445 ms against 0.485 on whole rows; the first
-// 0.81 against 0.48, the eleventh 0.331 against 0.48), when half of the rows
-// leave 2% to the tail; rows of up to 512 cities, whose own step is shorter,
-// two iterations later (n = 500: 0.168 against 0.184 ms in the ninth).  Longer
-// rows are bound by memory, and the short reads leave room for the others
-// from the first iteration (n = 2400: 5.9 against 6.1 ms, n = 2000 3.42 against
-// 3.38 and from the second on less, n = 1800 3.00 against 2.37).
-__device__ __forceinline__ float by_list_share(int n) {
-    return n <= 512 ? 0.004f : n < 2000 ? 0.02f : 1.0f;
+// so the lists have to settle more than half of the steps unless the launch
+// is bound by memory.  Shares at which lists and whole rows take the same time:
+// n = 500 0.007, n = 1000 0.017, n = 1500 0.05 (0.02 with clustered cities), with
+// m = n as with 256 ants.  Rows of four passes and more leave the L2, and the
+// share follows what m ants ask for at once, 4 m n bytes: m n = 0.6e6 (n = 2400,
+// m = 256) 0.06, 2.6e6 (1600, 1600) 0.04, 3e6 (3000, 1000) 0.10, 3.6e6 (1900, 1900)
+// 0.18, 4.1e6 (4096, 1000) 0.31, 5.8e6 (2400, 2400) 0.55, 9e6 (3000, 3000) 0.6; n <
+// 2000 and m of 4096 and 12000 0.2 to 0.28.  Lists from the first iteration where
+// they settle little cost up to 48% (n = 2000, m = 256 2.32 against 1.56 ms; with
+// beta = 1, n = 2400, m = 2400, 6.48 against 6.19).
+__device__ __forceinline__ float by_list_share(int n, int m) {
+    if (n <= 512) return 0.004f;
+    if (n <= 1536) return 0.02f;
+    const float x = 1e-6f * (float)m * (float)n;
+    const float share = 0.001f * (x * x) * (x * x);
+    const float most = n < 2000 ? 0.2f : 0.5f;
+    return share < 0.02f ? 0.02f : share > most ? most : share;
 }
 
 // Wide lists: construction with m = n, without and with them, n = 3000 by
@@ -234,7 +240,7 @@ __device__ __forceinline__ void short_list_row(const Colony& c, int i,
         [&](int rank, uint32_t bits, int city, float above, int) {
             out[rank] = u32x2{bits, list_meta(city, above)};
         });
-    if (tid == 0) c.by_list[i] = entries > 0 && rest <= total * by_list_share(n) ? 1 : 0;
+    if (tid == 0) c.by_list[i] = entries > 0 && rest <= total * by_list_share(n, c.m) ? 1 : 0;
     if (wave == 0 && lane >= entries && lane < kListEntries) out[lane] = u32x2{0u, 0u};
     const float short_rest = rest;
     int wide_tried = 0;

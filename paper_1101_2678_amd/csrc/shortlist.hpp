@@ -172,6 +172,19 @@ __device__ __forceinline__ int roulette_wide_pick(const WideEntries& v, const ui
     return j;
 }
 
+// Whether the roulette of colony c may start its steps from the short lists
+// (it then does where enough rows count, by_list): at tile 4 (n <= 256 by default)
+// a step from the list takes longer than one from the row (n = 200: 0.41 against
+// 0.37 us), except for the rows of five blocks that have the flat layout; and
+// of up to 512 cities, up to 8 ants, one to an XCD's L2, gain nothing even
+// when converged (n = 400, m = 8 0.150 against 0.146 ms; m = 16 0.127 against
+// 0.150).  What builds the lists and what reads them ask this same question.
+constexpr int kMinListCities = 256, kMaxFlatCities = 320;
+__host__ __device__ inline bool uses_lists(const Colony& c) {
+    return c.n > kMinListCities && (c.n <= kMaxFlatCities || c.tile == 8) && c.waves == 1 &&
+           (c.n > 512 || c.m > 8);
+}
+
 // Lists of the n rows of colony c from its current choice matrix, and the
 // rows the roulette starts from (c.by_list); wide lists where c.wide is
 // not null.

@@ -100,3 +100,27 @@ def test_wide_lists(rule, kind, n):
 def test_equal_weights(rule, side, beta):
     xy = np.array([(x, y) for x in range(side) for y in range(side)], np.int64) * 10
     check(rule, tsp_inputs.euc2d(xy), 30, 1, beta, "own")
+
+
+@pytest.mark.parametrize("kind", ["own", "steep"])
+@pytest.mark.parametrize("n,m", [(320, 8), (321, 9), (512, 8), (512, 9), (513, 8)])
+def test_few_ants(kind, n, m):
+    """Ant counts on each side of the line below which short rows have no lists,
+    after a product construction has built lists that are then out of date."""
+    from paper_1101_2678_amd.aco import Colony
+
+    _, d = tsp_inputs.instance(n, "uniform", seed=n)
+    tau = pheromone(kind, n, np.random.default_rng(n))
+    ref = oracle.init(d, m, 1, 2, 0.5, 3)
+    col = Colony(d, m, 1, 2, 0.5, 3, atomic=False)
+    steep = pheromone("steep", n, np.random.default_rng(n + 1))
+    col.restore(steep, 0)
+    col.construct_product(0)
+    col.restore(ref.tau if tau is None else tau, 0)
+    if tau is not None:
+        ref.choice = oracle.choice(tau, d, 1, 2)
+    tours, lens = oracle.construct(ref.choice, d, m, 3, 0, threads=ORACLE_THREADS)
+    col.construct(0)
+    got, got_lens = col.tours()
+    assert np.array_equal(got, tours) and np.array_equal(got_lens, lens)
+    col.close()
