@@ -80,8 +80,8 @@ __device__ __forceinline__ void mark_visited(int j, int lane, B& lane_bits,
     lane_bits &= lane == owner ? ~((B)1 << bit) : ~(B)0;
 }
 
-// Stages the masked weights of block `b` into s_w (city 64b + t at
-// s_w[64 (b mod G) + t]).  The block lives in pass b/G, lanes
+// Stages the masked weights of block `b` into s_w (city 64b + t at s_w[t]).
+// The block lives in pass b/G, lanes
 // (64/G)(b mod G) .. (64/G)(b mod G + 1) - 1; the pass index is wave-uniform
 // but not a compile-time constant, so each pass has its own branch, and the
 // stores are opaque to the optimiser so that it cannot merge the branches
@@ -91,7 +91,7 @@ __device__ __forceinline__ void stage_block(const u32x4 (&wa)[P], const u32x4 (&
                                             float* s_w, int lane) {
     const int pb = b / G;
     if (lane / Tile<G>::kLanesPerBlock != (b % G)) return;
-    const uint32_t addr = (uint32_t)(uintptr_t)(s_w + lane * G);
+    const uint32_t addr = (uint32_t)(uintptr_t)(s_w + lane % Tile<G>::kLanesPerBlock * G);
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         if (p == pb) {
@@ -115,7 +115,9 @@ __device__ __forceinline__ void stage_block(const u32x4 (&wa)[P], const u32x4 (&
 // cities but inside the span read padding or the next row, and masking
 // (whose bits exist only for cities < n) zeroes them.  With SKIP, a 16-byte
 // load whose four cities are all visited goes out of range instead.
-template <int G, int P, bool SKIP, typename B>
+// With FEW, at most six loads are in flight: a load waits until all but two of
+// those before it have returned.
+template <int G, int P, bool SKIP, bool FEW = false, typename B>
 __device__ __forceinline__ void load_row(const float* __restrict__ mat, int records, int row,
                                          int row_bytes, B lane_bits, int lane, u32x4 (&wa)[P],
                                          u32x4 (&wb)[P]) {
@@ -125,6 +127,7 @@ __device__ __forceinline__ void load_row(const float* __restrict__ mat, int reco
     for (int p = 0; p < P; ++p) {
         const uint32_t bits = (uint32_t)(lane_bits >> (p * G));
         const int off = (p * Tile<G>::kPass + lane * G) * 4;
+        if (FEW && p >= 2) asm volatile("s_waitcnt vmcnt(2)" : : : "memory");
         const int oa = (!SKIP || (bits & 0xFu)) ? off : kSkipOffset;
         wa[p] = __builtin_amdgcn_raw_buffer_load_b128(rs, oa, soff, 0);
         if (G == 8) {
@@ -250,7 +253,7 @@ __device__ __forceinline__ int pick_loaded(u32x4 (&wa)[P], u32x4 (&wb)[P], int n
                 w = s_w[b * 64 + lane];
             } else {
                 stage_block<G, P>(wa, wb, b, s_w, lane);
-                w = s_w[(b % G) * 64 + lane];
+                w = s_w[lane];
             }
             const uint64_t vis = lane_u64(block_bits, b);
             const float s = s64_scan(w);
@@ -277,14 +280,17 @@ __device__ __forceinline__ int r64_pick(const float* __restrict__ mat, int recor
 // LDS a construction workgroup needs besides the tour and the visited flags.
 template <int W>
 struct AntShared {
-    float w[W];   // masked weights of rows up to 1024 cities, else a staged pass
+    float w[W];   // masked weights of rows up to 1024 cities, else a staged block
     float T[64];  // block totals in block order
 };
 
-// Staging of a kernel for rows of P passes: less for long rows, so that 12
-// ants of 3000 cities fit a compute unit.
+// Staging of a kernel for rows of P passes: for long rows a block, and the 64 P
+// bytes that bits_from_flags uses, so that 14 ants of 3500 cities fit a compute
+// unit and m = n = 3500 runs in one round (with a whole pass staged two rounds,
+// 22.1 against 20.6 ms on whole rows).
 template <int G, int P>
-constexpr int kStaged = kWriteAllPasses<G, P> ? 1024 : Tile<G>::kPass;
+constexpr int kStaged = kWriteAllPasses<G, P> ? 1024 : 128;
+static_assert(64 * (kMaxCities / 512) <= 128 * sizeof(float), "bits_from_flags' scratch");
 
 // Tiles whose colonies use the short lists (uses_lists).
 template <int G>
@@ -475,6 +481,15 @@ __global__ __launch_bounds__(64) void k_construct_flat(Colony c, uint32_t iter) 
                                                      s_tour, threadIdx.x);
 }
 
+// Rows of five passes and more, read whole, are loaded in one burst where the
+// launch is bound by latency, and with few loads in flight where it is bound by
+// memory (more rows in flight then only displace one another from the caches).
+// One burst / few, alpha 0, beta 1: n = 2400, m = 1024 2.80 / 3.17 ms, m = 2048 5.15 /
+// 5.20, m = 2400 6.16 / 5.93; n = 3000, m = 1400 5.88 / 5.85, m = 2000 8.5 / 8.3; n =
+// 4096, m = 1000 8.18 / 8.22, m = 1500 13.4 / 12.2.
+constexpr int kMinFewPasses = 5;
+__device__ __forceinline__ bool memory_bound(const Colony& c) { return c.m * c.n >= 5000000; }
+
 // The whole tour of ant k of colony c in iteration `iter`: placement, n - 1
 // roulette steps, then length, deposit, tour and neighbour tables.
 template <int G, int P, bool SKIP, bool LOAD_FIRST, bool LIST, int W>
@@ -537,20 +552,28 @@ __device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t i
             return j < 0 ? 0 : j;
         });
     } else {
-        cur = walk<true>(n, key, iter, k, s_tour, lane, [&](int at, float u, int) {
-            u32x4 wa[P], wb[P];
-            if (LOAD_FIRST)
-                load_row<G, P, SKIP>(c.choice, records, at, row_bytes, lane_bits, lane, wa, wb);
-            mark_visited<G>(at, lane, lane_bits, block_bits);
-            if (!LOAD_FIRST)
-                load_row<G, P, SKIP>(c.choice, records, at, row_bytes, lane_bits, lane, wa, wb);
-            const int j = pick_loaded<G, P>(wa, wb, n, lane_bits, block_bits, sh.T, sh.w, u,
-                                            lane);
-            // At every step at least one city is unvisited, so j >= 0; the
-            // clamp only keeps the LDS indices in range should that ever
-            // break.
-            return j < 0 ? 0 : j;
-        });
+        const auto whole_rows = [&]<bool FEW>() {
+            cur = walk<true>(n, key, iter, k, s_tour, lane, [&](int at, float u, int) {
+                u32x4 wa[P], wb[P];
+                if (LOAD_FIRST)
+                    load_row<G, P, SKIP, FEW>(c.choice, records, at, row_bytes, lane_bits, lane,
+                                              wa, wb);
+                mark_visited<G>(at, lane, lane_bits, block_bits);
+                if (!LOAD_FIRST)
+                    load_row<G, P, SKIP, FEW>(c.choice, records, at, row_bytes, lane_bits, lane,
+                                              wa, wb);
+                const int j = pick_loaded<G, P>(wa, wb, n, lane_bits, block_bits, sh.T, sh.w, u,
+                                                lane);
+                // At every step at least one city is unvisited, so j >= 0; the
+                // clamp only keeps the LDS indices in range should that ever
+                // break.
+                return j < 0 ? 0 : j;
+            });
+        };
+        if (P >= kMinFewPasses && memory_bound(c))
+            whole_rows.template operator()<(P >= kMinFewPasses)>();
+        else
+            whole_rows.template operator()<false>();
     }
     finish_ant(c, k, cur, s_tour, lane);
 }

@@ -67,3 +67,21 @@ def test_many_ants_stay_resident(n):
 
     assert ants_per_cu(n) * 256 >= n
     assert ants_per_cu(16384) >= 20
+
+
+@pytest.mark.parametrize("n,m", [(2100, 2380), (2100, 2381), (2600, 1924), (3100, 1613),
+                                 (4096, 1220), (4096, 1221)])
+def test_whole_rows_on_each_side_of_the_memory_bound(n, m):
+    """Rows of five to eight passes that no list settles, loaded in one burst
+    and with few loads in flight (from m n = 5e6 on)."""
+    from paper_1101_2678_amd.aco import Colony
+
+    _, d = tsp_inputs.instance(n, "uniform", seed=n)
+    ref = oracle.init(d, m, 0, 1, 0.5, 7)
+    col = Colony(d, m, 0, 1, 0.5, 7, atomic=False)
+    col.construct(2)
+    tours, lens = col.tours()
+    for k in np.linspace(0, m - 1, 9).astype(int):
+        tour, length = oracle.construct_ant(ref.choice, d, 7, 2, int(k))
+        assert np.array_equal(tours[k], tour) and lens[k] == length, k
+    col.close()
