@@ -176,7 +176,7 @@ aco_status aco_solve(aco_ctx* c, uint32_t iters, aco_update_kind kind,
  * (step, ant, iter, 1 + j / 4); the start city is drawn as for aco_construct.
  * This is not a sample of Eq. (1): the win probabilities differ from the
  * proportional ones.  Tours, lengths, deposits and the update are those of
- * aco_construct / aco_update.  Two kernel launches.  Asynchronous. */
+ * aco_construct / aco_update.  At most two kernel launches.  Asynchronous. */
 aco_status aco_construct_product(aco_ctx* c, uint32_t iter);
 
 /* aco_solve with aco_construct_product in place of aco_construct.

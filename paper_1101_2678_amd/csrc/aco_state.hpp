@@ -32,7 +32,7 @@ struct Colony {
     double* delta;       // n x ld binary64 deposits (atomic update), or null
     uint32_t* iter_dev;  // next iteration (batched path; advanced on the device)
     uint64_t* lists;     // n x 64 entries: the short list of every choice row (shortlist.hpp)
-    uint8_t* by_list;    // n (64 a block): 1 where the roulette starts from the list
+    uint8_t* by_list;    // n (64 a block): which rules start from row i's list (shortlist.hpp)
     int32_t tile;        // construction tile: cities per lane per pass (4 or 8)
     int32_t waves;       // construction wavefronts per ant (1, or 2 / 4 for n <= 1024)
     int32_t dep_emin;    // every deposit fl32(1/C^k) has a binary32 exponent field >= this

@@ -311,15 +311,7 @@ __host__ __device__ size_t masked_lds_bytes(int n) {
 // Whether the roulette of colony c starts its steps from the short lists:
 // where half of the rows have a list that covers them well.
 __device__ __forceinline__ bool starts_from_lists(const Colony& c, int lane) {
-    if (!uses_lists(c)) return false;
-    int rows = 0;
-    for (int j = 16 * lane; j < c.n; j += 16 * 64) {  // by_list is 0 past n
-        const uint4 v = *reinterpret_cast<const uint4*>(c.by_list + j);
-        rows += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) rows += __shfl_xor(rows, off);
-    return 2 * __builtin_amdgcn_readfirstlane(rows) >= c.n;
+    return uses_lists(c) && half_by_list(c, kRouletteRow, lane);
 }
 
 // The end of a tour: its last city `cur`, then length, deposit, tour and

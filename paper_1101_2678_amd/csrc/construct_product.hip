@@ -10,19 +10,19 @@
 // (step, ant, iter, 1 + j / 4), key = seed: one Philox block serves four
 // consecutive cities.
 //
-// One wavefront per ant.  A step draws for the 63 largest entries of the row
-// first (one Philox block a lane, 512 bytes read): a winner above the largest
-// entry of the rest is the winner of the whole row, and nearly every step
-// ends there, bound by the latency of that chain.  Otherwise the wave reads
-// the whole row; in pass p lane l holds cities 512 p + 8 l .. +7 (two 16-byte
-// loads of the choice row, two Philox blocks).  All loads of such a step
-// are issued before the first Philox block is computed, so the row streams
-// while the vector unit generates the draws; it does n / 4 Philox blocks and
-// reads 4n bytes, which makes it bound by integer multiply throughput rather
-// than by memory.  Each lane keeps only the
-// largest product key of each pass (one max per city); a DPP reduction gives
-// the wave's largest key, a ballot per pass finds the lowest pass and lane
-// holding it, and that lane's lowest position holding it gives the city.
+// One wavefront per ant.  Where the weights of the rows differ enough, a step
+// draws for the 63 largest entries of the row first (one Philox block a lane,
+// 512 bytes read): a winner above the largest entry of the rest is the winner of
+// the whole row, and nearly every step ends there, bound by the latency of that
+// chain.  Otherwise the wave reads the whole row; in pass p lane l holds cities
+// 512 p + 8 l .. +7 (two 16-byte loads of the choice row, two Philox blocks).
+// All loads of such a step are issued before the first Philox block is
+// computed, so the row streams while the vector unit generates the draws; it
+// does n / 4 Philox blocks and reads 4n bytes, which makes it bound by integer
+// multiply throughput rather than by memory.  Each lane keeps only the largest
+// product key of each pass (one max per city); a DPP reduction gives the wave's
+// largest key, a ballot per pass finds the lowest pass and lane holding it, and
+// that lane's lowest position holding it gives the city.
 #include <hip/hip_runtime.h>
 
 #include "aco_device.hpp"
@@ -303,6 +303,32 @@ __device__ __forceinline__ int product_wide_pick(const WideEntries& v, const uin
     return __builtin_amdgcn_readlane(city, __builtin_ctzll(ballot(largest == top)));
 }
 
+// Bits of a new tour: cities < n.
+template <int P>
+__device__ __forceinline__ uint64_t initial_bits(int n, int lane) {
+    uint64_t bits = 0;
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int e = 0; e < kG; ++e)
+            if (city_of(p, lane, e) < n) bits |= 1ull << (kG * p + e);
+    return bits;
+}
+
+// Clears city j's bit in the lane that holds it.
+__device__ __forceinline__ void mark_visited(int j, int lane, uint64_t& bits) {
+    // j >= 0: unsigned, so the divisions are shifts and masks
+    const uint32_t uj = (uint32_t)j;
+    const uint32_t p = uj / kPass, rem = uj - p * kPass;
+    if ((int)(rem / kG) == lane) bits &= ~(1ull << (kG * p + rem % kG));
+}
+
+// Whether colony c's product rule may use the short lists: not where every
+// weight is tau^0 / d^0 = 1.  What builds the lists and what reads them ask this.
+__host__ __device__ inline bool product_uses_lists(const Colony& c) {
+    return c.alpha != 0 || c.beta != 0;
+}
+
 template <int P>
 __global__ __launch_bounds__(64) void k_construct_product(Colony c, uint32_t iter) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -311,15 +337,11 @@ __global__ __launch_bounds__(64) void k_construct_product(Colony c, uint32_t ite
     const int k = ant_of_block(blockIdx.x, c.m);
     const int n = c.n;
     uint16_t* s_tour = reinterpret_cast<uint16_t*>(smem);
-    uint8_t* s_seen = clear_flags(smem + tour_bytes(n), n, 512 * P, lane);
     const PhiloxKey key{(uint32_t)c.seed, (uint32_t)(c.seed >> 32)};
-    const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
     const uint32_t x0 = draw(key, iter, (uint32_t)k, 0u);
     int cur = (int)(((uint64_t)x0 * (uint64_t)(uint32_t)n) >> 32);
 
-    const auto whole_row = [&](int at, int step) {
-        uint64_t bits, blocks;
-        bits_from_flags<P>(reinterpret_cast<const uint2*>(s_seen), s_bits, lane, bits, blocks);
+    const auto whole_row = [&](int at, int step, uint64_t bits) {
         const PhiloxDraws draws{key.k0, key.k1, (uint32_t)step, (uint32_t)k, iter};
         const uint32_t j =
             product_pick<P>(c.choice + (size_t)at * c.ld, n, bits, draws, lane).city;
@@ -328,35 +350,51 @@ __global__ __launch_bounds__(64) void k_construct_product(Colony c, uint32_t ite
         return j == ~0u ? 0 : (int)j;
     };
 
-    // A step reads its city's short list first, for long rows the wide list
-    // where that does not settle the selection, and then the whole row.
-    // Whole rows only -> lists, mean of 20 iterations with m = n: n = 2400
-    // 8.56 -> 1.30 ms, n = 1000 0.816 -> 0.400 ms, n = 333 0.177 -> 0.130 ms,
-    // n = 100 0.0546 -> 0.0459 ms (with the launch that builds the lists, 4 to
-    // 15 us).
-    int step = 1;
-    do {
-        const u32x2 entry = load_list(lists, cur, lane);
-        if (lane == 0) {
-            s_tour[step - 1] = (uint16_t)cur;
-            s_seen[cur] = 1;
+    if (product_uses_lists(c) && half_by_list(c, kProductRow, lane)) {
+        // A step reads its city's short list first, for long rows the wide
+        // list where that does not settle the selection, and then the whole
+        // row.  Whole rows only -> lists, mean of 20 iterations with m = n: n =
+        // 2400 8.56 -> 1.30 ms, n = 1000 0.816 -> 0.400 ms, n = 333 0.177 -> 0.130
+        // ms, n = 100 0.0546 -> 0.0459 ms (with the launch that builds the
+        // lists, 4 to 15 us).
+        uint8_t* s_seen = clear_flags(smem + tour_bytes(n), n, 512 * P, lane);
+        const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
+        int step = 1;
+        do {
+            const u32x2 entry = load_list(lists, cur, lane);
+            if (lane == 0) {
+                s_tour[step - 1] = (uint16_t)cur;
+                s_seen[cur] = 1;
+            }
+            const uint64_t hit =
+                product_list_hit(entry, s_seen[list_city(entry.y)] == 0, key.k0, key.k1,
+                                 (uint32_t)step, (uint32_t)k, iter, lane);
+            if (__builtin_expect(hit != 0, 1)) {
+                cur = list_city(__builtin_amdgcn_readlane(entry.y, __builtin_ctzll(hit)));
+            } else {
+                int next = -1;
+                if constexpr (kPass * (P - 1) >= kMinWideCities)
+                    next = product_wide_pick(load_wide(wide_rsrc(c), cur, lane), s_seen, key.k0,
+                                             key.k1, (uint32_t)step, (uint32_t)k, iter, lane);
+                if (next < 0) {
+                    uint64_t bits, blocks;
+                    bits_from_flags<P>(reinterpret_cast<const uint2*>(s_seen), s_bits, lane, bits,
+                                       blocks);
+                    next = whole_row(cur, step, bits);
+                }
+                cur = next;
+            }
+            // one city for the wavefront
+            cur = __builtin_amdgcn_readfirstlane(cur);
+        } while (++step < n);
+    } else {
+        uint64_t bits = initial_bits<P>(n, lane);
+        for (int step = 1; step < n; ++step) {
+            if (lane == 0) s_tour[step - 1] = (uint16_t)cur;
+            mark_visited(cur, lane, bits);
+            cur = __builtin_amdgcn_readfirstlane(whole_row(cur, step, bits));
         }
-        const uint64_t hit =
-            product_list_hit(entry, s_seen[list_city(entry.y)] == 0, key.k0, key.k1,
-                             (uint32_t)step, (uint32_t)k, iter, lane);
-        if (__builtin_expect(hit != 0, 1)) {
-            cur = list_city(__builtin_amdgcn_readlane(entry.y, __builtin_ctzll(hit)));
-        } else {
-            int next = -1;
-            if constexpr (kPass * (P - 1) >= kMinWideCities)
-                next = product_wide_pick(load_wide(wide_rsrc(c), cur, lane), s_seen, key.k0, key.k1,
-                                         (uint32_t)step, (uint32_t)k, iter, lane);
-            if (next < 0) next = whole_row(cur, step);
-            cur = next;
-        }
-        // one city for the wavefront
-        cur = __builtin_amdgcn_readfirstlane(cur);
-    } while (++step < n);
+    }
     if (lane == 0) s_tour[n - 1] = (uint16_t)cur;
     __syncthreads();
     if (lane == 0) s_tour[n] = s_tour[0];
@@ -437,8 +475,10 @@ hipError_t dispatch_passes(int n, F&& f) {
 
 hipError_t launch_construct_product(const Colony& c, uint32_t iter, hipStream_t s) {
     if (c.n < 1 || c.n > kMaxCities) return hipErrorInvalidValue;
-    const hipError_t e = launch_short_lists(c, s);
-    if (e != hipSuccess) return e;
+    if (product_uses_lists(c)) {
+        const hipError_t e = launch_short_lists(c, s);
+        if (e != hipSuccess) return e;
+    }
     return dispatch_passes(c.n, [&]<int P>() {
         hipLaunchKernelGGL((k_construct_product<P>), dim3(c.m), dim3(64),
                            tour_bytes(c.n) + seen_lds_bytes(c.n), s, c, iter);

@@ -49,6 +49,18 @@ __device__ __forceinline__ float by_list_share(int n, int m) {
     return share < 0.02f ? 0.02f : share > most ? most : share;
 }
 
+// A row counts for the product rule's lists where the draws of its entries
+// settle a step on the whole of a new tour with probability 1 - 2^-8 or more:
+// entry j's product passes the tail's largest weight M unless r <= M / w_j, so
+// that the entries together fail with probability prod M / w_j, and the sum
+// of their log2(w_j / M) is at least an eighth of the bins between them and the
+// first bin of the tail, summed over the entries.  With beta = 2 that sum is about
+// 87 (w falls as 1 / j), with beta = 1 43; a launch starts from the lists where
+// half of the rows count.  Without the vote, rows of equal weights (alpha = beta
+// = 0, or beta = 0 on a new colony) paid for a list that settles nothing at
+// every step: n = 100 0.053 -> 0.084 ms, 1000 0.86 -> 1.09, 2400 8.4 -> 9.7.
+constexpr uint32_t kProductBins = 8 * 8;
+
 // Wide lists: construction with m = n, without and with them, n = 3000 by
 // iteration: 12.3 and 12.3 ms in the second (uniform cities), 2.10 and 2.16 in
 // the 13th, 1.64 and 1.34 in the 24th; clustered cities 11.3 and 10.8, 1.95 and
@@ -223,6 +235,12 @@ __device__ __forceinline__ void short_list_row(const Colony& c, int i,
         return (uint32_t)__builtin_amdgcn_readfirstlane(wave_sum(bins));
     };
     const uint32_t taken = bins_up_to(kListEntries);
+    // sum over the entries of the bins from theirs to bin `taken`
+    uint32_t above_tail = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        above_tail += 4u * (uint32_t)lane + (uint32_t)e < taken ? before + cum[e] : 0u;
+    above_tail = wave_sum(above_tail);
     const uint32_t wide_taken = WIDE ? bins_up_to(kWideEntries) : 0u;
     select_entries<Q>(w, edge, taken, wave, lane, sh.tier[0]);
     if constexpr (WIDE) select_entries<Q>(w, edge, wide_taken, wave, lane, sh.tier[1]);
@@ -240,7 +258,11 @@ __device__ __forceinline__ void short_list_row(const Colony& c, int i,
         [&](int rank, uint32_t bits, int city, float above, int) {
             out[rank] = u32x2{bits, list_meta(city, above)};
         });
-    if (tid == 0) c.by_list[i] = entries > 0 && rest <= total * by_list_share(n, c.m) ? 1 : 0;
+    if (tid == 0) {
+        const bool roulette = entries > 0 && rest <= total * by_list_share(n, c.m);
+        c.by_list[i] = (uint8_t)((roulette ? kRouletteRow : 0u) |
+                                 (above_tail >= kProductBins ? kProductRow : 0u));
+    }
     if (wave == 0 && lane >= entries && lane < kListEntries) out[lane] = u32x2{0u, 0u};
     const float short_rest = rest;
     int wide_tried = 0;

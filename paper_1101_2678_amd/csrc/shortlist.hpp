@@ -185,8 +185,26 @@ __host__ __device__ inline bool uses_lists(const Colony& c) {
            (c.n > 512 || c.m > 8);
 }
 
+// Bits of c.by_list[i]: whether row i counts for starting the steps of a
+// construction from the lists (shortlist.hip).
+constexpr uint32_t kRouletteRow = 1, kProductRow = 2;
+
+// Whether half of colony c's rows count for the rule of bit `row_bit`; the same
+// for every wavefront.
+__device__ __forceinline__ bool half_by_list(const Colony& c, uint32_t row_bit, int lane) {
+    const uint32_t mask = row_bit * 0x01010101u;
+    int rows = 0;
+    for (int j = 16 * lane; j < c.n; j += 16 * 64) {  // by_list is 0 past n
+        const uint4 v = *reinterpret_cast<const uint4*>(c.by_list + j);
+        rows += __popc(v.x & mask) + __popc(v.y & mask) + __popc(v.z & mask) + __popc(v.w & mask);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) rows += __shfl_xor(rows, off);
+    return 2 * __builtin_amdgcn_readfirstlane(rows) >= c.n;
+}
+
 // Lists of the n rows of colony c from its current choice matrix, and the
-// rows the roulette starts from (c.by_list); wide lists where c.wide is
+// rows that count for starting from them (c.by_list); wide lists where c.wide is
 // not null.
 hipError_t launch_short_lists(const Colony& c, hipStream_t s);
 // As above for the rows of a batch: (colony << 16) | row per entry of rowmap;

@@ -124,3 +124,12 @@ def test_few_ants(kind, n, m):
     got, got_lens = col.tours()
     assert np.array_equal(got, tours) and np.array_equal(got_lens, lens)
     col.close()
+
+
+@pytest.mark.parametrize("alpha,beta", [(0, 0), (1, 0), (2, 0)])
+@pytest.mark.parametrize("n,m", [(63, 63), (65, 65), (333, 333), (1000, 60), (2561, 8)])
+def test_product_rows_of_equal_weights(n, m, alpha, beta):
+    """Product constructions that start on whole rows, because all weights are
+    equal, and where tau counts may go over to the lists as it gathers."""
+    _, d = tsp_inputs.instance(n, "uniform", seed=n)
+    check("product", d, m, alpha, beta, "own", iters=8 if n < 400 else 2)
