@@ -246,7 +246,15 @@ __global__ __launch_bounds__(kListThreads) void k_nn_lists_batch(
 // With the launch for the lists, construction with nn = 30, mean of 20
 // iterations: n = 3000 1.26 -> 1.13 ms, n = 2400 0.836 -> 0.790, n = 1500
 // 0.442 -> 0.439, n = 1000 0.265 both, n = 100 0.0346 -> 0.0390.
+// Fewer than 64 ants leave too few such steps for the launch (n = 1300 with 4
+// ants 0.483 -> 0.504 ms, n = 2400 with 64 0.663 -> 0.657), and without the heuristic
+// (beta = 0) a new colony's rows have no list (n = 2400, m = n 0.919 -> 0.978 ms).
+// What builds the lists and what reads them ask nn_uses_lists.
 constexpr int kMinNnListPasses = 6;
+constexpr int kMinNnListAnts = 64;
+__host__ __device__ inline bool nn_uses_lists(const Colony& c) {
+    return c.n > 256 * (kMinNnListPasses - 1) && c.m >= kMinNnListAnts && c.beta > 0;
+}
 template <int P>
 constexpr bool kNnLists = P >= kMinNnListPasses;
 
@@ -281,6 +289,7 @@ __global__ __launch_bounds__(64) void k_construct_nn(Colony c, NnTables t, uint3
     const __amdgpu_buffer_rsrc_t crs = __builtin_amdgcn_make_buffer_rsrc(
         t.cand, (short)0, n * kp * (int)sizeof(uint64_t), 0x00020000);
     const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
+    const bool use_lists = kNnLists<P> && nn_uses_lists(c);
     // A step's candidate row is loaded as soon as its city is known; the
     // city's bookkeeping (tour entry, visited flag) follows the load, before
     // the flags are read (one wavefront: its LDS accesses stay in order).  64
@@ -315,7 +324,7 @@ __global__ __launch_bounds__(64) void k_construct_nn(Colony c, NnTables t, uint3
                 const int r = hit ? __builtin_ctzll(hit) : 63 - __builtin_clzll(live);
                 next = __builtin_amdgcn_readlane(city, r);
             } else {
-                next = kNnLists<P> ? largest_listed(lists, cur, s_vis, lane) : -1;
+                next = use_lists ? largest_listed(lists, cur, s_vis, lane) : -1;
                 if (next < 0) {
                     next = fallback_argmax<P>(c.choice + (size_t)cur * c.ld, n, s_vis, lane);
                     // at least one city is unvisited, so next >= 0; the clamp
@@ -576,7 +585,7 @@ hipError_t launch_construct_nn(const Colony& c, const NnTables& t, uint32_t iter
     const int cells = c.n * t.kp;
     hipLaunchKernelGGL(k_cand_refresh, dim3((cells + 255) / 256), dim3(256), 0, s, c, t);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess && c.n > 256 * (kMinNnListPasses - 1)) {
+    if (e == hipSuccess && nn_uses_lists(c)) {
         Colony short_only = c;
         short_only.wide = nullptr;
         e = launch_short_lists(short_only, s);
