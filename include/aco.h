@@ -363,7 +363,7 @@ aco_status aco_batch_init(aco_batch** out, int32_t count, const aco_params* para
                           void* hip_stream);
 
 /* Advances every instance by `iters` iterations (construction, best-so-far,
- * gather update): four launches per iteration for the whole batch.  With
+ * gather update): at most four launches per iteration for the whole batch.  With
  * use_graph != 0 the launches are captured once into a HIP graph (kept for
  * the next call with the same `iters`) and replayed; this needs a
  * non-default stream.  Asynchronous. */
@@ -479,7 +479,7 @@ aco_status aco_server_submit(aco_server* s, const aco_params* p, const int32_t* 
  * whose initialisation has finished join their class, and starts the next
  * tick of every idle class that has running requests.  A tick advances each
  * running request of the class by one iteration (Section II: construction,
- * best-so-far, update) in four launches.  *running_out (may be NULL)
+ * best-so-far, update) in at most four launches.  *running_out (may be NULL)
  * receives the number of requests in ticks now in flight. */
 aco_status aco_server_step(aco_server* s, int32_t* running_out);
 

@@ -2,10 +2,10 @@
 // the construction-tile autotuner.
 //
 // A batch keeps every instance resident in one caller-owned workspace.  One
-// AS iteration of the whole batch is four launches: the short lists of every
-// row, construction of every
-// ant of every instance (one workgroup per ant, instances ordered largest n
-// first so the longest tours start first), the best-so-far of every
+// AS iteration of the whole batch is at most four launches: the short lists of
+// the rows that use them (if any do), construction of every ant of every
+// instance (one workgroup per ant, instances ordered largest n first so the
+// longest tours start first), the best-so-far of every
 // instance, and the gather update of every row of every instance.  Each
 // instance keeps its own iteration counter on the device, so the launches of
 // `iters` iterations can be captured once into a HIP graph and replayed.
@@ -36,6 +36,7 @@ struct aco_batch {
     uint32_t* d_antmap = nullptr;      // (position << 16) | ant
     uint32_t* d_rowmap = nullptr;      // (position << 16) | row
     int total_ants = 0, total_rows = 0, max_n = 0, max_ld = 0;
+    int list_rows = 0;             // rows at the head of rowmap that may have lists
     hipStream_t stream = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -97,7 +98,7 @@ aco_status batch_device_fail(aco_batch* b, hipError_t e, const char* where) {
 
 // One construction of every instance: the lists, then the ants.
 hipError_t enqueue_construction(aco_batch* b) {
-    hipError_t e = aco::launch_short_lists_batch(b->d_cols, b->d_rowmap, b->total_rows, b->max_n,
+    hipError_t e = aco::launch_short_lists_batch(b->d_cols, b->d_rowmap, b->list_rows, b->max_n,
                                                  b->stream);
     if (e != hipSuccess) return e;
     return aco::launch_construct_batch(
@@ -241,6 +242,7 @@ aco_status aco_batch_init(aco_batch** out, int32_t count, const aco_params* para
     }
     b->total_ants = B.total_ants;
     b->total_rows = B.total_rows;
+    b->list_rows = aco::list_rows(launch_cols.data(), count);
     b->d_cols = reinterpret_cast<aco::Colony*>(base + B.cols_off);
     b->d_antmap = reinterpret_cast<uint32_t*>(base + B.antmap_off);
     b->d_rowmap = reinterpret_cast<uint32_t*>(base + B.rowmap_off);
@@ -377,6 +379,7 @@ aco_status aco_batch_set_config(aco_batch* b, const aco_batch_config* cfg) {
         b->cols[q].tile = tile;
         b->launch_cols[pos].tile = tile;
     }
+    b->list_rows = aco::list_rows(b->launch_cols.data(), b->count);
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->d_cols, b->launch_cols.data(), sizeof(aco::Colony) * b->count,
                            hipMemcpyHostToDevice, b->stream);

@@ -10,8 +10,9 @@
 //
 // Each size class has its own running set, device tables, stream and tick:
 // a tick advances every running request of the class by one AS iteration with
-// the batched kernels (one construction launch over all their ants, one
-// best-so-far launch, one gather launch over all their rows).  Classes tick
+// the batched kernels (a launch for the short lists of the rows that use them,
+// one construction launch over all their ants, one best-so-far launch, one
+// gather launch over all their rows).  Classes tick
 // independently and concurrently, so a 100-city request is not paced by the
 // iterations of a 3000-city one, and requests that arrive while others run
 // share the device.  aco_server_step never blocks: it completes the ticks
@@ -57,7 +58,7 @@ struct SizeClass {
     std::vector<int> running;  // slot indices in launch order (largest n first)
     std::vector<aco::Colony> h_cols;
     std::vector<uint32_t> h_antmap, h_rowmap;  // host copies kept alive for async uploads
-    int total_ants = 0, total_rows = 0, run_max_n = 0, run_max_ld = 0;
+    int total_ants = 0, total_rows = 0, list_rows = 0, run_max_n = 0, run_max_ld = 0;
     bool dirty = false, in_flight = false;
     hipStream_t stream = nullptr;
     hipEvent_t done = nullptr;
@@ -175,6 +176,7 @@ hipError_t rebuild_class(aco_server* s, int c) {
     k.running = run;
     k.total_ants = (int)k.h_antmap.size();
     k.total_rows = (int)k.h_rowmap.size();
+    k.list_rows = aco::list_rows(k.h_cols.data(), (int)k.h_cols.size());
     k.run_max_n = max_n;
     k.run_max_ld = max_ld;
     k.dirty = false;
@@ -330,7 +332,7 @@ aco_status aco_server_step(aco_server* s, int32_t* running_out) {
         if (k.dirty) e = rebuild_class(s, (int)c);
         if (e != hipSuccess) return server_fail(s, e, "aco_server_step");
         if (k.running.empty()) continue;
-        e = aco::launch_short_lists_batch(k.d_cols, k.d_rowmap, k.total_rows, k.run_max_n, k.stream);
+        e = aco::launch_short_lists_batch(k.d_cols, k.d_rowmap, k.list_rows, k.run_max_n, k.stream);
         if (e != hipSuccess) return server_fail(s, e, "aco_server_step");
         e = aco::launch_construct_batch(
             k.d_cols, k.d_antmap, k.total_ants, k.run_max_n,

@@ -301,7 +301,9 @@ __global__ __launch_bounds__(kThreads) void k_short_lists(Colony c) {
     short_list_row<Q, WIDE>(c, blockIdx.x, sh);
 }
 
-// Q > 10: some colonies have wide lists.
+// Rows of colonies that use no lists leave at once.  Rows of up to 512 cities
+// have a body of their own in every launch: two blocks a wavefront.  Q > 10: some
+// colonies have wide lists.
 template <int Q>
 __global__ __launch_bounds__(kThreads) void k_short_lists_batch(
     const Colony* __restrict__ cols, const uint32_t* __restrict__ rowmap) {
@@ -309,6 +311,11 @@ __global__ __launch_bounds__(kThreads) void k_short_lists_batch(
     const uint32_t e = rowmap[blockIdx.x];
     const Colony c = cols[e >> 16];
     const int i = (int)(e & 0xffffu);
+    if (!uses_lists(c)) return;
+    if (c.n <= 512) {
+        short_list_row<2, false>(c, i, sh);
+        return;
+    }
     if constexpr (Q > 10) {
         if (c.wide) {
             __shared__ ListShared<2> wide;
@@ -321,11 +328,11 @@ __global__ __launch_bounds__(kThreads) void k_short_lists_batch(
 
 }  // namespace
 
-hipError_t launch_short_lists_batch(const Colony* cols, const uint32_t* rowmap, int total_rows,
+hipError_t launch_short_lists_batch(const Colony* cols, const uint32_t* rowmap, int list_rows,
                                     int max_n, hipStream_t s) {
-    if (total_rows <= 0) return hipSuccess;
+    if (list_rows <= 0) return hipSuccess;
     if (max_n < 1 || max_n > kMaxCities) return hipErrorInvalidValue;
-    const dim3 grid(total_rows), block(kThreads);
+    const dim3 grid(list_rows), block(kThreads);
     if (max_n <= 1024)
         hipLaunchKernelGGL(k_short_lists_batch<4>, grid, block, 0, s, cols, rowmap);
     else if (max_n <= 2560)
@@ -335,10 +342,21 @@ hipError_t launch_short_lists_batch(const Colony* cols, const uint32_t* rowmap, 
     return hipGetLastError();
 }
 
+int list_rows(const Colony* cols, int count) {
+    int rows = 0, upto = 0;
+    for (int q = 0; q < count; ++q) {
+        rows += cols[q].n;
+        if (uses_lists(cols[q])) upto = rows;
+    }
+    return upto;
+}
+
 hipError_t launch_short_lists(const Colony& c, hipStream_t s) {
     if (c.n < 1 || c.n > kMaxCities) return hipErrorInvalidValue;
     const dim3 grid(c.n), block(kThreads);
-    if (c.n <= 1024)
+    if (c.n <= 512)
+        hipLaunchKernelGGL((k_short_lists<2, false>), grid, block, 0, s, c);
+    else if (c.n <= 1024)
         hipLaunchKernelGGL((k_short_lists<4, false>), grid, block, 0, s, c);
     else if (c.n <= 2560)
         hipLaunchKernelGGL((k_short_lists<10, false>), grid, block, 0, s, c);

@@ -207,9 +207,14 @@ __device__ __forceinline__ bool half_by_list(const Colony& c, uint32_t row_bit, 
 // rows that count for starting from them (c.by_list); wide lists where c.wide is
 // not null.
 hipError_t launch_short_lists(const Colony& c, hipStream_t s);
-// As above for the rows of a batch: (colony << 16) | row per entry of rowmap;
+// As above for the first list_rows entries of a batch's rowmap ((colony << 16) |
+// row, colony by colony); rows of colonies that use no lists are left out.
 // max_n: the largest n among the colonies.
-hipError_t launch_short_lists_batch(const Colony* cols, const uint32_t* rowmap, int total_rows,
+hipError_t launch_short_lists_batch(const Colony* cols, const uint32_t* rowmap, int list_rows,
                                     int max_n, hipStream_t s);
+// The rows of `count` colonies (host), in their order, up to those of the last
+// colony that uses lists.  Batches order colonies by falling n, so that the rest
+// are those of the short rows, which use none.
+int list_rows(const Colony* cols, int count);
 
 }  // namespace aco
