@@ -303,6 +303,32 @@ constexpr bool kWideLists = 64 * G * (P - 1) >= kMinWideCities;
 // Dynamic LDS of an ant: the tour, then the flags.
 __host__ __device__ size_t ant_lds_bytes(int n) { return tour_lds_bytes(n) + seen_lds_bytes(n); }
 
+// Whether the flags of P passes lie in AntShared<W>::w behind what the kernel
+// for P passes stages there: in the batched launch, whose W serves rows that
+// stage two whole passes, and rows of one and of three to seven passes then ask
+// for no more LDS than their tour (n = 2400: 16 ants a compute unit against 12).
+template <int G, int P, int W>
+constexpr bool kFlagsInStaging =
+    W * sizeof(float) >=
+    (kWriteAllPasses<G, P> ? 64 * G * P : kStaged<G, P>) * sizeof(float) + 512 * P;
+
+// Dynamic LDS of an ant of n cities in the batched launch.
+size_t batch_ant_lds_bytes(int n) {
+    const int passes = (n + 511) / 512;
+    const bool flags = n <= 64 * kMaxFlatBlocks ? n > kMinListCities : passes == 2 || passes == 8;
+    return tour_lds_bytes(n) + (flags ? seen_lds_bytes(n) : 0);
+}
+
+// The same for any ant of up to max_n cities: the largest of each kind.
+size_t batch_ants_lds_bytes(int max_n) {
+    size_t most = 0;
+    for (int n : {64 * kMaxFlatBlocks, 1024, kMaxCities}) {
+        const size_t need = batch_ant_lds_bytes(n < max_n ? n : max_n);
+        most = need > most ? need : most;
+    }
+    return most;
+}
+
 // The same for an ant that keeps the visited set as factors.
 __host__ __device__ size_t masked_lds_bytes(int n) {
     return tour_lds_bytes(n) + seen_lds_bytes(n) * sizeof(float);
@@ -520,8 +546,11 @@ __device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t i
         // 13.3; mean of the first 24: 0.157 / 0.198, 0.363 / 0.519, 0.791 /
         // 1.32, 2.61 / 6.05, 5.10 / 13.2.
         const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
-        uint8_t* s_seen = clear_flags(reinterpret_cast<uint8_t*>(s_tour) + tour_lds_bytes(n), n,
-                                      512 * P, lane);
+        constexpr int kUsed = kWriteAllPasses<G, P> ? 64 * G * P : kStaged<G, P>;
+        uint8_t* s_seen = clear_flags(
+            kFlagsInStaging<G, P, W> ? reinterpret_cast<uint8_t*>(sh.w + kUsed)
+                                     : reinterpret_cast<uint8_t*>(s_tour) + tour_lds_bytes(n),
+            n, 512 * P, lane);
         cur = walk<false>(n, key, iter, k, s_tour, lane, [&](int at, float u, int i) {
             const u32x2 entry = load_list(lists, at, lane);
             if (lane == 0) {
@@ -734,7 +763,7 @@ constexpr int kCapRounds = 8;
 }  // namespace
 
 size_t batch_lds_bytes(int max_n, int wg_per_cu, size_t lds_per_cu) {
-    const size_t tour = ant_lds_bytes(max_n);
+    const size_t tour = batch_ants_lds_bytes(max_n);
     if (wg_per_cu <= 0 || lds_per_cu == 0) return tour;
     const size_t per_wg = lds_per_cu / (size_t)wg_per_cu;
     const size_t fixed = sizeof(AntShared<1024>) + 64;  // static LDS and its alignment
@@ -876,7 +905,11 @@ hipError_t launch_construct_batch(const Colony* cols, const uint32_t* antmap, in
                                   int max_n, size_t lds, hipStream_t s) {
     if (total_ants <= 0) return hipSuccess;
     if (max_n < 1 || max_n > kMaxCities) return hipErrorInvalidValue;
-    if (lds < ant_lds_bytes(max_n)) return hipErrorInvalidValue;
+    if (lds < batch_ants_lds_bytes(max_n)) return hipErrorInvalidValue;
+    static_assert(!kFlagsInStaging<8, 2, 1024> && !kFlagsInStaging<8, 8, 1024> &&
+                      kFlagsInStaging<8, 1, 1024> && kFlagsInStaging<8, 3, 1024> &&
+                      kFlagsInStaging<8, 7, 1024>,
+                  "batch_ant_lds_bytes");
     const int passes = (max_n + 511) / 512;
     const dim3 grid(total_ants), block(64);
     if (passes <= 2)

@@ -39,6 +39,13 @@ def test_long_batches_at_the_pass_bounds(sizes):
     check_batch([(n, 24) for n in sizes], 24)
 
 
+@pytest.mark.parametrize("sizes", [(2048, 2049, 600), (2561, 330), (3584, 3585)])
+def test_long_batches_of_long_rows(sizes):
+    """Rows of four to eight passes, whose flags lie behind the staged block (up to
+    seven passes) or behind the tour."""
+    check_batch([(n, 10) for n in sizes], 18)
+
+
 def test_lists_behind_colonies_without():
     """The colonies of 600 and 330 cities at tile 4 and those of up to 256 have
     no lists, nor has the one of 400 with 8 ants; those of 700, 500 and 300 do."""
