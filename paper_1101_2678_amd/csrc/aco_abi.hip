@@ -236,7 +236,7 @@ Colony carve(char* base, const Layout& L, const aco_params& p, bool with_delta, 
 // pageable memory moves row by row, about 7 us each (n = 2400: 17 ms against
 // 0.7 ms for copy and kernel).
 hipError_t upload_and_init(const Colony& col, const int32_t* dist_host, size_t base_bytes,
-                           hipStream_t stream) {
+                           bool alone, hipStream_t stream) {
     hipError_t e = hipMemsetAsync(col.tau, 0, base_bytes, stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(col.tau, dist_host, (size_t)col.n * col.n * sizeof(int32_t),
@@ -244,7 +244,7 @@ hipError_t upload_and_init(const Colony& col, const int32_t* dist_host, size_t b
     if (e == hipSuccess)
         e = launch_pad_rows(reinterpret_cast<const uint32_t*>(col.tau),
                             reinterpret_cast<uint32_t*>(col.dist), col.n, col.ld, stream);
-    if (e == hipSuccess) e = launch_init(col, stream);
+    if (e == hipSuccess) e = launch_init(col, alone, stream);
     return e;
 }
 
@@ -490,7 +490,7 @@ aco_status aco_init(aco_ctx** out, const aco_params* p, const int32_t* dist_host
                               aco::host::tile_for(p->n), aco::host::waves_for(p->n));
     c->stream = static_cast<hipStream_t>(hip_stream);
     c->ws_bytes = ws_bytes;
-    hipError_t e = aco::host::upload_and_init(c->col, dist_host, L.base_end, c->stream);
+    hipError_t e = aco::host::upload_and_init(c->col, dist_host, L.base_end, true, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
         aco_status s = device_fail(c, e, "aco_init");

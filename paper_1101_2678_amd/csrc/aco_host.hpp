@@ -40,8 +40,9 @@ Colony carve(char* base, const Layout& L, const aco_params& p, bool with_delta, 
              int tile, int waves = 1);
 // Clears the colony's base arrays, uploads the distances and enqueues the
 // initialisation kernels (nearest-neighbour tour, tau0, tau and choice fill).
+// alone: no other work is expected on the device (launch_nn_tour).
 hipError_t upload_and_init(const Colony& col, const int32_t* dist_host, size_t base_bytes,
-                           hipStream_t stream);
+                           bool alone, hipStream_t stream);
 // `rows` rows of row_bytes bytes, `pitch` bytes apart on the device, to dst
 // (host, contiguous).  Blocking.
 hipError_t read_rows(void* dst, size_t row_bytes, const void* src, size_t pitch, size_t rows);

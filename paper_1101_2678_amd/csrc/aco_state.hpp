@@ -80,12 +80,13 @@ hipError_t launch_update_gather(const Colony& c, hipStream_t s);
 // combine_in_lds: the shared-memory deposit (one global atomic per distinct
 // edge of a row's workgroup); false: one global atomic per tour edge.
 hipError_t launch_update_atomic(const Colony& c, bool combine_in_lds, hipStream_t s);
-hipError_t launch_init(const Colony& c, hipStream_t s);
+// alone: as launch_nn_tour.
+hipError_t launch_init(const Colony& c, bool alone, hipStream_t s);
 // Initialisation of `count` colonies whose distances (n x n, contiguous) lie in
-// their tau matrices: spreads them to the pitch, then as launch_init.  rowmap
-// and max_n as in launch_nn_tour_batch.
-hipError_t launch_init_batch(const Colony* cols, int count, const uint32_t* rowmap,
-                             int total_rows, int max_n, hipStream_t s);
+// their tau matrices: spreads them to the pitch, then as launch_init (alone).
+// host_cols, rowmap and max_n as in launch_nn_tour_batch.
+hipError_t launch_init_batch(const Colony* cols, const Colony* host_cols, int count,
+                             const uint32_t* rowmap, int total_rows, int max_n, hipStream_t s);
 // n rows of n 4-byte words (contiguous at src) to rows of pitch ld at dst; the
 // padding columns become 0.  src and dst must not overlap.
 hipError_t launch_pad_rows(const uint32_t* src, uint32_t* dst, int n, int ld, hipStream_t s);

@@ -256,8 +256,8 @@ aco_status aco_batch_init(aco_batch** out, int32_t count, const aco_params* para
         e = hipMemcpyAsync(b->d_rowmap, rowmap.data(), sizeof(uint32_t) * rowmap.size(),
                            hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess)
-        e = aco::launch_init_batch(b->d_cols, count, b->d_rowmap, b->total_rows, b->max_n,
-                                   b->stream);
+        e = aco::launch_init_batch(b->d_cols, launch_cols.data(), count, b->d_rowmap,
+                                   b->total_rows, b->max_n, b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) {
         const aco_status s = batch_device_fail(b, e, "aco_batch_init");
@@ -489,7 +489,7 @@ aco_status aco_autotune(void* d_workspace, size_t ws_bytes, const int32_t* sizes
             const aco::Colony col =
                 aco::host::carve(static_cast<char*>(d_workspace), L, p, false, dep_emin, tile,
                                  waves);
-            e = aco::host::upload_and_init(col, d.data(), L.base_end, s);
+            e = aco::host::upload_and_init(col, d.data(), L.base_end, true, s);
             if (e == hipSuccess) e = aco::launch_construct(col, 0, s);  // warm-up
             if (e == hipSuccess) e = hipEventRecord(e0, s);
             for (int r = 0; r < reps && e == hipSuccess; ++r)

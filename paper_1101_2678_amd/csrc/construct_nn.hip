@@ -418,7 +418,14 @@ __device__ __forceinline__ int nearest_unseen(const int32_t* row, int n, const u
 // wavefront walks; the tour is kept in LDS and summed at the end.  A step is
 // a chain of dependent reads, so the workgroup first copies the first `staged`
 // entries of every list to LDS (32 where they fit, to n = 2350, else 16;
-// n = 100 28 -> 18 us, n = 1000 290 -> 159, n = 2400 712 -> 400).
+// n = 100 28 -> 18 us, n = 1000 290 -> 159, n = 2400 712 -> 400).  That takes up
+// to a compute unit's whole LDS.  Beside other work (the server's admissions)
+// rows of more than 512 cities stage nothing: a workgroup of more than 40 KB then
+// waits until enough ants on some compute unit have ended.  Mean and longest
+// walk in a trace of requests, staged / not: n <= 256 0.04, 0.07 / 0.09, 0.22 ms;
+// n <= 512 0.07, 0.10 / 0.19, 0.86; n <= 1024 0.45, 6.3 / 0.50, 2.2; n <= 1536 3.1,
+// 10.3 / 0.73, 1.6; n <= 2048 0.90, 4.6 / 0.89, 2.3.
+constexpr int kMaxStagedBeside = 512;
 constexpr int kTourThreads = 256;
 constexpr size_t kTourLds = 160u << 10;
 
@@ -427,9 +434,9 @@ __host__ __device__ size_t nn_tour_lds(int n, int staged) {
 }
 __host__ __device__ int staged_entries(int n) { return nn_tour_lds(n, 32) <= kTourLds ? 32 : 16; }
 
-template <int P>
+template <int P, bool STAGED>
 __device__ __forceinline__ void nn_tour(const Colony& c, const NnTables& t, unsigned char* smem) {
-    const int n = c.n, nn = t.nn, kp = t.kp, staged = staged_entries(n);
+    const int n = c.n, nn = t.nn, kp = t.kp, staged = STAGED ? staged_entries(n) : kp;
     uint8_t* s_seen = smem;
     uint16_t* s_tour = reinterpret_cast<uint16_t*>(smem + kVisBytes);
     uint16_t* s_list = reinterpret_cast<uint16_t*>(smem + kVisBytes + tour_bytes(n));
@@ -443,7 +450,7 @@ __device__ __forceinline__ void nn_tour(const Colony& c, const NnTables& t, unsi
     if (tid == 0) s_tour[0] = 0;
     // 16-byte pieces of eight entries; kp = 32
     const int pieces = staged / 8;
-    for (int q = tid; q < n * pieces; q += kTourThreads) {
+    for (int q = tid; STAGED && q < n * pieces; q += kTourThreads) {
         const int i = q / pieces, e = q - i * pieces;
         reinterpret_cast<uint4*>(s_list)[q] =
             *reinterpret_cast<const uint4*>(t.nnl + (size_t)i * kp + 8 * e);
@@ -456,15 +463,18 @@ __device__ __forceinline__ void nn_tour(const Colony& c, const NnTables& t, unsi
     const int col = lane & (staged - 1);
     int cur = 0;
     for (int step = 1; step < n; ++step) {
-        const int city = s_list[cur * staged + col];
+        const int city = STAGED ? s_list[cur * staged + col] : t.nnl[(size_t)cur * kp + col];
         uint64_t live = ballot(in_held & (s_seen[city] == 0));
         int next;
         if (__builtin_expect(live != 0ull, 1)) {
             next = __builtin_amdgcn_readlane(city, __builtin_ctzll(live));
         } else {
             // the entries past the staged ones, then the whole row
-            const int more = t.nnl[(size_t)cur * kp + (lane & 31)];
-            live = ballot((lane < nn) & (s_seen[more] == 0));
+            int more = 0;
+            if (STAGED) {
+                more = t.nnl[(size_t)cur * kp + (lane & 31)];
+                live = ballot((lane < nn) & (s_seen[more] == 0));
+            }
             if (live) {
                 next = __builtin_amdgcn_readlane(more, __builtin_ctzll(live));
             } else {
@@ -495,10 +505,10 @@ __device__ __forceinline__ void nn_tour(const Colony& c, const NnTables& t, unsi
     }
 }
 
-template <int P>
+template <int P, bool STAGED>
 __global__ __launch_bounds__(kTourThreads) void k_nn_tour(Colony c) {
     extern __shared__ __align__(16) unsigned char smem[];
-    nn_tour<P>(c, init_tables(c), smem);
+    nn_tour<P, STAGED>(c, init_tables(c), smem);
 }
 
 // Workgroup q: the tour of colony cols[q]; every colony has n <= 256 P.
@@ -506,7 +516,7 @@ template <int P>
 __global__ __launch_bounds__(kTourThreads) void k_nn_tour_batch(const Colony* __restrict__ cols) {
     extern __shared__ __align__(16) unsigned char smem[];
     const Colony c = cols[blockIdx.x];
-    nn_tour<P>(c, init_tables(c), smem);
+    nn_tour<P, true>(c, init_tables(c), smem);
 }
 
 // Calls f.template operator()<P>() for a P of 1, 2, 4, 6, 8, 10, 12 or 16 with
@@ -526,19 +536,24 @@ hipError_t dispatch_scan_passes(int n, F&& f) {
 
 }  // namespace
 
-hipError_t launch_nn_tour(const Colony& c, hipStream_t s) {
+hipError_t launch_nn_tour(const Colony& c, bool alone, hipStream_t s) {
     if (c.n < 2 || c.n > kMaxCities || c.mp < 32) return hipErrorInvalidValue;
     hipError_t e = launch_nn_lists(c, init_tables(c), s);
     if (e != hipSuccess) return e;
     return dispatch_scan_passes(c.n, [&]<int P>() {
-        hipLaunchKernelGGL(k_nn_tour<P>, dim3(1), dim3(kTourThreads),
-                           nn_tour_lds(c.n, staged_entries(c.n)), s, c);
+        if (alone || c.n <= kMaxStagedBeside)
+            hipLaunchKernelGGL((k_nn_tour<P, true>), dim3(1), dim3(kTourThreads),
+                               nn_tour_lds(c.n, staged_entries(c.n)), s, c);
+        else
+            hipLaunchKernelGGL((k_nn_tour<P, false>), dim3(1), dim3(kTourThreads),
+                               nn_tour_lds(c.n, 0), s, c);
         return hipGetLastError();
     });
 }
 
-hipError_t launch_nn_tour_batch(const Colony* cols, int count, const uint32_t* rowmap,
-                                int total_rows, int max_n, hipStream_t s) {
+hipError_t launch_nn_tour_batch(const Colony* cols, const Colony* host_cols, int count,
+                                const uint32_t* rowmap, int total_rows, int max_n,
+                                hipStream_t s) {
     if (count <= 0 || total_rows <= 0) return hipSuccess;
     if (max_n < 2 || max_n > kMaxCities) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_nn_lists_batch, dim3(total_rows), dim3(kListThreads), 0, s, cols, rowmap);
@@ -546,7 +561,9 @@ hipError_t launch_nn_tour_batch(const Colony* cols, int count, const uint32_t* r
     if (e != hipSuccess) return e;
     // every colony's request: a smaller one may stage more entries a row
     size_t lds = 0;
-    for (int n = 2; n <= max_n; ++n) {
+    for (int q = 0; q < count; ++q) {
+        const int n = host_cols[q].n;
+        if (n < 2 || n > max_n) return hipErrorInvalidValue;
         const size_t need = nn_tour_lds(n, staged_entries(n));
         lds = need > lds ? need : lds;
     }

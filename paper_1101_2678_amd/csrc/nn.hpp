@@ -40,11 +40,12 @@ hipError_t launch_construct_nn(const Colony& c, const NnTables& t, uint32_t iter
 // C_nn (nearest-neighbour tour from city 0, ties to the lowest index), tau0
 // = fl32(m / C_nn) and the best-so-far reset, written to the colony.  Uses
 // the successor table as scratch for 32-entry neighbour lists, so it must run
-// before the first construction.
-hipError_t launch_nn_tour(const Colony& c, hipStream_t s);
-// The same for `count` colonies at once; rowmap: (colony << 16) | row of every
-// row of them; max_n: the largest n.
-hipError_t launch_nn_tour_batch(const Colony* cols, int count, const uint32_t* rowmap,
-                                int total_rows, int max_n, hipStream_t s);
+// before the first construction.  alone: no other work is expected on the
+// device, so that the walk may take a compute unit's LDS.
+hipError_t launch_nn_tour(const Colony& c, bool alone, hipStream_t s);
+// The same for `count` colonies at once (alone); host_cols: the host's copy of
+// cols; rowmap: (colony << 16) | row of every row of them; max_n: the largest n.
+hipError_t launch_nn_tour_batch(const Colony* cols, const Colony* host_cols, int count,
+                                const uint32_t* rowmap, int total_rows, int max_n, hipStream_t s);
 
 }  // namespace aco

@@ -287,7 +287,7 @@ aco_status aco_server_submit(aco_server* s, const aco_params* p, const int32_t* 
     sl.request_id = request_id;
     sl.cls = cls;
     sl.reported = false;
-    hipError_t e = aco::host::upload_and_init(sl.col, dist_host, L.base_end, s->init_stream);
+    hipError_t e = aco::host::upload_and_init(sl.col, dist_host, L.base_end, false, s->init_stream);
     if (e == hipSuccess) e = hipEventRecord(sl.ready, s->init_stream);
     if (e != hipSuccess) {
         pool_free(s, off, L.base_end);

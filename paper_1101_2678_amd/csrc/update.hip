@@ -529,19 +529,19 @@ hipError_t launch_update_atomic(const Colony& c, bool combine_in_lds, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_init(const Colony& c, hipStream_t s) {
-    const hipError_t e = launch_nn_tour(c, s);
+hipError_t launch_init(const Colony& c, bool alone, hipStream_t s) {
+    const hipError_t e = launch_nn_tour(c, alone, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_fill_init, cell_grid(c), dim3(256), 0, s, c);
     return hipGetLastError();
 }
 
-hipError_t launch_init_batch(const Colony* cols, int count, const uint32_t* rowmap,
-                             int total_rows, int max_n, hipStream_t s) {
+hipError_t launch_init_batch(const Colony* cols, const Colony* host_cols, int count,
+                             const uint32_t* rowmap, int total_rows, int max_n, hipStream_t s) {
     if (count <= 0 || total_rows <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_pad_dist_batch, dim3(total_rows), dim3(256), 0, s, cols, rowmap);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = launch_nn_tour_batch(cols, count, rowmap, total_rows, max_n, s);
+    if (e == hipSuccess) e = launch_nn_tour_batch(cols, host_cols, count, rowmap, total_rows, max_n, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_fill_init_batch, dim3(total_rows), dim3(256), 0, s, cols, rowmap);
     return hipGetLastError();

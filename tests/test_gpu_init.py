@@ -48,3 +48,21 @@ def test_batch():
     for q, d in enumerate(dists):
         ref = oracle.init(d, 4 + q, 1, 3, 0.25, 1)
         assert np.array_equal(bits(batch.tau(q)), bits(ref.tau))
+
+
+@pytest.mark.parametrize("layout", ["uniform", "cluster"])
+def test_served(layout):
+    """The server's initialisation walks the lists where they lie: nothing
+    staged in LDS beside the ticks of other requests."""
+    from paper_1101_2678_amd.serve import Request, Server, run_open_loop
+
+    reqs = [Request(rid=q, arrival=0.0, m=5 + q, iters=1, seed=q + 1,
+                    dist=tsp_inputs.instance(n, layout, side=5_000, seed=n)[1])
+            for q, n in enumerate([3, 33, 34, 300, 1025, 2350, 2400, 3100])]
+    server = Server(pool_bytes=1 << 30, max_slots=8)
+    run_open_loop(server, reqs, keep_tau=True)
+    server.close()
+    for r in reqs:
+        st = oracle.solve(r.dist, r.m, 1, 2, 0.5, r.seed, 1)
+        assert np.array_equal(bits(r.extra["tau"]), bits(st.tau)), r.n
+        assert r.best_len == st.best_len
