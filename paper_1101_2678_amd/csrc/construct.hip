@@ -722,6 +722,17 @@ __global__ __launch_bounds__(64) void k_test_select_masked(const float* rows, in
     __syncthreads();
     u32x4 wa[P], wb[P];
     load_passes<P>(rows + (size_t)q * ld, ((n + 3) & ~3) * 4, 0, ld * 4, lane, wa, wb);
+    // The factors mask by multiplication, which an infinity or a NaN passes.
+    // Choice rows hold neither; a row given here may, where it is not feasible.
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        uint32_t bits = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            bits |= s_f[512 * p + 8 * lane + e] != 0.0f ? 1u << e : 0u;
+        mask4<0>(wa[p], bits);
+        mask4<4>(wb[p], bits);
+    }
     const int j = pick_masked<P>(wa, wb, n, s_f, sh.T, sh.w, us[q], lane);
     if (lane == 0) out[q] = j;
 }

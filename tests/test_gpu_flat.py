@@ -30,6 +30,21 @@ def test_select(n):
     assert (got == oracle.r64_select_batch(rows, feas, u)).all()
 
 
+@pytest.mark.parametrize("n", [100, 320, 321, 513, 1025, 1537])
+def test_select_ignores_infeasible_weights(n):
+    """A city that may not be chosen counts for nothing, whatever its weight."""
+    import torch
+    from paper_1101_2678_amd import aco
+    from test_gpu_parity import _adversarial_rows
+
+    rng = np.random.default_rng(n)
+    rows, feas, u = _adversarial_rows(n, 300, rng)
+    dirty = np.where(feas != 0, rows, rng.choice(np.float32([np.inf, np.nan, 3e38]), rows.shape))
+    args = [torch.from_numpy(a).cuda() for a in (dirty.astype(np.float32), feas, u)]
+    got = aco.test_select(*args).cpu().numpy()
+    assert (got == oracle.r64_select_batch(np.where(feas != 0, rows, np.float32(0)), feas, u)).all()
+
+
 @pytest.mark.parametrize("n", [n for n in EDGES if n > 2])
 def test_parity(n):
     _, d = tsp_inputs.instance(n, "cluster" if n % 2 else "uniform", side=10_000, seed=n + 1)
