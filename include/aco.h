@@ -282,6 +282,13 @@ aco_status aco_test_select_shape(int32_t tile, int32_t waves, int32_t n, int32_t
                                  const float* rows_dev, const uint8_t* feasible_dev,
                                  const float* u_dev, int32_t* out_dev, void* hip_stream);
 
+/* As aco_test_select, through the code of the batched launch, whose rows of 257
+ * to 1536 cities at tile 8 have other layouts than the single-instance launch
+ * of up to a few thousand ants.  Asynchronous on hip_stream. */
+aco_status aco_test_select_batched(int32_t tile, int32_t n, int32_t count, const float* rows_dev,
+                                   const uint8_t* feasible_dev, const float* u_dev,
+                                   int32_t* out_dev, void* hip_stream);
+
 /* The product selection on `count` independent rows through the device code
  * aco_construct_product uses, with the draws given instead of generated.
  *   rows_dev      count rows of ld floats (device), ld = n rounded up to 64,

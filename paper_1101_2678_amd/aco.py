@@ -79,6 +79,7 @@ def _load():
         "aco_describe": (i32, [vp, c.c_char_p, sz]),
         "aco_test_select": (i32, [i32, i32, i32, vp, vp, vp, vp, vp]),
         "aco_test_select_shape": (i32, [i32, i32, i32, i32, vp, vp, vp, vp, vp]),
+        "aco_test_select_batched": (i32, [i32, i32, i32, vp, vp, vp, vp, vp]),
         "aco_set_tile": (i32, [i32, i32, i32]),
         "aco_set_shape": (i32, [i32, i32, i32, i32]),
         "aco_get_tile": (i32, [i32]),
@@ -298,9 +299,11 @@ class Colony:
             pass
 
 
-def test_select(rows, feasible, u, tile: int = 8, waves: int = 1, stream=None):
+def test_select(rows, feasible, u, tile: int = 8, waves: int = 1, stream=None,
+                batched: bool = False):
     """R64 roulette on independent rows through the construction kernel's code
-    of the given shape (tile cities per lane, waves wavefronts per ant).
+    of the given shape (tile cities per lane, waves wavefronts per ant), or with
+    `batched` the batched launch's of the given tile.
     rows: (count, n) float32 torch tensor on the GPU; feasible: (count, n)
     uint8; u: (count,) float32.  Returns a (count,) int32 tensor."""
     import torch
@@ -312,11 +315,13 @@ def test_select(rows, feasible, u, tile: int = 8, waves: int = 1, stream=None):
     feas = feasible.to(torch.uint8).contiguous()
     uu = u.to(torch.float32).contiguous()
     out = torch.empty(count, dtype=torch.int32, device=rows.device)
-    _check(lib.aco_test_select_shape(tile, waves, n, count, ctypes.c_void_p(padded.data_ptr()),
-                                     ctypes.c_void_p(feas.data_ptr()),
-                                     ctypes.c_void_p(uu.data_ptr()),
-                                     ctypes.c_void_p(out.data_ptr()), _stream_handle(stream)),
-           "aco_test_select_shape")
+    args = (n, count, ctypes.c_void_p(padded.data_ptr()), ctypes.c_void_p(feas.data_ptr()),
+            ctypes.c_void_p(uu.data_ptr()), ctypes.c_void_p(out.data_ptr()),
+            _stream_handle(stream))
+    if batched:
+        _check(lib.aco_test_select_batched(tile, *args), "aco_test_select_batched")
+    else:
+        _check(lib.aco_test_select_shape(tile, waves, *args), "aco_test_select_shape")
     return out
 
 

@@ -748,9 +748,9 @@ aco_status aco_describe(aco_ctx* c, char* buf, size_t len) {
     return ACO_OK;
 }
 
-aco_status aco_test_select_shape(int32_t tile, int32_t waves, int32_t n, int32_t count,
-                                 const float* rows_dev, const uint8_t* feasible_dev,
-                                 const float* u_dev, int32_t* out_dev, void* hip_stream) {
+static aco_status test_select(int32_t tile, int32_t waves, bool batched, int32_t n, int32_t count,
+                              const float* rows_dev, const uint8_t* feasible_dev,
+                              const float* u_dev, int32_t* out_dev, void* hip_stream) {
     if (n < 1 || n > aco::kMaxCities) return fail(ACO_ERR_INVALID, "n must be in [1, 4096]");
     if (!aco::host::shape_supported(tile, waves, n))
         return fail(ACO_ERR_INVALID, "construction shape not supported for this n");
@@ -761,12 +761,26 @@ aco_status aco_test_select_shape(int32_t tile, int32_t waves, int32_t n, int32_t
         return fail(ACO_ERR_INVALID, "rows must be 16-byte aligned");
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const hipError_t e =
-        waves == 1 ? aco::launch_test_select(tile, n, count, rows_dev, feasible_dev, u_dev,
-                                             out_dev, s)
+        waves == 1 ? aco::launch_test_select(tile, batched, n, count, rows_dev, feasible_dev,
+                                             u_dev, out_dev, s)
                    : aco::launch_test_select_split(tile, waves, n, count, rows_dev,
                                                    feasible_dev, u_dev, out_dev, s);
     if (e != hipSuccess) return device_fail(nullptr, e, "aco_test_select");
     return ACO_OK;
+}
+
+aco_status aco_test_select_shape(int32_t tile, int32_t waves, int32_t n, int32_t count,
+                                 const float* rows_dev, const uint8_t* feasible_dev,
+                                 const float* u_dev, int32_t* out_dev, void* hip_stream) {
+    return test_select(tile, waves, false, n, count, rows_dev, feasible_dev, u_dev, out_dev,
+                       hip_stream);
+}
+
+aco_status aco_test_select_batched(int32_t tile, int32_t n, int32_t count, const float* rows_dev,
+                                   const uint8_t* feasible_dev, const float* u_dev,
+                                   int32_t* out_dev, void* hip_stream) {
+    return test_select(tile, 1, true, n, count, rows_dev, feasible_dev, u_dev, out_dev,
+                       hip_stream);
 }
 
 aco_status aco_test_select(int32_t tile, int32_t n, int32_t count, const float* rows_dev,

@@ -94,7 +94,8 @@ hipError_t launch_pad_rows(const uint32_t* src, uint32_t* dst, int n, int ld, hi
 hipError_t launch_unpad_rows(const uint32_t* src, uint32_t* dst, int rows, int n, int ld,
                              hipStream_t s);
 hipError_t launch_refresh_choice(const Colony& c, hipStream_t s);
-hipError_t launch_test_select(int tile, int n, int count, const float* rows,
+// batched: through the code of the batched launch (and of launches of many ants).
+hipError_t launch_test_select(int tile, bool batched, int n, int count, const float* rows,
                               const uint8_t* feasible, const float* u, int32_t* out,
                               hipStream_t s);
 hipError_t launch_probe_copy(void* dst, const void* src, size_t bytes, hipStream_t s);

@@ -934,13 +934,13 @@ hipError_t launch_construct_batch(const Colony* cols, const uint32_t* antmap, in
     return hipGetLastError();
 }
 
-hipError_t launch_test_select(int tile, int n, int count, const float* rows,
+hipError_t launch_test_select(int tile, bool batched, int n, int count, const float* rows,
                               const uint8_t* feasible, const float* u, int32_t* out,
                               hipStream_t s) {
     if (count <= 0) return hipSuccess;
     if (!tile_supported(tile, n)) return hipErrorInvalidValue;
     const int ld = (n + 63) & ~63;
-    return dispatch_tile(tile, n, true, [&]<int G, int P>() {
+    return dispatch_tile(tile, n, !batched, [&]<int G, int P>() {
         hipLaunchKernelGGL((test_select_kernel<G, P>()), dim3(count), dim3(64), 0, s, rows, ld, n,
                            feasible, u, out);
         return hipGetLastError();

@@ -145,6 +145,15 @@ def test_probe_and_select_validation(aco):
     assert rows(16, 10, 4160, 4097, 1, 1, 16, None) == aco.ACO_ERR_INVALID
 
 
+def test_batched_select_validation(aco):
+    sel = aco.lib.aco_test_select_batched
+    for tile, n, count in [(8, 0, 1), (8, 4097, 1), (8, 10, -1), (4, 1025, 1), (6, 100, 1)]:
+        assert sel(tile, n, count, 16, 16, 16, 16, None) == aco.ACO_ERR_INVALID
+    assert sel(8, 10, 1, None, 16, 16, 16, None) == aco.ACO_ERR_INVALID
+    assert sel(8, 10, 1, 8, 16, 16, 16, None) == aco.ACO_ERR_INVALID  # rows not 16-byte aligned
+    assert sel(8, 10, 0, None, None, None, None, None) == aco.ACO_OK
+
+
 def test_tile_table(aco):
     aco.reset_tiles()
     # default: tile 4 up to n = 256, 8 above

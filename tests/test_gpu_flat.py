@@ -30,6 +30,48 @@ def test_select(n):
     assert (got == oracle.r64_select_batch(rows, feas, u)).all()
 
 
+BATCHED = [255, 257, 320, 321, 385, 511, 512, 513, 1000, 1023, 1024, 1025, 1500, 1535, 1536, 1537,
+           2400, 4096]
+
+
+@pytest.mark.parametrize("n,tile", [(n, 8) for n in BATCHED] + [(n, 4) for n in BATCHED if n <= 1024])
+def test_select_batched(n, tile):
+    """The same rows through the batched launch's code, which keeps the bits."""
+    import torch
+    from paper_1101_2678_amd import aco
+    from test_gpu_parity import _adversarial_rows
+
+    rows, feas, u = _adversarial_rows(n, 1500, np.random.default_rng(9000 + n))
+    feas[::97] = 0  # no feasible city
+    args = [torch.from_numpy(a).cuda() for a in (rows, feas, u)]
+    got = aco.test_select(*args, tile=tile, batched=True).cpu().numpy()
+    assert (got == oracle.r64_select_batch(rows, feas, u)).all()
+
+
+def test_select_batched_non_monotone_prefix():
+    """Rows with a block whose tree prefix exceeds a later one."""
+    import torch
+    from paper_1101_2678_amd import aco
+
+    rng = np.random.default_rng(78)
+    rows = []
+    while len(rows) < 200:
+        w = rng.random(64).astype(np.float32)
+        w[63] = 0
+        s = oracle.s64(w)
+        if (s[:63] > s[63]).any():
+            rows.append(np.concatenate([rng.random(64 * (5 + len(rows) % 19)).astype(np.float32),
+                                        w]))
+    for k in range(19):
+        part = np.array([r for r in rows if len(r) == 64 * (6 + k)])
+        feas = np.ones(part.shape, np.uint8)
+        u = np.full(len(part), 1.0 - 2.0**-24, np.float32)
+        args = [torch.from_numpy(a).cuda() for a in (part, feas, u)]
+        want = oracle.r64_select_batch(part, feas, u)
+        assert (aco.test_select(*args, batched=True).cpu().numpy() == want).all()
+        assert (aco.test_select(*args).cpu().numpy() == want).all()
+
+
 @pytest.mark.parametrize("n", [100, 320, 321, 513, 1025, 1537])
 def test_select_ignores_infeasible_weights(n):
     """A city that may not be chosen counts for nothing, whatever its weight."""
