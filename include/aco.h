@@ -401,13 +401,15 @@ typedef struct {
 aco_status aco_batch_set_config(aco_batch* b, const aco_batch_config* cfg);
 aco_status aco_batch_get_config(aco_batch* b, aco_batch_config* cfg);
 
-/* Autotuner of the batched launch: times the construction of the whole batch
- * (eager launches, HIP events on the batch's stream) with each of the `count`
- * candidate configurations (host array), `iters` times (at least twice), half
- * of them on the state at hand and half on the state before the last of the
- * iterations below; keeps the fastest configuration.  best_index (host, may be NULL)
- * receives its index, ms_per_iter (count floats, host, may be NULL) every
- * candidate's mean over the two states of the time per construction.
+/* Autotuner of the batched launch: times the `count` candidate configurations
+ * (host array) on the same states of the batch (eager launches, HIP events on
+ * the batch's stream): the construction of the whole batch `iters` times (at
+ * least twice) with each, half of them on the state at hand and half on the
+ * state before the last of the iterations below, and in both states the rest
+ * of an iteration, which does not depend on the configuration.  Keeps the
+ * fastest configuration.  best_index (host, may be NULL) receives its index,
+ * ms_per_iter (count floats, host, may be NULL) every candidate's time per
+ * iteration, the mean over the two states.
  * Advances every instance by count * (iters + 1) iterations, computed exactly
  * as any other iterations of the batch.  Synchronous. */
 aco_status aco_batch_autotune(aco_batch* b, const aco_batch_config* cands, int32_t count,

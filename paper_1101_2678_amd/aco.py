@@ -445,7 +445,7 @@ class Batch:
     def autotune(self, candidates, iters: int = 2):
         """candidates: (wg_per_cu, tile4_max_n) pairs.  Times each on this
         batch (advancing it, see aco_batch_autotune) and keeps the fastest;
-        returns (best index, ms per construction of every candidate)."""
+        returns (best index, ms per iteration of every candidate)."""
         arr = (BatchConfig * len(candidates))(*[BatchConfig(w, t) for w, t in candidates])
         best = ctypes.c_int32(-1)
         ms = np.zeros(len(candidates), np.float32)

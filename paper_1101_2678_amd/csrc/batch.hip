@@ -106,14 +106,19 @@ hipError_t enqueue_construction(aco_batch* b) {
         aco::batch_lds_bytes(b->max_n, b->config.wg_per_cu, b->lds_per_cu), b->stream);
 }
 
+// What follows a construction in an iteration: the best-so-far, the update.
+hipError_t enqueue_update(aco_batch* b) {
+    hipError_t e = aco::launch_best_batch(b->d_cols, b->count, b->stream);
+    if (e != hipSuccess) return e;
+    return aco::launch_update_gather_batch(b->d_cols, b->d_rowmap, b->total_rows, b->max_ld,
+                                           b->stream);
+}
+
 hipError_t enqueue_iterations(aco_batch* b, uint32_t iters) {
     hipError_t e = hipSuccess;
     for (uint32_t i = 0; i < iters && e == hipSuccess; ++i) {
         e = enqueue_construction(b);
-        if (e == hipSuccess) e = aco::launch_best_batch(b->d_cols, b->count, b->stream);
-        if (e == hipSuccess)
-            e = aco::launch_update_gather_batch(b->d_cols, b->d_rowmap, b->total_rows, b->max_ld,
-                                                b->stream);
+        if (e == hipSuccess) e = enqueue_update(b);
     }
     return e;
 }
@@ -415,12 +420,28 @@ aco_status aco_batch_autotune(aco_batch* b, const aco_batch_config* cands, int32
     // repeats the construction of the iteration at hand (its tours are not
     // used), half of them before and half after the iterations that the batch
     // advances by; the last of these comes at the end and leaves its tours.
+    // The rest of an iteration does not depend on the configuration; it is
+    // timed once in each state and counts for every candidate.
     const uint32_t reps[2] = {(iters + 1) / 2, iters > 1 ? iters / 2 : 1u};
     std::vector<float> ms(count, 0.0f);
+    float rest = 0.0f;
+    const auto timed = [&](auto&& work, float* t) {
+        hipError_t err = hipEventRecord(e0, b->stream);
+        if (err == hipSuccess) err = work();
+        if (err == hipSuccess) err = hipEventRecord(e1, b->stream);
+        if (err == hipSuccess) err = hipEventSynchronize(e1);
+        if (err == hipSuccess) err = hipEventElapsedTime(t, e0, e1);
+        return err;
+    };
+    // one iteration of the batch, its update timed
+    const auto advance_timed = [&] {
+        float t = 0.0f;
+        hipError_t err = enqueue_construction(b);
+        if (err == hipSuccess) err = timed([&] { return enqueue_update(b); }, &t);
+        rest += 0.5f * t;
+        return err;
+    };
     for (int half = 0; half < 2 && e == hipSuccess; ++half) {
-        if (half == 1)
-            for (int i = 0; i < count && e == hipSuccess; ++i)
-                e = enqueue_iterations(b, i < count - 1 ? iters + 1 : iters);
         for (int i = 0; i < count && e == hipSuccess; ++i) {
             if (aco_status s = aco_batch_set_config(b, &cands[i])) {
                 (void)hipEventDestroy(e0);
@@ -428,16 +449,25 @@ aco_status aco_batch_autotune(aco_batch* b, const aco_batch_config* cands, int32
                 return s;
             }
             if (i == 0) e = enqueue_construction(b);  // warm-up
-            if (e == hipSuccess) e = hipEventRecord(e0, b->stream);
-            for (uint32_t r = 0; r < reps[half] && e == hipSuccess; ++r) e = enqueue_construction(b);
-            if (e == hipSuccess) e = hipEventRecord(e1, b->stream);
-            if (e == hipSuccess) e = hipEventSynchronize(e1);
             float t = 0.0f;
-            if (e == hipSuccess) e = hipEventElapsedTime(&t, e0, e1);
+            if (e == hipSuccess)
+                e = timed(
+                    [&] {
+                        hipError_t err = hipSuccess;
+                        for (uint32_t r = 0; r < reps[half] && err == hipSuccess; ++r)
+                            err = enqueue_construction(b);
+                        return err;
+                    },
+                    &t);
             ms[i] += 0.5f * t / (float)reps[half];
         }
+        // count * (iters + 1) iterations in all, the first and the last timed
+        if (e == hipSuccess) e = advance_timed();
+        if (half == 0)
+            for (int i = 0; i < count && e == hipSuccess; ++i)
+                e = enqueue_iterations(b, i < count - 1 ? iters + 1 : iters - 1);
     }
-    if (e == hipSuccess) e = enqueue_iterations(b, 1);
+    for (float& t : ms) t += rest;
     const int best = (int)(std::min_element(ms.begin(), ms.end()) - ms.begin());
     if (ms_per_iter && e == hipSuccess) std::copy(ms.begin(), ms.end(), ms_per_iter);
     if (e0) (void)hipEventDestroy(e0);
