@@ -336,15 +336,18 @@ void aco_reset_tiles(void);
 /* Autotuner: for each of the `count` strictly increasing instance sizes
  * (3..4096), builds a synthetic uniform instance with m = n on d_workspace
  * (>= aco_workspace_bytes for the largest size with m = n, without the
- * atomic part), times `reps` constructions with every shape that supports
- * the size, and sets the shape table so that bucket i, sizes
- * (sizes[i-1], sizes[i]] (the last bucket up to 4096), uses the fastest;
- * sizes of the bucket that shape does not support get its tile with one
- * wavefront (tile 8 where tile 4 stops).
+ * atomic part), times `reps` constructions on a new colony and `reps` on the
+ * same colony after 16 iterations with every shape that supports the size
+ * (once where two shapes run the same kernel), and sets the shape table so that
+ * bucket i, sizes (sizes[i-1], sizes[i]] (the last bucket up to 4096), uses the
+ * fastest (tile 8 with one wavefront where none is faster); sizes of the bucket
+ * that shape does not support get its tile with one wavefront (tile 8 where tile
+ * 4 stops).
  *   chosen_tile, chosen_waves  count int32 each: the shape picked per size
  *   ms                         count * ACO_NUM_SHAPES floats, row i for
- *                              sizes[i]: ms per construction, -1 where the
- *                              shape does not support the size
+ *                              sizes[i]: ms per construction, the mean over
+ *                              the two states, -1 where the shape does not
+ *                              support the size
  * Each output may be NULL.  Synchronous; overwrites the workspace. */
 aco_status aco_autotune(void* d_workspace, size_t ws_bytes, const int32_t* sizes, int32_t count,
                         int32_t reps, void* hip_stream, int32_t* chosen_tile,

@@ -41,6 +41,8 @@ struct Colony {
 
 constexpr int kMaxCities = 4096;
 constexpr int kMinWideCities = 2560;  // longer rows have a wide list too (shortlist.hip)
+// Up to here one wavefront per ant runs the same kernel at either tile.
+constexpr int kMaxOneLayoutCities = 256;
 constexpr int kMaxTile4Cities = 1024;  // tile 4 holds 16 passes of 256 cities at most
 // Largest n aco_update_atomic_noalloc takes (its static deposit matrix holds
 // n * ld binary64 cells, ld = n rounded up to 64).

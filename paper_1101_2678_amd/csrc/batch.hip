@@ -501,40 +501,56 @@ aco_status aco_autotune(void* d_workspace, size_t ws_bytes, const int32_t* sizes
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
-    std::vector<int> best(count, 1);  // index into kShapes
+    // index into kShapes; tile 8 with one wavefront, which every size supports,
+    // where none is faster
+    std::vector<int> best(count, 1);
+    constexpr uint32_t kTuneIterations = 16;
     for (int i = 0; i < count && e == hipSuccess; ++i) {
         const int n = sizes[i];
         const aco_params p{n, n, 1, 2, 0.5f, 1};
         const aco::host::Layout L = aco::host::make_layout(p);
         const std::vector<int32_t> d = tuning_instance(n);
-        // construction only: the deposits' scale is not used, but is filled in
         std::string why;
         int dep_emin = 0;
         (void)aco::host::dist_valid(d.data(), n, n, &why, &dep_emin);
-        float t_best = 1e30f;
-        for (int k = 0; k < ACO_NUM_SHAPES; ++k) {
-            const int tile = kShapes[k][0], waves = kShapes[k][1];
-            if (ms) ms[(size_t)i * ACO_NUM_SHAPES + k] = -1.0f;
-            if (!aco::host::shape_supported(tile, waves, n)) continue;
-            const aco::Colony col =
-                aco::host::carve(static_cast<char*>(d_workspace), L, p, false, dep_emin, tile,
-                                 waves);
-            e = aco::host::upload_and_init(col, d.data(), L.base_end, true, s);
-            if (e == hipSuccess) e = aco::launch_construct(col, 0, s);  // warm-up
-            if (e == hipSuccess) e = hipEventRecord(e0, s);
-            for (int r = 0; r < reps && e == hipSuccess; ++r)
-                e = aco::launch_construct(col, (uint32_t)r + 1u, s);
-            if (e == hipSuccess) e = hipEventRecord(e1, s);
-            if (e == hipSuccess) e = hipEventSynchronize(e1);
-            float t = 0.0f;
-            if (e == hipSuccess) e = hipEventElapsedTime(&t, e0, e1);
-            if (e != hipSuccess) break;
-            t /= (float)reps;
-            if (ms) ms[(size_t)i * ACO_NUM_SHAPES + k] = t;
-            if (t < t_best) {
-                t_best = t;
-                best[i] = k;
+        const auto colony = [&](int tile, int waves) {
+            return aco::host::carve(static_cast<char*>(d_workspace), L, p, false, dep_emin, tile,
+                                    waves);
+        };
+        float t_shape[ACO_NUM_SHAPES] = {};
+        // Each shape on a new colony and on a converged one: what a solve of
+        // some length spends on either.  Only one wavefront at tile 8 has the
+        // short lists of a converged colony.
+        const aco::Colony plain = colony(8, 1);
+        e = aco::host::upload_and_init(plain, d.data(), L.base_end, true, s);
+        uint32_t iter = 0;
+        for (int state = 0; state < 2; ++state) {
+            for (int k = 0; k < ACO_NUM_SHAPES && e == hipSuccess; ++k) {
+                const int tile = kShapes[k][0], waves = kShapes[k][1];
+                if (!aco::host::shape_supported(tile, waves, n)) continue;
+                if (tile == 4 && waves == 1 && n <= aco::kMaxOneLayoutCities) continue;
+                const aco::Colony col = colony(tile, waves);
+                e = aco::launch_construct(col, iter, s);  // warm-up
+                if (e == hipSuccess) e = hipEventRecord(e0, s);
+                for (int r = 0; r < reps && e == hipSuccess; ++r)
+                    e = aco::launch_construct(col, iter + (uint32_t)r + 1u, s);
+                if (e == hipSuccess) e = hipEventRecord(e1, s);
+                if (e == hipSuccess) e = hipEventSynchronize(e1);
+                float t = 0.0f;
+                if (e == hipSuccess) e = hipEventElapsedTime(&t, e0, e1);
+                t_shape[k] += 0.5f * t / (float)reps;
             }
+            for (; state == 0 && iter < kTuneIterations && e == hipSuccess; ++iter) {
+                e = aco::launch_construct(plain, iter, s);
+                if (e == hipSuccess) e = aco::launch_update_gather(plain, s);
+            }
+        }
+        if (e != hipSuccess) break;
+        if (n <= aco::kMaxOneLayoutCities) t_shape[0] = t_shape[1];
+        for (int k = 0; k < ACO_NUM_SHAPES; ++k) {
+            const bool timed = aco::host::shape_supported(kShapes[k][0], kShapes[k][1], n);
+            if (ms) ms[(size_t)i * ACO_NUM_SHAPES + k] = timed ? t_shape[k] : -1.0f;
+            if (timed && t_shape[k] < t_shape[best[i]]) best[i] = k;
         }
     }
     if (e0) (void)hipEventDestroy(e0);

@@ -846,7 +846,7 @@ auto construct_kernel() {
 template <typename F>
 hipError_t dispatch_tile(int tile, int n, bool masked, F&& f) {
     static_assert(64 * kMaxFlatBlocks == kMaxFlatCities, "uses_lists");
-    if (n <= 64 * (masked && tile == 8 ? 4 : kMaxFlatBlocks)) return dispatch_flat(n, f);
+    if (n <= (masked && tile == 8 ? kMaxOneLayoutCities : kMaxFlatCities)) return dispatch_flat(n, f);
     if (tile == 4) {
         switch ((n + 255) / 256) {
             case 2: return f.template operator()<4, 2>();

@@ -311,3 +311,20 @@ def test_batch_configs_same_bits():
     assert e.value.status == aco.ACO_ERR_INVALID
     b.close()
     fresh.close()
+
+
+def test_autotune_where_shapes_share_a_kernel():
+    """Rows of up to 256 cities run one kernel at either tile: both columns hold
+    one time, and the bucket that runs on to longer rows keeps tile 8, which
+    alone uses the short lists there."""
+    from paper_1101_2678_amd import aco
+
+    try:
+        tiles, waves, ms = aco.autotune([200], reps=2)
+        assert (tiles[0], waves[0]) == (8, 1) and ms[0, 0] == ms[0, 1] > 0
+        assert all(aco.get_tile(n) == 8 and aco.get_waves(n) == 1 for n in (3, 200, 300, 1000, 4096))
+        # a size whose converged constructions tile 8 shortens by half
+        tiles, waves, _ = aco.autotune([1000], reps=2)
+        assert (tiles[0], waves[0]) == (8, 1)
+    finally:
+        aco.reset_tiles()
