@@ -167,7 +167,10 @@ __global__ __launch_bounds__(256) void k_cand_refresh(Colony c, NnTables t) {
 // the key 2^64 - 1 and are never taken because nn <= n - 1.  Three barriers
 // instead of two for each entry: n = 100 26 -> 7.5 us, n = 1000 42 -> 15,
 // n = 2400 84 -> 29 (nn = 32).
+// Lists of up to four entries take a minimum of the workgroup an entry, which is
+// shorter there (n = 1000, nn = 1 20 us a call against 28, n = 4096 33 against 55).
 constexpr int kListThreads = 256;
+constexpr int kMaxMinimumNn = 4;
 
 struct NnShared {
     uint64_t least[kListThreads];
@@ -196,6 +199,33 @@ __device__ __forceinline__ void nn_list_row(const Colony& c, const NnTables& t, 
                      : ~0ull;
         least = key[q] < least ? key[q] : least;
     }
+    uint16_t* out = t.nnl + (size_t)i * t.kp;
+    for (int r = nn + tid; r < t.kp; r += kListThreads) out[r] = 0;
+    if (nn <= kMaxMinimumNn) {
+        for (int r = 0; r < nn; ++r) {
+            uint64_t mn = least;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                const uint64_t o = __shfl_xor((unsigned long long)mn, off);
+                mn = o < mn ? o : mn;
+            }
+            // buffers by parity: one barrier an entry
+            uint64_t* part = sh.least + 4 * (r & 1);
+            if ((tid & 63) == 0) part[tid >> 6] = mn;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < kListThreads / 64; ++w) mn = part[w] < mn ? part[w] : mn;
+            if (tid == 0) out[r] = (uint16_t)(mn & 0xFFFFu);
+            if (least == mn) {
+                // this thread's smallest is taken: its next
+                least = ~0ull;
+#pragma unroll
+                for (int q = 0; q < kMaxCities / kListThreads; ++q)
+                    least = key[q] > mn && key[q] < least ? key[q] : least;
+            }
+        }
+        return;
+    }
     sh.least[tid] = least;
     if (tid == 0) sh.count = 0;
     __syncthreads();
@@ -207,13 +237,11 @@ __device__ __forceinline__ void nn_list_row(const Colony& c, const NnTables& t, 
         if (key[q] <= bound) sh.cand[atomicAdd(&sh.count, 1u)] = key[q];
     __syncthreads();
     const int count = (int)sh.count;
-    uint16_t* out = t.nnl + (size_t)i * t.kp;
     for (int q = tid; q < count; q += kListThreads) {
         const uint64_t k = sh.cand[q];
         const int r = keys_below(sh.cand, count, k);
         if (r < nn) out[r] = (uint16_t)(k & 0xFFFFu);
     }
-    for (int r = nn + tid; r < t.kp; r += kListThreads) out[r] = 0;
 }
 
 __global__ __launch_bounds__(kListThreads) void k_nn_lists(Colony c, NnTables t) {

@@ -66,3 +66,17 @@ def test_served(layout):
         st = oracle.solve(r.dist, r.m, 1, 2, 0.5, r.seed, 1)
         assert np.array_equal(bits(r.extra["tau"]), bits(st.tau)), r.n
         assert r.best_len == st.best_len
+
+
+@pytest.mark.parametrize("n", [6, 64, 257, 700, 4096])
+def test_lists_of_few_entries(n):
+    """On each side of the length up to which every entry is a minimum of the
+    workgroup."""
+    from paper_1101_2678_amd.aco import Colony
+
+    _, d = tsp_inputs.instance(n, "cluster", side=60 * n, seed=n)
+    col = Colony(d, 3, 1, 2, 0.5, 1, atomic=False)
+    for nn in (1, 2, 4, 5):
+        col.attach_nn(nn)
+        assert np.array_equal(col.nn_lists(), oracle.nn_lists(d, nn)), nn
+    col.close()
