@@ -478,7 +478,8 @@ aco_status aco_server_create(aco_server** out, void* d_pool, size_t pool_bytes, 
 /* Admission: a request for `iters` iterations of instance (p, dist_host) is
  * admitted if a slot is free, the running set stays within max_ants/max_rows
  * (else ACO_ERR_STATE) and the pool has a free block of
- * aco_workspace_bytes(p, 0) bytes (else ACO_ERR_NOMEM); nothing changes on a
+ * aco_workspace_bytes(p, 0) bytes (for n <= 256 a little less; else
+ * ACO_ERR_NOMEM); nothing changes on a
  * refusal.  On success *slot_out receives the slot; the distances are
  * uploaded and the colony initialised asynchronously, and the request joins
  * the running set at the first tick after that.  dist_host must stay valid

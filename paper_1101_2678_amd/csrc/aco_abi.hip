@@ -73,7 +73,7 @@ bool params_valid(const aco_params* p, std::string* why) {
     return true;
 }
 
-Layout make_layout(const aco_params& p) {
+Layout make_layout(const aco_params& p, bool served) {
     Layout L{};
     L.ld = (int32_t)round_up((size_t)p.n, 64);
     L.tp = (int32_t)round_up((size_t)p.n + 1, 64);
@@ -98,11 +98,12 @@ Layout make_layout(const aco_params& p) {
     L.cnn = take(sizeof(int64_t));
     L.tau0 = take(sizeof(float));
     L.iter = take(sizeof(uint32_t));
-    L.lists = take((size_t)p.n * kListLanes * sizeof(uint64_t));
+    const bool lists = !served || p.n > kMinListCities;
+    L.lists = take(lists ? (size_t)p.n * kListLanes * sizeof(uint64_t) : 0);
     // directly behind the lists: read_matrix uses both as one piece
     static_assert(kListLanes * sizeof(uint64_t) % kAlign == 0, "no gap before the wide lists");
     L.wide = take(p.n > kMinWideCities ? (size_t)p.n * kWideBytes : 0);
-    L.by_list = take((size_t)L.ld);
+    L.by_list = take(lists ? (size_t)L.ld : 0);
     L.base_end = off;
     L.delta = take(cells * sizeof(double));
     L.atomic_end = off;

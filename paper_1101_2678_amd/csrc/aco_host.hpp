@@ -35,7 +35,9 @@ bool params_valid(const aco_params* p, std::string* why);
 // Checks the distances; dep_emin (may be NULL) receives a lower bound on the
 // binary32 exponent field of every deposit fl32(1/C^k) the instance can have.
 bool dist_valid(const int32_t* d, int n, int m, std::string* why, int* dep_emin = nullptr);
-Layout make_layout(const aco_params& p);
+// served: a request of the server, whose roulette uses no short lists up to
+// kMinListCities cities and then has no room for them.
+Layout make_layout(const aco_params& p, bool served = false);
 Colony carve(char* base, const Layout& L, const aco_params& p, bool with_delta, int dep_emin,
              int tile, int waves = 1);
 // Clears the colony's base arrays, uploads the distances and enqueues the

@@ -3,7 +3,8 @@
 // A server owns a caller-provided device pool.  A request (an instance and a
 // number of iterations) is admitted when a slot is free and the pool has a
 // free block for the request's whole workspace (first fit; the footprint is
-// aco_workspace_bytes without the atomic part).  Its distances are uploaded
+// aco_workspace_bytes without the atomic part and without the short lists where
+// the roulette has none).  Its distances are uploaded
 // and its colony initialised on the server's admission stream; it joins the
 // running set of its size class at the first tick after that work has
 // finished.
@@ -275,7 +276,7 @@ aco_status aco_server_submit(aco_server* s, const aco_params* p, const int32_t* 
     if (free_slot < 0) return fail(ACO_ERR_STATE, "no free slot");
     if (class_ants + p->m > s->max_ants || class_rows + p->n > s->max_rows)
         return fail(ACO_ERR_STATE, "the size class would exceed max_ants or max_rows");
-    const aco::host::Layout L = aco::host::make_layout(*p);
+    const aco::host::Layout L = aco::host::make_layout(*p, true);
     size_t off = 0;
     if (!pool_alloc(s, L.base_end, &off)) return fail(ACO_ERR_NOMEM, "no free pool block large enough");
     Slot& sl = s->slots[free_slot];

@@ -179,3 +179,29 @@ def test_small_requests_not_paced_by_large():
         time.sleep(1e-4)
     assert order == [2, 1], order
     srv.close()
+
+
+def test_short_requests_need_no_room_for_lists():
+    """A request of up to 256 cities takes what its arrays need and no more: the
+    three matrices, the tours, the two neighbour tables and the small arrays."""
+    from paper_1101_2678_amd.aco import workspace_bytes
+    from paper_1101_2678_amd.serve import Request, Server
+
+    def up(x, a):
+        return (x + a - 1) // a * a
+
+    srv = Server(pool_bytes=64 << 20, max_slots=8)
+    for q, (n, m) in enumerate([(20, 20), (100, 90), (256, 256), (257, 100)]):
+        _, d = tsp_inputs.instance(n, "uniform", seed=n)
+        before = srv.stats()["free_bytes"]
+        slot = srv.submit(Request(rid=q, arrival=0.0, dist=d, m=m, iters=1, seed=1))
+        assert slot is not None
+        used = before - srv.stats()["free_bytes"]
+        ld, tp, mp = up(n, 64), up(n + 1, 64), up(m, 64)
+        arrays = [4 * n * ld] * 3 + [2 * m * tp, 2 * n * mp, 2 * n * mp, 8 * m, 4 * m, 8, 2 * tp, 8,
+                                     4, 4]
+        if n <= 256:
+            assert used == sum(up(x, 256) for x in arrays), n
+        else:
+            assert used == workspace_bytes(n, m, atomic=False), n
+    srv.close()
