@@ -255,7 +255,10 @@ const char* aco_status_str(aco_status s);
 /* Human-readable detail of the last failure on this thread ("" if none). */
 const char* aco_last_error(void);
 
-/* Kernel configuration chosen for a context, as "key=value" pairs. */
+/* Kernel configuration chosen for a context, as "key=value" pairs.  layout: how
+ * the roulette's whole-row step holds a row (flat: one city of every 64-city
+ * block a lane, whatever cities_per_lane says; factors, bits: cities_per_lane
+ * neighbours a lane and pass; split: the same over several wavefronts). */
 aco_status aco_describe(aco_ctx* c, char* buf, size_t len);
 
 /* ---- verification and measurement entry points ------------------------ */

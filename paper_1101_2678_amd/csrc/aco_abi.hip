@@ -743,9 +743,10 @@ aco_status aco_describe(aco_ctx* c, char* buf, size_t len) {
     std::snprintf(buf, len,
                   "construct=workgroup_per_ant waves_per_ant=%d cities_per_lane=%d passes=%d "
                   "blocks=%d ld=%d ants_per_cu=%d cus=%d lds_per_cu=%d "
-                  "update_gather_threads=256 atomic=%d nn=%d",
+                  "update_gather_threads=256 atomic=%d nn=%d layout=%s",
                   col.waves, col.tile, (col.n + pass - 1) / pass, (col.n + 63) / 64, col.ld,
-                  aco::construct_occupancy(col), cus, lds_cu, c->has_atomic ? 1 : 0, c->nn.nn);
+                  aco::construct_occupancy(col), cus, lds_cu, c->has_atomic ? 1 : 0, c->nn.nn,
+                  aco::construct_layout(col));
     return ACO_OK;
 }
 

@@ -76,6 +76,9 @@ hipError_t launch_best_batch(const Colony* cols, int count, hipStream_t s);
 // One workgroup per entry of rowmap: (colony << 16) | row.
 hipError_t launch_update_gather_batch(const Colony* cols, const uint32_t* rowmap, int total_rows,
                                       int max_ld, hipStream_t s);
+// The layout of a row that colony c's construction runs: "flat" (construct_flat.hpp),
+// "factors" (construct_masked.hpp), "bits" (construct.hip) or "split".
+const char* construct_layout(const Colony& c);
 // Construction workgroups (ants) resident per compute unit, or -1.
 int construct_occupancy(const Colony& c);
 hipError_t launch_update_gather(const Colony& c, hipStream_t s);

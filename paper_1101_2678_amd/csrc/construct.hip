@@ -885,6 +885,16 @@ bool tile_supported(int tile, int n) {
     return false;
 }
 
+const char* construct_layout(const Colony& c) {
+    if (c.waves > 1) return "split";
+    const char* name = "none";
+    (void)dispatch_tile(c.tile, c.n, masked_rows(c.n, c.m), [&]<int G, int P>() {
+        name = G == 0 ? "flat" : G == 1 ? "factors" : "bits";
+        return hipSuccess;
+    });
+    return name;
+}
+
 int construct_occupancy(const Colony& c) {
     if (c.waves > 1) return construct_split_occupancy(c);
     int blocks = -1;

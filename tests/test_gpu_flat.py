@@ -142,3 +142,21 @@ def test_whole_rows_on_each_side_of_the_memory_bound(n, m):
         tour, length = oracle.construct_ant(ref.choice, d, 7, 2, int(k))
         assert np.array_equal(tours[k], tour) and lens[k] == length, k
     col.close()
+
+
+@pytest.mark.parametrize("n,m,tile,layout", [
+    (100, 10, 4, "flat"), (256, 10, 8, "flat"), (257, 10, 8, "factors"), (320, 10, 4, "flat"),
+    (321, 10, 4, "bits"), (512, 65535, 8, "factors"), (1000, 3072, 8, "factors"),
+    (1000, 3073, 8, "bits"), (1536, 2048, 8, "factors"), (1536, 2049, 8, "bits"),
+    (1537, 10, 8, "bits")])
+def test_described_layout(n, m, tile, layout):
+    from paper_1101_2678_amd import aco
+
+    aco.set_tile(n, n, tile)
+    try:
+        col = aco.Colony(tsp_inputs.instance(n, "uniform", seed=n)[1], m, 1, 2, 0.5, 1,
+                         atomic=False)
+        assert f"layout={layout}" in col.describe().split()
+        col.close()
+    finally:
+        aco.reset_tiles()
