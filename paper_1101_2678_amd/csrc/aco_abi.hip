@@ -272,27 +272,32 @@ hipError_t read_rows(void* dst, size_t row_bytes, const void* src, size_t pitch,
     return hipSuccess;
 }
 
-// Large matrices lose their padding on the device and come down in pieces that
-// need no repacking.  The pieces go through the memory of the short lists,
-// which nothing reads between calls: every construction that selects from
-// lists writes them first, in the same call and so in the same capture.
-// (Nothing else of the workspace is free to hold them: the neighbour tables,
-// for one, may belong to an update that a graph replays later.)  By rows / in
-// pieces: n = 1000 0.35 / 0.38 ms, 1500 0.73 / 0.66, 2400 1.9 / 1.7, 4095 8.2 /
-// 6.5; below 8 MB the launches cost more than the host's repacking.
-hipError_t read_matrix(const Colony& c, const float* src, float* dst, hipStream_t stream) {
-    const size_t row_bytes = (size_t)c.n * sizeof(float);
-    if (c.ld == c.n || c.n * row_bytes < kPackedReadBytes)
+// Large matrices lose their padding on the device.  Where the neighbour tables
+// are free they hold the packed matrix (4 n mp bytes side by side, rewritten whole
+// by the next construction), which comes down in one copy.  Elsewhere it comes
+// in pieces through the memory of the short lists, which nothing reads between
+// calls: every construction that selects from lists writes them first, in the
+// same call and so in the same capture.  By rows / in pieces / whole: n = 1000
+// 0.35 / 0.38 / 0.24 ms, 1500 0.73 / 0.66 / 0.53, 2400 1.9 / 1.7 / 1.3, 4095 8.2 /
+// 6.5 / 6.5; smaller matrices come down by rows, where the launches and waits cost
+// more than the host's repacking.
+hipError_t read_matrix(const Colony& c, const float* src, float* dst, bool tables_free,
+                       hipStream_t stream) {
+    const size_t row_bytes = (size_t)c.n * sizeof(float), bytes = c.n * row_bytes;
+    const bool whole = tables_free && c.mp >= c.n && bytes >= kPackedReadBytes;
+    if (c.ld == c.n || (!whole && bytes < kPiecedReadBytes))
         return read_rows(dst, row_bytes, src, (size_t)c.ld * sizeof(float), (size_t)c.n);
-    const size_t scratch = (size_t)c.n * (kListLanes * sizeof(uint64_t) + (c.wide ? kWideBytes : 0));
-    const int piece = (int)(scratch / row_bytes);
+    uint32_t* const scratch =
+        whole ? reinterpret_cast<uint32_t*>(c.succ) : reinterpret_cast<uint32_t*>(c.lists);
+    const size_t list_bytes = kListLanes * sizeof(uint64_t) + (c.wide ? kWideBytes : 0);
+    const int piece = whole ? c.n : (int)(c.n * list_bytes / row_bytes);
     hipError_t e = hipSuccess;
     for (int r = 0; r < c.n && e == hipSuccess; r += piece) {
         const int rows = std::min(piece, c.n - r);
-        e = launch_unpad_rows(reinterpret_cast<const uint32_t*>(src) + (size_t)r * c.ld,
-                              reinterpret_cast<uint32_t*>(c.lists), rows, c.n, c.ld, stream);
+        e = launch_unpad_rows(reinterpret_cast<const uint32_t*>(src) + (size_t)r * c.ld, scratch,
+                              rows, c.n, c.ld, stream);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(dst + (size_t)r * c.n, c.lists, rows * row_bytes,
+            e = hipMemcpyAsync(dst + (size_t)r * c.n, scratch, rows * row_bytes,
                                hipMemcpyDeviceToHost, stream);
     }
     const hipError_t done = hipStreamSynchronize(stream);
@@ -402,6 +407,16 @@ aco_status usable(aco_ctx* c) {
     return ACO_OK;
 }
 
+// Before a construction or an update is enqueued: remembers whether it is
+// captured instead of run.  A stream whose state cannot be told counts as one
+// that is.
+void note_capture(aco_ctx* c) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(c->stream, &status);
+    if (e != hipSuccess) (void)hipGetLastError();  // not the next launch's error
+    if (e != hipSuccess || status != hipStreamCaptureStatusNone) c->captured = true;
+}
+
 aco_status sync_ctx(aco_ctx* c, const char* where) {
     const hipError_t e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return device_fail(c, e, where);
@@ -420,6 +435,7 @@ aco_status update_ready(aco_ctx* c) {
 }
 
 aco_status enqueue_update(aco_ctx* c, aco_update_kind kind, double* delta) {
+    ::note_capture(c);
     // the update kernels also keep the best-so-far tour
     hipError_t e;
     if (kind == ACO_UPDATE_GATHER) {
@@ -528,6 +544,7 @@ void aco_reset_tiles(void) { aco::host::reset_tiles(); }
 
 aco_status aco_construct(aco_ctx* c, uint32_t iter) {
     if (aco_status s = usable(c)) return s;
+    note_capture(c);
     const hipError_t e = aco::launch_construct(c->col, iter, c->stream);
     if (e != hipSuccess) return device_fail(c, e, "aco_construct");
     c->pending = true;
@@ -566,6 +583,7 @@ aco_status aco_solve(aco_ctx* c, uint32_t iters, aco_update_kind kind, uint16_t*
 
 aco_status aco_construct_product(aco_ctx* c, uint32_t iter) {
     if (aco_status s = usable(c)) return s;
+    note_capture(c);
     const hipError_t e = aco::launch_construct_product(c->col, iter, c->stream);
     if (e != hipSuccess) return device_fail(c, e, "aco_construct_product");
     c->pending = true;
@@ -616,6 +634,7 @@ aco_status aco_nn_attach(aco_ctx* c, int32_t nn, void* d_nn_workspace, size_t by
 aco_status aco_construct_nn(aco_ctx* c, uint32_t iter) {
     if (aco_status s = usable(c)) return s;
     if (c->nn.nn == 0) return fail(ACO_ERR_STATE, "aco_construct_nn needs aco_nn_attach first");
+    note_capture(c);
     const hipError_t e = aco::launch_construct_nn(c->col, c->nn, iter, c->stream);
     if (e != hipSuccess) return device_fail(c, e, "aco_construct_nn");
     c->pending = true;
@@ -673,7 +692,7 @@ static aco_status read_matrix(aco_ctx* c, const float* src, float* host, const c
     if (!host) return fail(ACO_ERR_INVALID, "host pointer is NULL");
     if (aco_status s = sync_ctx(c, where)) return s;
     const aco::Colony& col = c->col;
-    const hipError_t e = aco::host::read_matrix(col, src, host, c->stream);
+    const hipError_t e = aco::host::read_matrix(col, src, host, !c->pending && !c->captured, c->stream);
     if (e != hipSuccess) return device_fail(c, e, where);
     return ACO_OK;
 }

@@ -18,6 +18,10 @@ struct aco_ctx {
     uint32_t pending_iter;  // iteration of the construction awaiting update
     bool pending;           // a construction has not been followed by an update
     bool poisoned;
+    // A construction or an update was enqueued while its stream was being
+    // captured: a graph may run it at any later time, so `pending` no longer
+    // says when the neighbour tables are in use.
+    bool captured;
     bool has_atomic;
     void* scratch;          // this device's address of the static deposit matrix, or null
     hipError_t scratch_err; // why it is null

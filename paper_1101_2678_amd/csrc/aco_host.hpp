@@ -48,11 +48,15 @@ hipError_t upload_and_init(const Colony& col, const int32_t* dist_host, size_t b
 // `rows` rows of row_bytes bytes, `pitch` bytes apart on the device, to dst
 // (host, contiguous).  Blocking.
 hipError_t read_rows(void* dst, size_t row_bytes, const void* src, size_t pitch, size_t rows);
-// The n x n matrix `src` (tau or choice) of colony c to dst (host).  Work before
-// it on `stream` must have finished.  Of the workspace it writes the short
-// lists only.  Blocking.
-constexpr size_t kPackedReadBytes = 8u << 20;  // smaller matrices come down by read_rows
-hipError_t read_matrix(const Colony& c, const float* src, float* dst, hipStream_t stream);
+// The n x n matrix `src` (tau or choice) of colony c to dst (host).  tables_free:
+// no update that is queued, or that a graph may replay, reads the neighbour
+// tables of a construction before this call; the matrix may then be packed
+// there.  Otherwise it writes, of the workspace, the short lists at most.  Work
+// before it on `stream` must have finished.  Blocking.
+constexpr size_t kPackedReadBytes = 1u << 20;  // smaller matrices come down by read_rows
+constexpr size_t kPiecedReadBytes = 8u << 20;  // the same where the tables are not free
+hipError_t read_matrix(const Colony& c, const float* src, float* dst, bool tables_free,
+                       hipStream_t stream);
 // Best-so-far tour (n + 1 cities) and length; either pointer may be null.
 hipError_t read_best(const Colony& col, uint16_t* tour_host, int64_t* len_host);
 // Compute units and LDS bytes per compute unit of the current device.

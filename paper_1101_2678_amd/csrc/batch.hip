@@ -344,7 +344,8 @@ aco_status aco_batch_read_tau(aco_batch* b, int32_t q, float* tau_host) {
     const aco::Colony* c;
     if (aco_status s = batch_instance(b, q, &c)) return s;
     if (!tau_host) return fail(ACO_ERR_INVALID, "tau_host is NULL");
-    const hipError_t e = aco::host::read_matrix(*c, c->tau, tau_host, b->stream);
+    // every construction of a batch is followed by its update, in a capture too
+    const hipError_t e = aco::host::read_matrix(*c, c->tau, tau_host, true, b->stream);
     if (e != hipSuccess) return batch_device_fail(b, e, "aco_batch_read_tau");
     return ACO_OK;
 }

@@ -1,5 +1,6 @@
-"""Matrices read back in packed pieces (large) and by rows (small): the read
-changes nothing that a later call sees, replays of captured calls among them."""
+"""Matrices read back through the neighbour tables (large, no construction
+pending and none captured), in pieces, and by rows: the read changes nothing that
+a later call sees, replays of captured calls among them."""
 from __future__ import annotations
 
 import numpy as np
@@ -100,6 +101,7 @@ def test_read_between_capture_and_replay(kind, n, m):
         assert_same_f32(col.tau(), ref.tau, f"tau {what}")
         assert_same_f32(col.choice(), ref.choice, f"choice {what}")
 
+    check("before any capture")
     col.construct(0)
     captured_update = capture(update)
     captured_construct = capture(lambda: col.construct(1))
