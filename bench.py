@@ -19,10 +19,35 @@ HBM and 160 MB streaming probes, the same steps with candidate-list
 construction (`nn_list`) and with the product-and-argmax rule (`product`),
 the oracle timed on a bounded sample on the host (`cpu_baseline`), and under
 `configs` every other workload: n = 100, n = 1000 (uniform and 20-cluster),
-256 uneven instances as one graph-replayed batch against one instance per
-launch (`batch256`, solves/s), and a Poisson trace through the
+256 uneven instances solved as one batch against one instance per launch, both
+from new colonies (`batch256`, solves/s), and a Poisson trace through the
 continuous-batching server against one request at a time (`served`, solves/s
 with p50 and p99).
+
+What the fields of the line mean is said here, once:
+  * `roofline.peak` of a construction is the better of two reads of the choice
+    matrix's own footprint, measured live: a streaming read, every XCD walking
+    all of it, the best of PROBE_SHAPES, and random whole rows with 1, 2, 4 and
+    8 times the kernel's wavefronts and one or two rows in flight each, where
+    each XCD's L2 keeps a share of the rows as it does for the kernel.
+  * `roofline.achieved` counts the whole n-city row (4n bytes) of every ant-step.
+    A step that its row's short list settles reads 512 bytes instead, so `frac`
+    can pass 1 as a colony converges.  `requested_bytes` is what the same tours
+    would ask for with a row read at every step, without the 4-city groups that
+    are all visited; the bytes past the L2 are in `traffic`, where recorded.
+  * An update kernel's peak is one copy launch over its own footprint.
+  * The product rule's peak is the Philox rate of aco_probe_philox; its achieved
+    rate counts the draws of every city, of which a step that the short list
+    settles computes 63.
+  * `latency_floor`: one construction step is a chain of dependent operations;
+    with 256 ants no two wavefronts share a SIMD, so their time a step is the
+    chain's own latency, and `frac` is that over the time a step of all ants.
+  * `launch_autotune`: ms per iteration by tile4_max_n (-1: the tile table, 0: all
+    tile 8) and wg_per_cu (0: no cap).  `shapes`: ms per construction, -1 where a
+    shape does not support the size.
+  * A whole-job rate (`batch256`, `served`) counts the choice-row bytes of every
+    construction over the wall time of the job; the matrices lie in the caches,
+    so it can pass the HBM figure.
 
 `--workload NAME` runs one of them alone.  Profiled runs add
 `--sync-launches`.  The library runs on one GPU: `--gpus` other than 1 exits
@@ -108,7 +133,6 @@ def job_roofline(con_bytes: float, seconds: float, solves: int) -> dict:
     achieved = con_bytes / seconds / 1e9
     return {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": None,
-            "scope": "whole job: construction bytes of every solve / wall time",
             "algorithmic_bytes": int(con_bytes),
             "hbm_bound_solves_per_s": round(solves / (con_bytes / (HBM_PEAK_GBPS * 1e9)), 3)}
 
@@ -213,10 +237,10 @@ def cpu_baseline(d: np.ndarray, m: int, seconds: float):
         "sample": (f"{k} ants of iteration 0 at n={n} ({k * (n - 1)} ant-steps) built by "
                    f"{threads} threads in {t_construct:.1f} s, plus one full update with m={m} "
                    f"tours ({t_update:.2f} s, one thread); step time extrapolated to m={m} ants"),
-        "construct_ant_steps_per_s": (n - 1) / per_ant,
-        "update_s": t_update,
-        "step_s_extrapolated": step_s,
-        "one_core_construct_ant_steps_per_s": solo * (n - 1) / t_solo,
+        "construct_ant_steps_per_s": round((n - 1) / per_ant, 1),
+        "update_s": round(t_update, 4),
+        "step_s_extrapolated": round(step_s, 4),
+        "one_core_construct_ant_steps_per_s": round(solo * (n - 1) / t_solo, 1),
         "one_core_sample": f"{solo} ants of iteration 0 built one after another in {t_solo:.1f} s",
         "cpu_model": host_cpu_model(),
     }
@@ -367,14 +391,15 @@ def requested_bytes(tours: np.ndarray, n: int, skip: bool) -> int:
     return 16 * total
 
 
-def construct_kernel(n: int, tile: int) -> str:
-    """The construction kernel a single-instance launch of n cities runs."""
-    if n <= 320:
+def construct_kernel(n: int, tile: int, layout: str) -> str:
+    """The construction kernel of a single-instance launch of n cities, from the
+    tile and the layout that aco_describe gives."""
+    if layout == "flat":
         return f"k_construct_flat<{(n + 63) // 64}>"
     passes = (n + 64 * tile - 1) // (64 * tile)
-    if tile == 8 and passes <= 3:
+    if layout == "factors":
         return f"k_construct_masked<{passes}>"
-    return f"k_construct<{tile},{passes}>"
+    return f"k_construct{'_split' if layout == 'split' else ''}<{tile},{passes}>"
 
 
 SYNC_LAUNCHES = False
@@ -562,11 +587,6 @@ def bench_product(torch, aco, d, m: int, steps: int, warmup: int, update: str, c
         "roofline": {"bound": "alu", "achieved": round(blocks / (t_con * 1e-3), 1),
                      "peak": ceiling[0], "unit": "Philox4x32-10 blocks/s",
                      "frac": round(blocks / (t_con * 1e-3) / ceiling[0], 4),
-                     "peak_note": "measured: aco_probe_philox, the same Philox formulation with "
-                                  "no loads or selection, 16 wavefronts per SIMD",
-                     "frac_note": "achieved counts the draws of every city at every step; a step "
-                                  "that the row's short list settles computes those of its 63 "
-                                  "entries only, so the fraction can pass 1",
                      "ceiling_at_m_wavefronts": ceiling[1],
                      "kernel": "k_construct_product"},
     }
@@ -590,9 +610,11 @@ def bench_product(torch, aco, d, m: int, steps: int, warmup: int, update: str, c
 
 def bench_batch(args, torch, aco):
     """256 independent instances, n = round(exp(U(ln 50, ln 1000))), m = n,
-    uniform cities, alpha 1, beta 2, rho 0.5, 25 iterations each, tiles from
-    the autotuner; the batch (one graph replay of 25 iterations x 3 launches)
-    against the same set run one instance per launch on one stream."""
+    uniform cities, alpha 1, beta 2, rho 0.5, solved by 25 iterations each from
+    new colonies: as one batch in the tuned configuration (one HIP graph of all
+    launches, its capture timed too), and one instance per launch on one stream.
+    The tuning runs on a batch of its own.  `next_25_ms` is one replay of the
+    same graph, the iterations after the solve."""
     count, iters = 256, 25
     sizes = tsp_inputs.log_uniform_sizes(count, 50, 1000, seed=4)
     dists = [tsp_inputs.instance(int(n), "uniform", side=1_000_000, seed=q + 1)[1]
@@ -606,36 +628,49 @@ def bench_batch(args, torch, aco):
     stream = torch.cuda.Stream()
     b = aco.Batch(dists, params, stream=stream)
     default_cfg = b.config
-    # the batched launch's own autotuner: workgroups per CU x tile policy,
-    # timed on this batch (each candidate advances it by 3 iterations)
-    cands = [(w, t) for t in (-1, 0, 1024) for w in (0, 8, 12, 16, 20, 24, 32)]
+    # the batched launch's own autotuner: workgroups per CU x tile policy
+    policies, caps = (-1, 0, 1024), (0, 8, 12, 16, 20, 24, 32)
+    cands = [(w, t) for t in policies for w in caps]
     best, cand_ms = b.autotune(cands, iters=2)
-    log(f"bench batch: launch autotune chose {cands[best]} ({cand_ms[best]:.3f} ms/construction; "
+    log(f"bench batch: launch autotune chose {cands[best]} ({cand_ms[best]:.3f} ms/iteration; "
         f"default {default_cfg})")
-    b.run(iters, graph=True)  # captures the graph and runs 25 iterations
+    b.run(2, graph=True)  # the first graph of the process
     b.sync()
+    b.close()
+    b = aco.Batch(dists, params, stream=stream)
+    b.set_config(*cands[best])
+    torch.cuda.synchronize()
     t0 = time.perf_counter()
-    b.run(iters, graph=True)  # replays it: iterations 25..49
+    b.run(iters, graph=True)
     b.sync()
     t_batch = time.perf_counter() - t0
     # bytes of a construction that reads a row at every step (4-city groups
     # once all are visited left out), from each instance's last tours
     req_iter = sum(requested_bytes(b.tours(q)[0], int(n), skip=True)
                    for q, n in enumerate(sizes))
+    t0 = time.perf_counter()
+    b.run(iters, graph=True)
+    b.sync()
+    t_next = time.perf_counter() - t0
+    b.close()
     choice_footprint = sum(int(n) * ((int(n) + 63) // 64 * 64) * 4 for n in sizes)
-    cols = [aco.Colony(d, p["m"], ALPHA, BETA, RHO, p["seed"], atomic=False, stream=stream)
-            for d, p in zip(dists, params)]
-    for c in cols:
-        for it in range(2):
-            c.construct(it)
-            c.update("gather")
+
+    def colonies(count):
+        return [aco.Colony(d, p["m"], ALPHA, BETA, RHO, p["seed"], atomic=False, stream=stream)
+                for d, p in zip(dists[:count], params)]
+
+    def solve(cols):
+        for c in cols:
+            for it in range(iters):
+                c.construct(it)
+                c.update("gather")
+        torch.cuda.synchronize()
+
+    solve(colonies(8))  # warm-up
+    cols = colonies(count)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
-    for c in cols:
-        for it in range(2, 2 + iters):
-            c.construct(it)
-            c.update("gather")
-    torch.cuda.synchronize()
+    solve(cols)
     t_single = time.perf_counter() - t0
     ant_steps = int(sum(int(n) * (int(n) - 1) for n in sizes)) * iters
     rec = {
@@ -644,7 +679,7 @@ def bench_batch(args, torch, aco):
         "unit": "solves/s",
         "n_gpus": 1,
         "steps": 1,
-        "warmup": 1,
+        "warmup": 0,
         "ms_per_step": round(t_batch * 1e3, 3),
         "higher_is_better": True,
         "scaling": "weak",
@@ -653,42 +688,28 @@ def bench_batch(args, torch, aco):
         "data": "synthetic",
         "config": {"workload": f"{count} independent instances, n log-uniform in [50, 1000] "
                                f"(sum n = {int(sizes.sum())}), m = n, uniform cities, alpha 1, "
-                               f"beta 2, rho 0.5, {iters} iterations each, gather update, "
-                               "one HIP graph replay",
+                               f"beta 2, rho 0.5, {iters} iterations each from new colonies, "
+                               "gather update, one HIP graph",
                    "count": count, "iterations": iters},
         "one_instance_per_launch": {"seconds": round(t_single, 4),
                                     "solves_per_s": round(count / t_single, 2)},
         "speedup_vs_one_per_launch": round(t_single / t_batch, 2),
+        "next_25_ms": round(t_next * 1e3, 3),
         "ant_steps_per_s": round(ant_steps / t_batch, 1),
         "shapes": {"sizes": tune_sizes, "tile": tiles.tolist(), "waves": waves.tolist(),
-                   "ms_per_construction": {f"tile{t}_waves{w}": [round(float(x), 4) for x in col]
-                                           for (t, w), col in zip(aco.SHAPES, shape_ms.T)},
-                   "note": "single-instance construction shape per size (m = n) from the "
-                           "autotuner, used by the one-instance-per-launch comparison; the "
-                           "batched launch takes only the tile; -1 = shape does not support "
-                           "the size"},
+                   "ms": {f"tile{t}_waves{w}": [round(float(x), 4) for x in col]
+                          for (t, w), col in zip(aco.SHAPES, shape_ms.T)}},
         "launch_autotune": {
-            "candidates": [{"wg_per_cu": w, "tile4_max_n": t, "ms_per_construction": round(float(x), 4)}
-                           for (w, t), x in zip(cands, cand_ms)],
+            "wg_per_cu": list(caps),
+            "ms_by_tile4_max_n": {str(t): [round(float(x), 3) for x in row]
+                                  for t, row in zip(policies, np.reshape(cand_ms, (3, -1)))},
             "chosen": {"wg_per_cu": cands[best][0], "tile4_max_n": cands[best][1]},
-            "default": default_cfg,
-            "note": "wg_per_cu: construction workgroups per CU allowed by the LDS request (0 = "
-                    "no cap); tile4_max_n: instances up to this n use 4 cities per lane (-1 = "
-                    "the tile table above, 0 = all 8)"},
+            "default": default_cfg},
         "roofline": job_roofline(
             float(sum(construct_bytes(int(n), int(n)) for n in sizes)) * iters, t_batch, count),
     }
-    rf = rec["roofline"]
-    rf["requested_bytes"] = int(req_iter) * iters
-    rf["choice_footprint_bytes"] = choice_footprint
-    rf["frac_note"] = (
-        f"achieved counts every ant-step's whole choice row; steps that read it ask for "
-        f"{req_iter * iters / rf['algorithmic_bytes']:.3f} of those bytes (4-city groups are "
-        f"skipped once all are visited; from each instance's last tours), steps that the row's "
-        f"short list settles for 512 bytes, and the construction reads only the choice "
-        f"matrices, {choice_footprint / 1e6:.0f} MB together, which the Infinity Cache holds "
-        f"and of which the small instances' sit in L2, so the whole-job rate can pass the HBM "
-        f"figure")
+    rec["roofline"]["requested_bytes"] = int(req_iter) * iters
+    rec["roofline"]["choice_footprint_bytes"] = choice_footprint
     aco.reset_tiles()
     return rec
 
@@ -725,6 +746,13 @@ def bench_served(args, torch, aco):
                      for a, b in zip(reqs, plain_reqs))
     mismatched += sum(int(a.best_len != b.best_len or not np.array_equal(a.best_tour, b.best_tour))
                       for a, b in zip(fifo_reqs, plain_reqs))
+
+    def summary(run: dict, *tables) -> dict:
+        out = {k: round(v, 4) if isinstance(v, float) else v for k, v in run.items()
+               if not isinstance(v, dict)}
+        out.update({k: run[k] for k in tables})
+        return out
+
     rec = {
         "metric": "served solves/s and p99 latency (50 AS iterations per request)",
         "value": round(batched["solves_per_s"], 3),
@@ -745,15 +773,13 @@ def bench_served(args, torch, aco):
                    "pool_bytes": pool},
         "latency_p50_s": round(batched["latency_p50_s"], 4),
         "latency_p99_s": round(batched["latency_p99_s"], 4),
-        "admission": "size-aware: requests waiting under 10 s offered smallest solve first, "
-                     "older ones first in arrival order",
-        "batched": batched,
-        "batched_fifo_admission": fifo,
-        "plain_one_request_at_a_time": plain,
+        "admission": "size-aware",
+        "batched": summary(batched, "by_size"),
+        "batched_fifo_admission": summary(fifo),
+        "plain_one_request_at_a_time": summary(plain),
         "results_differing_from_plain": mismatched,
         "footprint_bytes_total": int(sum(footprint)),
         "footprint_formula_12n2_2mn_total": int(sum(formula)),
-        "offered_load_note": "offered load exceeds device capacity; latency grows with trace length",
         "roofline": job_roofline(float(sum(construct_bytes(r.n, r.m) * r.iters for r in reqs)),
                                  batched["makespan_s"], len(reqs)),
     }
@@ -787,12 +813,7 @@ def latency_floor(torch, aco, d, n: int, m: int, m_iso: int) -> dict:
         col.close()
         ns.append(e0.elapsed_time(e1) / 5 * 1e6 / (n - 1))
     return {"ns_per_step_isolated": round(ns[1], 1), "ants_isolated": m_iso,
-            "ns_per_step": round(ns[0], 1), "frac": round(ns[1] / ns[0], 4),
-            "note": (f"one construction step is a chain of dependent operations (list load, "
-                     f"flag read, scan, pick); with {m_iso} ants no two wavefronts share a "
-                     f"SIMD, so their per-step time is the chain's own latency, the bound "
-                     f"of this latency-bound size; frac = that over the per-step time of "
-                     f"{m} ants, both from the state after 20 iterations")}
+            "ns_per_step": round(ns[0], 1), "frac": round(ns[1] / ns[0], 4)}
 
 
 def run_single(args, torch, aco, name: str, steps: int, warmup: int, main: bool) -> dict:
@@ -837,7 +858,8 @@ def run_single(args, torch, aco, name: str, steps: int, warmup: int, main: bool)
     t_upd = np.array([ev[3 * s + 1].elapsed_time(ev[3 * s + 2]) for s in range(K)])
     log(f"bench: {name}: timed {K} steps in {wall:.3f} s")
     tours, _ = col.tours()
-    tile = int(col.describe().split("cities_per_lane=")[1].split()[0])
+    described = dict(kv.split("=") for kv in col.describe().split())
+    tile, layout = int(described["cities_per_lane"]), described["layout"]
 
     # the other update variants, timed after the timed region on the same state
     t_other = {}
@@ -875,35 +897,16 @@ def run_single(args, torch, aco, name: str, steps: int, warmup: int, main: bool)
     peak = max(ceil["GBps"], rows_ceil["GBps"])
     roofline = {"bound": "mall" if foot > (4 << 20) else "l2", "achieved": round(achieved, 1),
                 "peak": peak, "unit": "GB/s", "frac": round(achieved / peak, 4),
-                "traffic": None, "kernel": construct_kernel(n, tile),
+                "traffic": None, "kernel": construct_kernel(n, tile, layout),
                 "algorithmic_bytes_per_launch": alg,
-                "peak_note": (f"measured at the choice matrix's {foot / 1e6:.1f} MB footprint, "
-                              f"the better of two reads of it: a streaming read, every XCD "
-                              f"walking all of it, best of {len(PROBE_SHAPES)} load shapes "
-                              f"(aco_probe_read_shape: {ceil['GBps']} GB/s with "
-                              f"{ceil['loads_in_flight']} loads in flight"
-                              f"{', nontemporal' if ceil['nontemporal'] else ''}, "
-                              f"{ceil['reps']} passes, {ceil['ms']} ms), and random whole rows "
-                              f"with 1, 2, 4 and 8 times the kernel's {m} wavefronts and one or "
-                              f"two rows in flight each (aco_probe_rows_shape: "
-                              f"{rows_ceil['GBps']} GB/s with wavefronts x rows in flight = "
-                              f"{rows_ceil['shape']}), where each XCD's L2 keeps a share of the "
-                              f"rows as it does for the kernel"),
                 "peak_stream_GBps": ceil["GBps"],
-                "peak_by_shape_GBps": ceil["by_shape_GBps"],
                 "peak_random_rows_GBps": rows_ceil["GBps"],
-                "peak_random_rows_by_shape_GBps": rows_ceil["by_shape_GBps"],
                 "hbm_peak": HBM_PEAK_GBPS, "frac_of_hbm_peak": round(achieved / HBM_PEAK_GBPS, 4),
                 "requested_bytes_per_launch": req}
-    if n > 256:
-        roofline["frac_note"] = (
-            f"achieved counts the whole {n}-city row per ant-step (4n bytes); a step that its "
-            f"row's short list settles reads 512 bytes instead, the more steps the further the "
-            f"colony has converged, so frac can pass 1.  requested_bytes_per_launch is what the "
-            f"same tours would ask for with a row read at every step ({req / alg:.3f} of the "
-            f"algorithmic bytes); the counter bytes past L2 are in traffic, where recorded")
     if main:
         traffic, traffic_note = traffic_from_profile()
+        roofline["peak_by_shape_GBps"] = ceil["by_shape_GBps"]
+        roofline["peak_random_rows_by_shape_GBps"] = rows_ceil["by_shape_GBps"]
         roofline["traffic"] = traffic
         roofline["traffic_note"] = traffic_note
         if traffic:
@@ -955,9 +958,6 @@ def run_single(args, torch, aco, name: str, steps: int, warmup: int, main: bool)
                 "bound": "mall" if b < (256 << 20) else "hbm", "achieved": upd[kind]["GBps"],
                 "peak": cc["GBps"], "unit": "GB/s",
                 "frac": round(upd[kind]["GBps"] / cc["GBps"], 4),
-                "peak_note": (f"measured: one aco_probe_copy launch over {b / 1e6:.1f} MB (half "
-                              f"read, half written), mean of 20 launches, "
-                              f"{cc['ms_per_launch']} ms each"),
                 "hbm_peak": HBM_PEAK_GBPS,
                 "frac_of_hbm_peak": round(upd[kind]["GBps"] / HBM_PEAK_GBPS, 4)}
     return rec, d
@@ -1072,10 +1072,14 @@ def run_configs(args, torch, aco) -> dict:
     for name in ("n100", "n1000u", "n1000c"):
         configs[name], _ = run_single(args, torch, aco, name, args.steps, args.warmup,
                                       main=False)
+        del configs[name]["metric"]  # the line's own
     log("bench: batch256")
     configs["batch256"] = bench_batch(args, torch, aco)
     log("bench: served")
     configs["served"] = bench_served(args, torch, aco)
+    for rec in configs.values():
+        for key in ("n_gpus", "scaling", "vs_baseline", "dtype", "data", "higher_is_better"):
+            del rec[key]  # the same in every record of the line
     return configs
 
 
