@@ -323,12 +323,12 @@ hipError_t read_best(const Colony& col, uint16_t* tour_host, int64_t* len_host) 
 
 // Construction shape per instance size: the tile (cities per lane) and the
 // wavefronts per ant.  Default: 4 cities per lane up to n = 256, 8 above,
-// one wavefront per ant.  Up to n = 320 both tiles run the same kernel; above
+// one wavefront per ant.  Up to n = 256 both tiles run the same kernel; above
 // (single-instance construction with m = n on MI355X, a new colony) tile 8
 // with one wavefront takes 0.188 ms at n = 512 against 0.201 at tile 4, 0.50
 // against 0.59 at n = 1024, and two or four wavefronts 14-34% longer; a
-// converged colony gains more, since only tile 8 with one wavefront uses the
-// short lists.  The table is filled once, on
+// converged colony gains more, since above n = 320 only tile 8 with one
+// wavefront uses the short lists.  The table is filled once, on
 // first use, by a function-local static (thread-safe initialisation);
 // changing it while other threads read it is not supported.
 namespace {

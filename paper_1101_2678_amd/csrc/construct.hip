@@ -146,7 +146,8 @@ constexpr bool kWriteAllPasses = (P * Tile<G>::kPass <= 1024);
 
 // Two passes: both passes' masks and lane sums before either's sums across
 // lanes (left to itself, the compiler finishes one pass and waits for its
-// cross-lane read before the next: n = 1000 560 against 520 us).
+// cross-lane read before the next: n = 1000 with 4096 ants 0.945 against 0.924
+// ms; no difference in batches).
 template <int P>
 constexpr bool kTogether = P == 2;
 
@@ -175,9 +176,10 @@ __device__ __forceinline__ int pick_loaded(u32x4 (&wa)[P], u32x4 (&wb)[P], int n
     // Block totals to lane b (0 past the row's blocks).  Rows of two or more
     // passes fetch them with one cross-lane read per pass from the last lane
     // of each group (and rows staged whole store their weights afterwards):
-    // against a masked LDS store per pass and a load, n = 1000 4%, n = 1500
-    // 4.5%, n = 2400 0.8% faster.  Rows of one pass keep the store and load
-    // (cross-lane reads measured 6% slower at n = 512).
+    // against a masked LDS store per pass and a load, n = 2400 0.8% faster, and
+    // batched one instance of 700 cities 0.395 against 0.434 ms, of 1000 0.591
+    // against 0.620, of 1500 1.46 against 1.50.  Rows of one pass keep the
+    // store and load (cross-lane reads measured 6% slower at n = 512).
     constexpr bool kPermute = P >= 2;
     const int nb = (n + 63) >> 6;
     float T = 0.0f;
@@ -456,7 +458,11 @@ __device__ __forceinline__ void construct_ant_masked(const Colony& c, int k, uin
     s_T[lane] = 0.0f;
     int cur;
     if (starts_from_lists(c, lane)) {
-        // as in construct_ant
+        // As in construct_ant; the factors serve both kinds of step.  m = n,
+        // with the lists' launch against whole rows with the bits, in the
+        // 20th iteration: n = 500 0.136 / 0.197 ms, n = 1000 0.285 / 0.508, n =
+        // 1500 0.496 / 1.31; mean of the first 24: 0.157 / 0.198, 0.363 /
+        // 0.519, 0.791 / 1.32.
         const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
         cur = walk<false>(n, key, iter, k, s_tour, lane, [&](int at, float u, int i) {
             const u32x2 entry = load_list(lists, at, lane);
@@ -541,10 +547,8 @@ __device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t i
         // the list does not settle the selection.  The usual step keeps the
         // flags only; the general step's bits are made from them.  m = n,
         // construction with the lists' launch against whole rows only, in
-        // the 20th iteration: n = 500 0.136 / 0.197 ms, n = 1000 0.285 /
-        // 0.508, n = 1500 0.496 / 1.31, n = 2400 1.10 / 6.05, n = 3000 1.68 /
-        // 13.3; mean of the first 24: 0.157 / 0.198, 0.363 / 0.519, 0.791 /
-        // 1.32, 2.61 / 6.05, 5.10 / 13.2.
+        // the 20th iteration: n = 2400 1.10 / 6.05 ms, n = 3000 1.68 / 13.3;
+        // mean of the first 24: 2.61 / 6.05, 5.10 / 13.2.
         const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
         constexpr int kUsed = kWriteAllPasses<G, P> ? 64 * G * P : kStaged<G, P>;
         uint8_t* s_seen = clear_flags(
@@ -763,10 +767,9 @@ __global__ __launch_bounds__(64) void k_test_select_flat(const float* rows, int 
 // covered.  The cap is part of a batch's launch configuration, chosen by the
 // batch autotuner; the default (used by the server) caps at 16 per CU, the
 // best on a 256-instance batch (n 50..1000; mean of a new and a converged
-// state 9.28 ms, 20 to 32 and no cap 9.30 to 9.34, 12 9.49, 8 11.0; where
-// whole rows are read alone, 18 and 20 were 0.7% slower, 24 2.5%, no cap
-// 8.7%), and only
-// launches of at least kCapRounds rounds at the cap: one that fits the
+// state 9.28 ms an iteration, 20 to 32 and no cap 9.29 to 9.33, 12 9.65, 8 11.2;
+// where whole rows are read alone, 18 and 20 were 0.7% slower, 24 2.5%, no
+// cap 8.7%), and only launches of at least kCapRounds rounds at the cap: one that fits the
 // device in a round or two would only gain a tail.
 constexpr int kBatchWgPerCu = 16;
 constexpr int kCapRounds = 8;

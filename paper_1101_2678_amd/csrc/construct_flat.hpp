@@ -17,7 +17,9 @@ namespace {
 // Rows of up to 64 times this many cities.  One construction with m = n,
 // tiled / flat: n = 64 0.0261 / 0.0180 ms, n = 100 0.0391 / 0.0276, n = 128
 // 0.0484 / 0.0335, n = 192 0.0710 / 0.0548, n = 256 0.0927 / 0.0817, n = 320
-// 0.137 / 0.123; n = 384 0.155 / 0.169 (every block costs six adds more).
+// 0.137 / 0.123; n = 384 0.155 / 0.169 (every block costs six adds more).  With
+// the factors (construct_masked.hpp) n = 320 takes 0.119, so the fifth block is
+// for tile 4 and the batched launch, which has none.
 constexpr int kMaxFlatBlocks = 5;
 
 // x of the lanes whose bit of `mask` (wave-uniform) is set, else +0.

@@ -1,5 +1,6 @@
 // construct_masked.hpp -- the roulette step for rows of one to three passes of
-// 512 cities: the tiled layout with the visited set as factors in LDS.
+// 512 cities: the tiled layout with the visited set as factors in LDS, for
+// launches whose ants fit the device in one round (masked_rows).
 //
 // The step of such a row is bound by the instructions of its one wavefront,
 // and half of them made masks: two for every city.  Here the ant keeps a
