@@ -67,9 +67,10 @@ hipError_t launch_test_select_split(int tile, int waves, int n, int count, const
 // batch_lds_bytes) holds the tour and sets how many workgroups fit a CU.
 hipError_t launch_construct_batch(const Colony* cols, const uint32_t* antmap, int total_ants,
                                   int max_n, size_t lds, hipStream_t s);
-// Dynamic LDS per batched construction workgroup for at most wg_per_cu
-// workgroups on a CU of lds_per_cu bytes (wg_per_cu 0: no cap, the tour only).
-size_t batch_lds_bytes(int max_n, int wg_per_cu, size_t lds_per_cu);
+// Dynamic LDS per batched construction workgroup of a launch of total_ants ants,
+// for at most wg_per_cu workgroups on a CU of lds_per_cu bytes (wg_per_cu 0: no
+// cap, what the ants need only).
+size_t batch_lds_bytes(int max_n, int total_ants, int wg_per_cu, size_t lds_per_cu);
 // The cap a batch of total_ants ants on `cus` compute units gets by default.
 int batch_default_cap(int total_ants, int cus);
 hipError_t launch_best_batch(const Colony* cols, int count, hipStream_t s);

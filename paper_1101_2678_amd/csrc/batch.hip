@@ -103,7 +103,7 @@ hipError_t enqueue_construction(aco_batch* b) {
     if (e != hipSuccess) return e;
     return aco::launch_construct_batch(
         b->d_cols, b->d_antmap, b->total_ants, b->max_n,
-        aco::batch_lds_bytes(b->max_n, b->config.wg_per_cu, b->lds_per_cu), b->stream);
+        aco::batch_lds_bytes(b->max_n, b->total_ants, b->config.wg_per_cu, b->lds_per_cu), b->stream);
 }
 
 // What follows a construction in an iteration: the best-so-far, the update.
@@ -370,7 +370,7 @@ aco_status aco_batch_set_config(aco_batch* b, const aco_batch_config* cfg) {
     if (!cfg) return fail(ACO_ERR_INVALID, "config is NULL");
     if (cfg->wg_per_cu < 0 || cfg->wg_per_cu > 64)
         return fail(ACO_ERR_INVALID, "wg_per_cu must be in [0, 64]");
-    if (aco::batch_lds_bytes(b->max_n, cfg->wg_per_cu, b->lds_per_cu) > b->max_lds_per_wg)
+    if (aco::batch_lds_bytes(b->max_n, b->total_ants, cfg->wg_per_cu, b->lds_per_cu) > b->max_lds_per_wg)
         return fail(ACO_ERR_INVALID, "wg_per_cu asks for more LDS than one workgroup may hold");
     if (cfg->tile4_max_n < -1 || cfg->tile4_max_n > aco::kMaxTile4Cities)
         return fail(ACO_ERR_INVALID, "tile4_max_n must be in [-1, 1024]");
@@ -409,7 +409,7 @@ aco_status aco_batch_autotune(aco_batch* b, const aco_batch_config* cands, int32
     if (iters < 1) return fail(ACO_ERR_INVALID, "iters must be >= 1");
     for (int i = 0; i < count; ++i) {
         if (cands[i].wg_per_cu < 0 || cands[i].wg_per_cu > 64 ||
-            aco::batch_lds_bytes(b->max_n, cands[i].wg_per_cu, b->lds_per_cu) > b->max_lds_per_wg ||
+            aco::batch_lds_bytes(b->max_n, b->total_ants, cands[i].wg_per_cu, b->lds_per_cu) > b->max_lds_per_wg ||
             cands[i].tile4_max_n < -1 || cands[i].tile4_max_n > aco::kMaxTile4Cities)
             return fail(ACO_ERR_INVALID, "candidate " + std::to_string(i) + " is out of range");
     }

@@ -137,12 +137,17 @@ __device__ __forceinline__ void load_row(const float* __restrict__ mat, int reco
     }
 }
 
-// Rows of at most 1024 cities: after masking, every pass's weights go to LDS
-// (s_w, city c at s_w[c]), so a candidate block is read back with one load
-// and nothing is staged on the way to the selection.  Longer rows keep the
-// masked weights in registers and stage only the pass of a candidate block.
-template <int G, int P>
-constexpr bool kWriteAllPasses = (P * Tile<G>::kPass <= 1024);
+// Whole rows in LDS: after masking, every pass's weights go to s_w (city c at
+// s_w[c]), so that a candidate block is read back with one load and nothing is
+// staged on the way to the selection.  Otherwise the masked weights stay in
+// registers and only a candidate block is staged.  Rows of one pass are stored
+// whole everywhere, rows of up to 1024 cities with ALL: where the launch is
+// bound by latency.  The 4 KB an ant that ALL takes leave room for fewer ants on a
+// compute unit where there are many.  All / block, whole rows: one batched
+// instance of 1000 cities 0.59 / 0.63 ms, four of 600 0.52 / 0.54, eight of 700 1.47 /
+// 1.23, 10 of 600 1.14 / 1.03; n = 1000 with 8192 ants 1.96 / 1.70.
+template <int G, int P, bool ALL>
+constexpr bool kWriteAllPasses = (P * Tile<G>::kPass <= (ALL ? 1024 : 512));
 
 // Two passes: both passes' masks and lane sums before either's sums across
 // lanes (left to itself, the compiler finishes one pass and waits for its
@@ -167,12 +172,12 @@ __device__ __forceinline__ float to_blocks(float t, int p, float T, int lane) {
 // Wave-uniform.  The workgroup is one wavefront: its LDS operations execute
 // in program order, and every LDS access below uses a lane-dependent index,
 // so the compiler keeps the order.
-template <int G, int P, typename B>
+template <int G, int P, bool ALL, typename B>
 __device__ __forceinline__ int pick_loaded(u32x4 (&wa)[P], u32x4 (&wb)[P], int n, B lane_bits,
                                            uint64_t block_bits, float* s_T, float* s_w, float u,
                                            int lane) {
     constexpr int LPB = Tile<G>::kLanesPerBlock;
-    constexpr bool kAll = kWriteAllPasses<G, P>;
+    constexpr bool kAll = kWriteAllPasses<G, P, ALL>;
     // Block totals to lane b (0 past the row's blocks).  Rows of two or more
     // passes fetch them with one cross-lane read per pass from the last lane
     // of each group (and rows staged whole store their weights afterwards):
@@ -230,7 +235,7 @@ __device__ __forceinline__ int pick_loaded(u32x4 (&wa)[P], u32x4 (&wb)[P], int n
     // block-total scan, which stage B leaves as it is; rows of at most 2^L
     // blocks need only its first L levels.
     float I;
-    if constexpr (kAll)
+    if constexpr (P * G <= 16)
         I = s64_scan_row0_levels<block_scan_levels(P * G)>(T);
     else
         I = s64_scan(T);
@@ -270,28 +275,28 @@ __device__ __forceinline__ int pick_loaded(u32x4 (&wa)[P], u32x4 (&wb)[P], int n
     return pick_fallback(block_bits);
 }
 
-template <int G, int P, bool SKIP, typename B>
+template <int G, int P, bool SKIP, bool ALL, typename B>
 __device__ __forceinline__ int r64_pick(const float* __restrict__ mat, int records, int row,
                                         int row_bytes, int n, B lane_bits, uint64_t block_bits,
                                         float* s_T, float* s_w, float u, int lane) {
     u32x4 wa[P], wb[P];
     load_row<G, P, SKIP>(mat, records, row, row_bytes, lane_bits, lane, wa, wb);
-    return pick_loaded<G, P>(wa, wb, n, lane_bits, block_bits, s_T, s_w, u, lane);
+    return pick_loaded<G, P, ALL>(wa, wb, n, lane_bits, block_bits, s_T, s_w, u, lane);
 }
 
 // LDS a construction workgroup needs besides the tour and the visited flags.
 template <int W>
 struct AntShared {
-    float w[W];   // masked weights of rows up to 1024 cities, else a staged block
+    float w[W];   // masked weights of whole rows, or a staged block
     float T[64];  // block totals in block order
 };
 
-// Staging of a kernel for rows of P passes: for long rows a block, and the 64 P
-// bytes that bits_from_flags uses, so that 14 ants of 3500 cities fit a compute
-// unit and m = n = 3500 runs in one round (with a whole pass staged two rounds,
-// 22.1 against 20.6 ms on whole rows).
-template <int G, int P>
-constexpr int kStaged = kWriteAllPasses<G, P> ? 1024 : 128;
+// Words that a kernel for rows of P passes stages: whole rows, or a block and the
+// 64 P bytes that bits_from_flags uses (with a whole pass staged, an ant of 3500
+// cities took an LDS granule more, and m = n = 3500 two rounds: 22.1 against 20.6
+// ms on whole rows).
+template <int G, int P, bool ALL>
+constexpr int kStaged = kWriteAllPasses<G, P, ALL> ? P * Tile<G>::kPass : 128;
 static_assert(64 * (kMaxCities / 512) <= 128 * sizeof(float), "bits_from_flags' scratch");
 
 // Tiles whose colonies use the short lists (uses_lists).
@@ -305,27 +310,39 @@ constexpr bool kWideLists = 64 * G * (P - 1) >= kMinWideCities;
 // Dynamic LDS of an ant: the tour, then the flags.
 __host__ __device__ size_t ant_lds_bytes(int n) { return tour_lds_bytes(n) + seen_lds_bytes(n); }
 
-// Whether the flags of P passes lie in AntShared<W>::w behind what the kernel
-// for P passes stages there: in the batched launch, whose W serves rows that
-// stage two whole passes, and rows of one and of three to seven passes then ask
-// for no more LDS than their tour (n = 2400: 16 ants a compute unit against 12).
-template <int G, int P, int W>
-constexpr bool kFlagsInStaging =
-    W * sizeof(float) >=
-    (kWriteAllPasses<G, P> ? 64 * G * P : kStaged<G, P>) * sizeof(float) + 512 * P;
+// Staging of the batched launch's kernel, which serves rows of any length.
+template <bool ALL>
+constexpr int kBatchStaged = ALL ? 1024 : 512;
+
+// Whether the flags of P passes lie in AntShared<W>::w behind what the ant stages
+// there: in the batched launch, where short and long rows share W, so that
+// rows of several lengths ask for no more LDS than their tour (n = 2400: 16 ants a
+// compute unit against 12).
+template <int G, int P, bool ALL, int W>
+constexpr bool kFlagsInStaging = W * sizeof(float) >=
+                                 kStaged<G, P, ALL> * sizeof(float) + 512 * P;
 
 // Dynamic LDS of an ant of n cities in the batched launch.
+template <bool ALL>
 size_t batch_ant_lds_bytes(int n) {
-    const int passes = (n + 511) / 512;
-    const bool flags = n <= 64 * kMaxFlatBlocks ? n > kMinListCities : passes == 2 || passes == 8;
+    constexpr int W = kBatchStaged<ALL>;
+    const bool behind[] = {kFlagsInStaging<8, 1, ALL, W>, kFlagsInStaging<8, 2, ALL, W>,
+                           kFlagsInStaging<8, 3, ALL, W>, kFlagsInStaging<8, 4, ALL, W>,
+                           kFlagsInStaging<8, 5, ALL, W>, kFlagsInStaging<8, 6, ALL, W>,
+                           kFlagsInStaging<8, 7, ALL, W>, kFlagsInStaging<8, 8, ALL, W>};
+    const bool flags =
+        n <= 64 * kMaxFlatBlocks ? n > kMinListCities : !behind[(n + 511) / 512 - 1];
     return tour_lds_bytes(n) + (flags ? seen_lds_bytes(n) : 0);
 }
 
-// The same for any ant of up to max_n cities: the largest of each kind.
+// The same for any ant of up to max_n cities: the largest of each layout and
+// pass count.
+template <bool ALL>
 size_t batch_ants_lds_bytes(int max_n) {
-    size_t most = 0;
-    for (int n : {64 * kMaxFlatBlocks, 1024, kMaxCities}) {
-        const size_t need = batch_ant_lds_bytes(n < max_n ? n : max_n);
+    size_t most = batch_ant_lds_bytes<ALL>(max_n < 64 * kMaxFlatBlocks ? max_n
+                                                                       : 64 * kMaxFlatBlocks);
+    for (int n = 512; n < max_n + 512; n += 512) {
+        const size_t need = batch_ant_lds_bytes<ALL>(n < max_n ? n : max_n);
         most = need > most ? need : most;
     }
     return most;
@@ -516,7 +533,7 @@ __device__ __forceinline__ bool memory_bound(const Colony& c) { return c.m * c.n
 
 // The whole tour of ant k of colony c in iteration `iter`: placement, n - 1
 // roulette steps, then length, deposit, tour and neighbour tables.
-template <int G, int P, bool SKIP, bool LOAD_FIRST, bool LIST, int W>
+template <int G, int P, bool SKIP, bool LOAD_FIRST, bool LIST, bool ALL, int W>
 __device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t iter,
                                               uint16_t* s_tour, AntShared<W>& sh) {
     const int lane = threadIdx.x;
@@ -550,9 +567,8 @@ __device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t i
         // the 20th iteration: n = 2400 1.10 / 6.05 ms, n = 3000 1.68 / 13.3;
         // mean of the first 24: 2.61 / 6.05, 5.10 / 13.2.
         const __amdgpu_buffer_rsrc_t lists = list_rsrc(c);
-        constexpr int kUsed = kWriteAllPasses<G, P> ? 64 * G * P : kStaged<G, P>;
         uint8_t* s_seen = clear_flags(
-            kFlagsInStaging<G, P, W> ? reinterpret_cast<uint8_t*>(sh.w + kUsed)
+            kFlagsInStaging<G, P, ALL, W> ? reinterpret_cast<uint8_t*>(sh.w + kStaged<G, P, ALL>)
                                      : reinterpret_cast<uint8_t*>(s_tour) + tour_lds_bytes(n),
             n, 512 * P, lane);
         cur = walk<false>(n, key, iter, k, s_tour, lane, [&](int at, float u, int i) {
@@ -572,7 +588,7 @@ __device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t i
             }
             bits_from_flags<P>(reinterpret_cast<const uint2*>(s_seen),
                                reinterpret_cast<uint8_t*>(sh.w), lane, lane_bits, block_bits);
-            const int j = r64_pick<G, P, SKIP>(c.choice, records, at, row_bytes, n, lane_bits,
+            const int j = r64_pick<G, P, SKIP, ALL>(c.choice, records, at, row_bytes, n, lane_bits,
                                                block_bits, sh.T, sh.w, u, lane);
             return j < 0 ? 0 : j;
         });
@@ -587,8 +603,8 @@ __device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t i
                 if (!LOAD_FIRST)
                     load_row<G, P, SKIP, FEW>(c.choice, records, at, row_bytes, lane_bits, lane,
                                               wa, wb);
-                const int j = pick_loaded<G, P>(wa, wb, n, lane_bits, block_bits, sh.T, sh.w, u,
-                                                lane);
+                const int j = pick_loaded<G, P, ALL>(wa, wb, n, lane_bits, block_bits, sh.T, sh.w,
+                                                     u, lane);
                 // At every step at least one city is unvisited, so j >= 0; the
                 // clamp only keeps the LDS indices in range should that ever
                 // break.
@@ -603,11 +619,13 @@ __device__ __forceinline__ void construct_ant(const Colony& c, int k, uint32_t i
     finish_ant(c, k, cur, s_tour, lane);
 }
 
+// Tile 8 with up to three passes comes here with many ants only (masked_rows).
 template <int G, int P>
 __global__ __launch_bounds__(64) void k_construct(Colony c, uint32_t iter) {
     extern __shared__ __align__(16) uint16_t s_tour[];
-    __shared__ __align__(16) AntShared<kStaged<G, P>> sh;
-    construct_ant<G, P, (P >= 3), (P < 4), kUseLists<G>>(c, ant_of_block(blockIdx.x, c.m), iter,
+    constexpr bool kAll = G == 4;
+    __shared__ __align__(16) AntShared<kStaged<G, P, kAll>> sh;
+    construct_ant<G, P, (P >= 3), (P < 4), kUseLists<G>, kAll>(c, ant_of_block(blockIdx.x, c.m), iter,
                                                          s_tour, sh);
 }
 
@@ -634,16 +652,16 @@ constexpr bool kBatchLoadFirst = NP < 4;
 // instance runs a loop specialised for its row length, with no per-pass
 // test of the pass count inside the step (256 instances, n 50..1000: 757 ->
 // 762 solves/s against one loop with run-time pass tests).
-template <int G, int NP, int PMAX>
+template <int G, int NP, int PMAX, bool ALL, int W>
 __device__ __forceinline__ void batch_ant(const Colony& c, int k, uint32_t iter, int np,
-                                          uint16_t* s_tour, AntShared<1024>& sh) {
+                                          uint16_t* s_tour, AntShared<W>& sh) {
     if constexpr (NP < PMAX) {
         if (np != NP) {
-            batch_ant<G, NP + 1, PMAX>(c, k, iter, np, s_tour, sh);
+            batch_ant<G, NP + 1, PMAX, ALL>(c, k, iter, np, s_tour, sh);
             return;
         }
     }
-    construct_ant<G, NP, true, kBatchLoadFirst<NP>, kUseLists<G>>(c, k, iter, s_tour, sh);
+    construct_ant<G, NP, true, kBatchLoadFirst<NP>, kUseLists<G>, ALL>(c, k, iter, s_tour, sh);
 }
 
 template <int B>
@@ -658,11 +676,15 @@ __device__ __forceinline__ void batch_ant_flat(const Colony& c, int k, uint32_t 
     construct_ant_flat<B, (64 * B > kMinListCities)>(c, k, iter, s_tour, threadIdx.x);
 }
 
-template <int P8>
-__global__ __launch_bounds__(64) void k_construct_batch(const Colony* __restrict__ cols,
+// Rows of up to two passes keep to the scalar registers that eight wavefronts a
+// SIMD leave (asked for seven, the compiler stays below; asked for eight, it
+// makes the steps 1% longer; with a block of registers more, 16 instances of 400
+// cities take two rounds, 0.595 ms against 0.512).
+template <int P8, bool ALL>
+__global__ __launch_bounds__(64, P8 == 2 ? 7 : 1) void k_construct_batch(const Colony* __restrict__ cols,
                                                         const uint32_t* __restrict__ antmap) {
     extern __shared__ __align__(16) uint16_t s_tour[];
-    __shared__ __align__(16) AntShared<1024> sh;
+    __shared__ __align__(16) AntShared<kBatchStaged<ALL>> sh;
     const uint32_t e = antmap[blockIdx.x];
     const Colony c = cols[e >> 16];
     // One value for the whole workgroup.  Read through a pointer the kernel
@@ -675,18 +697,18 @@ __global__ __launch_bounds__(64) void k_construct_batch(const Colony* __restrict
         batch_ant_flat<1>(c, k, iter, s_tour);
     } else if (c.tile == 4) {
         const int np = __builtin_amdgcn_readfirstlane((c.n + 255) / 256);
-        batch_ant<4, 2, 4>(c, k, iter, np, s_tour, sh);
+        batch_ant<4, 2, 4, ALL>(c, k, iter, np, s_tour, sh);
     } else {
         const int np = __builtin_amdgcn_readfirstlane((c.n + 511) / 512);
-        batch_ant<8, 1, P8>(c, k, iter, np, s_tour, sh);
+        batch_ant<8, 1, P8, ALL>(c, k, iter, np, s_tour, sh);
     }
 }
 
-template <int G, int P>
+template <int G, int P, bool ALL>
 __global__ __launch_bounds__(64) void k_test_select(const float* rows, int ld, int n,
                                                      const uint8_t* feasible, const float* us,
                                                      int32_t* out) {
-    __shared__ __align__(16) AntShared<kStaged<G, P>> sh;
+    __shared__ __align__(16) AntShared<kStaged<G, P, ALL>> sh;
     const int lane = threadIdx.x;
     const int q = blockIdx.x;
     const uint8_t* f = feasible + (size_t)q * n;
@@ -707,7 +729,7 @@ __global__ __launch_bounds__(64) void k_test_select(const float* rows, int ld, i
     __syncthreads();
     // one row per query: the span is that row's n cities (rounded up to whole
     // 16-byte loads; the caller's padding columns are zero)
-    const int j = r64_pick<G, P, true>(rows + (size_t)q * ld, ((n + 3) & ~3) * 4, 0, ld * 4, n,
+    const int j = r64_pick<G, P, true, ALL>(rows + (size_t)q * ld, ((n + 3) & ~3) * 4, 0, ld * 4, n,
                                        lane_bits, vis, sh.T, sh.w, us[q], lane);
     if (lane == 0) out[q] = j;
 }
@@ -774,13 +796,21 @@ __global__ __launch_bounds__(64) void k_test_select_flat(const float* rows, int 
 constexpr int kBatchWgPerCu = 16;
 constexpr int kCapRounds = 8;
 
+constexpr int kComputeUnits = 256;
+
+// Whether a launch of `ants` ants keeps whole rows in LDS (kWriteAllPasses).
+bool whole_rows_in_lds(int ants) { return ants <= 12 * kComputeUnits; }
+
 }  // namespace
 
-size_t batch_lds_bytes(int max_n, int wg_per_cu, size_t lds_per_cu) {
-    const size_t tour = batch_ants_lds_bytes(max_n);
+size_t batch_lds_bytes(int max_n, int total_ants, int wg_per_cu, size_t lds_per_cu) {
+    const bool all = whole_rows_in_lds(total_ants);
+    const size_t tour = all ? batch_ants_lds_bytes<true>(max_n) : batch_ants_lds_bytes<false>(max_n);
     if (wg_per_cu <= 0 || lds_per_cu == 0) return tour;
     const size_t per_wg = lds_per_cu / (size_t)wg_per_cu;
-    const size_t fixed = sizeof(AntShared<1024>) + 64;  // static LDS and its alignment
+    // static LDS and its alignment
+    const size_t fixed = (all ? sizeof(AntShared<kBatchStaged<true>>)
+                              : sizeof(AntShared<kBatchStaged<false>>)) + 64;
     const size_t cap = per_wg > fixed ? (per_wg - fixed) & ~(size_t)255 : 0;
     return tour > cap ? tour : cap;
 }
@@ -794,13 +824,12 @@ namespace {
 // Whether rows of n cities at tile 8 keep the visited set as factors
 // (construct_masked.hpp) in a launch of m ants: where the ants fit the device
 // in one round.  An ant of P passes then holds 4 KB of LDS a pass beside its
-// tour, so that 16 (P = 1, 2) or 9 (P = 3) fit a compute unit, against 24 and
+// tour, so that 16 (P = 1, 2) or 9 (P = 3) fit a compute unit, against 28 and
 // more with the bits.  First iteration, factors / bits: n = 1000, m = 1000 0.492 /
-// 0.511 ms, 2560 0.704 / 0.733, 3072 0.799 / 0.778, 3840 1.23 / 0.91, 16384 3.94 /
-// 3.47; n = 1500, m = 1500 1.22 / 1.37, 2048 1.42 / 1.48, 2560 2.44 / 1.73.  Rows
+// 0.511 ms, 2560 0.704 / 0.733, 3500 0.946 / 0.865, 4096 1.27 / 0.91, 16384 3.91 /
+// 2.96; n = 1500, m = 1500 1.22 / 1.37, 2048 1.42 / 1.48, 2560 2.44 / 1.73.  Rows
 // of one pass are shorter with factors at any m (n = 512, m = 512 0.188 / 0.218,
 // 32768 2.02 / 2.08).
-constexpr int kComputeUnits = 256;
 bool masked_rows(int n, int m) {
     const int passes = (n + 511) / 512;
     return passes == 1 || (passes <= kMaxMaskedPasses && m <= 24 / passes * kComputeUnits);
@@ -817,13 +846,13 @@ hipError_t dispatch_flat(int n, F&& f) {
 }
 
 template <int G, int P>
-auto test_select_kernel() {
+auto test_select_kernel(bool all) {
     if constexpr (G == 0)
         return k_test_select_flat<P>;
     else if constexpr (G == 1)
         return k_test_select_masked<P>;
     else
-        return k_test_select<G, P>;
+        return all ? k_test_select<G, P, true> : k_test_select<G, P, false>;
 }
 
 template <int G>
@@ -835,7 +864,7 @@ template <int G, int P>
 auto construct_kernel() {
     if constexpr (G == 0)
         return k_construct_flat<P>;
-    else if constexpr (G == 1)
+    else if constexpr (G == 1 || (G == 8 && P == 1))  // one pass: always with factors
         return k_construct_masked<P>;
     else
         return k_construct<G, P>;
@@ -929,22 +958,22 @@ hipError_t launch_construct_batch(const Colony* cols, const uint32_t* antmap, in
                                   int max_n, size_t lds, hipStream_t s) {
     if (total_ants <= 0) return hipSuccess;
     if (max_n < 1 || max_n > kMaxCities) return hipErrorInvalidValue;
-    if (lds < batch_ants_lds_bytes(max_n)) return hipErrorInvalidValue;
-    static_assert(!kFlagsInStaging<8, 2, 1024> && !kFlagsInStaging<8, 8, 1024> &&
-                      kFlagsInStaging<8, 1, 1024> && kFlagsInStaging<8, 3, 1024> &&
-                      kFlagsInStaging<8, 7, 1024>,
-                  "batch_ant_lds_bytes");
+    const bool all = whole_rows_in_lds(total_ants);
+    if (lds < (all ? batch_ants_lds_bytes<true>(max_n) : batch_ants_lds_bytes<false>(max_n)))
+        return hipErrorInvalidValue;
     const int passes = (max_n + 511) / 512;
     const dim3 grid(total_ants), block(64);
-    if (passes <= 2)
-        hipLaunchKernelGGL(k_construct_batch<2>, grid, block, lds, s, cols, antmap);
-    else if (passes <= 4)
-        hipLaunchKernelGGL(k_construct_batch<4>, grid, block, lds, s, cols, antmap);
-    else if (passes <= 6)
-        hipLaunchKernelGGL(k_construct_batch<6>, grid, block, lds, s, cols, antmap);
-    else
-        hipLaunchKernelGGL(k_construct_batch<8>, grid, block, lds, s, cols, antmap);
-    return hipGetLastError();
+    const auto launch = [&]<int P8>() {
+        if (all)
+            hipLaunchKernelGGL((k_construct_batch<P8, true>), grid, block, lds, s, cols, antmap);
+        else
+            hipLaunchKernelGGL((k_construct_batch<P8, false>), grid, block, lds, s, cols, antmap);
+        return hipGetLastError();
+    };
+    if (passes <= 2) return launch.template operator()<2>();
+    if (passes <= 4) return launch.template operator()<4>();
+    if (passes <= 6) return launch.template operator()<6>();
+    return launch.template operator()<8>();
 }
 
 hipError_t launch_test_select(int tile, bool batched, int n, int count, const float* rows,
@@ -954,7 +983,7 @@ hipError_t launch_test_select(int tile, bool batched, int n, int count, const fl
     if (!tile_supported(tile, n)) return hipErrorInvalidValue;
     const int ld = (n + 63) & ~63;
     return dispatch_tile(tile, n, !batched, [&]<int G, int P>() {
-        hipLaunchKernelGGL((test_select_kernel<G, P>()), dim3(count), dim3(64), 0, s, rows, ld, n,
+        hipLaunchKernelGGL((test_select_kernel<G, P>(whole_rows_in_lds(count))), dim3(count), dim3(64), 0, s, rows, ld, n,
                            feasible, u, out);
         return hipGetLastError();
     });

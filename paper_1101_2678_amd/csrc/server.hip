@@ -337,7 +337,8 @@ aco_status aco_server_step(aco_server* s, int32_t* running_out) {
         if (e != hipSuccess) return server_fail(s, e, "aco_server_step");
         e = aco::launch_construct_batch(
             k.d_cols, k.d_antmap, k.total_ants, k.run_max_n,
-            aco::batch_lds_bytes(k.run_max_n, aco::batch_default_cap(k.total_ants, s->cus),
+            aco::batch_lds_bytes(k.run_max_n, k.total_ants,
+                                 aco::batch_default_cap(k.total_ants, s->cus),
                                  s->lds_per_cu),
             k.stream);
         if (e == hipSuccess) e = aco::launch_best_batch(k.d_cols, (int)k.running.size(), k.stream);

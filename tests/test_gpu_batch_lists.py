@@ -46,6 +46,12 @@ def test_long_batches_of_long_rows(sizes):
     check_batch([(n, 10) for n in sizes], 18)
 
 
+@pytest.mark.parametrize("ants", [3072, 3073])
+def test_long_batches_on_each_side_of_the_staging(ants):
+    """Batches of as many ants as keep whole rows in LDS, and of one more."""
+    check_batch([(600, 20), (400, 20), (1100, 20), (1024, 20), (100, ants - 80)], 20)
+
+
 def test_lists_behind_colonies_without():
     """The colonies of 600 and 330 cities at tile 4 and those of up to 256 have
     no lists, nor has the one of 400 with 8 ants; those of 700, 500 and 300 do."""

@@ -36,16 +36,20 @@ BATCHED = [255, 257, 320, 321, 385, 511, 512, 513, 1000, 1023, 1024, 1025, 1500,
 
 @pytest.mark.parametrize("n,tile", [(n, 8) for n in BATCHED] + [(n, 4) for n in BATCHED if n <= 1024])
 def test_select_batched(n, tile):
-    """The same rows through the batched launch's code, which keeps the bits."""
+    """The same rows through the batched launch's code, which keeps the bits, with
+    as many rows as a launch stores whole in LDS, and with more."""
     import torch
     from paper_1101_2678_amd import aco
     from test_gpu_parity import _adversarial_rows
 
-    rows, feas, u = _adversarial_rows(n, 1500, np.random.default_rng(9000 + n))
+    rows, feas, u = _adversarial_rows(n, 3073, np.random.default_rng(9000 + n))
     feas[::97] = 0  # no feasible city
     args = [torch.from_numpy(a).cuda() for a in (rows, feas, u)]
+    want = oracle.r64_select_batch(rows, feas, u)
     got = aco.test_select(*args, tile=tile, batched=True).cpu().numpy()
-    assert (got == oracle.r64_select_batch(rows, feas, u)).all()
+    assert (got == want).all()
+    got = aco.test_select(*[a[:3072] for a in args], tile=tile, batched=True).cpu().numpy()
+    assert (got == want[:3072]).all()
 
 
 def test_select_batched_non_monotone_prefix():
